@@ -20,7 +20,7 @@ HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
 def build(verbose: bool = False, extra_flags=None) -> str:
     """Compile every source with hipcc into paper_2304_05592_amd/libawe.so; returns its path."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    objs = []
+    objs, jobs = [], []   # one compiler per source, all at once
     build_dir = os.path.join(HERE, "_build")
     os.makedirs(build_dir, exist_ok=True)
     flags = HIP_FLAGS + list(extra_flags or [])
@@ -31,8 +31,13 @@ def build(verbose: bool = False, extra_flags=None) -> str:
         cmd = [hipcc] + flags + inc + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.run(cmd, check=True)
+        jobs.append((cmd, subprocess.Popen(cmd)))
         objs.append(obj)
+    for cmd, p in jobs:
+        p.wait()
+    for cmd, p in jobs:
+        if p.returncode:
+            raise subprocess.CalledProcessError(p.returncode, cmd)
     tmp = LIB + ".tmp"
     cmd = [hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs
     if verbose:

@@ -62,6 +62,7 @@ long long align256(long long x) { return (x + 255) & ~255LL; }
 // forward solves (and Born modelling) and one for its adjoint steps (reverse sweeps and F^T), so
 // that each direction runs the tile shape that suits its kernel.
 struct Tiling {
+  int tx = awe::kTX;      // tile columns
   int tz = 32;            // 2D tile rows
   int ty = 8, bz = 0;     // 3D tile rows in y and z-block length
   std::vector<TileDev> tiles;
@@ -89,6 +90,7 @@ struct awe_plan {
   int fuse2 = 0;          // 2D: two time levels per launch where the storage allows
                           // (bit 0: forward solves, bit 1: reverse sweeps)
   Tiling fw, rv;          // launch shapes of forward solves / adjoint steps
+  Tiling fw2, rv2;        // their tables for the two-level kernels, whose tiles are wider (rows: fw.tz, rv.tz)
   std::vector<awe_shot> shots;
   std::vector<double> rec_pos;    // copy of the problem's receiver rows
   std::vector<ShotDev> sd;
@@ -238,7 +240,7 @@ awe_status build_tiling(awe_plan* P, Tiling& T) {
   for (int s : order) {
     const awe_shot& sh = P->shots[s];
     const int TZ = tz_of(s);
-    ntx[s] = (sh.nx + awe::kTX - 1) / awe::kTX;
+    ntx[s] = (sh.nx + T.tx - 1) / T.tx;
     nty[s] = nd == 2 ? 1 : (sh.ny + TY - 1) / TY;
     ntz[s] = (sh.nz + TZ - 1) / TZ;
     first_tile[s] = (int)T.tiles.size();
@@ -247,7 +249,7 @@ awe_status build_tiling(awe_plan* P, Tiling& T) {
         for (int kx = 0; kx < ntx[s]; ++kx) {
           TileDev t{};
           t.shot = s;
-          t.x0 = kx * awe::kTX;
+          t.x0 = kx * T.tx;
           t.y0 = ky * TY;
           t.z0 = kz * TZ;
           T.tiles.push_back(t);
@@ -255,7 +257,7 @@ awe_status build_tiling(awe_plan* P, Tiling& T) {
   }
   if (T.tiles.size() > (size_t)0x7fffffff) return fail(AWE_ERR_UNSUPPORTED, "too many tiles");
   auto tile_of = [&](int s, int i, int j, int k) {
-    return first_tile[s] + ((k / tz_of(s)) * nty[s] + (j / TY)) * ntx[s] + i / awe::kTX;
+    return first_tile[s] + ((k / tz_of(s)) * nty[s] + (j / TY)) * ntx[s] + i / T.tx;
   };
   // groups' tile ranges and active prefixes
   const int G = (int)P->g_shot0.size();
@@ -368,11 +370,11 @@ awe_status build_tiling(awe_plan* P, Tiling& T) {
       const int i = (int)(ip.p % px), k = (int)(ip.p / px);
       const int TZ = T.tz;
       for (int kz = std::max(0, (k - TZ - kHalo) / TZ - 1); kz <= (k + kHalo) / TZ; ++kz) {
-        for (int kx = std::max(0, (i - awe::kTX - kHalo) / awe::kTX - 1); kx <= (i + kHalo) / awe::kTX; ++kx) {
+        for (int kx = std::max(0, (i - T.tx - kHalo) / T.tx - 1); kx <= (i + kHalo) / T.tx; ++kx) {
           if (kz >= ntz[ip.shot] || kx >= ntx[ip.shot]) continue;
-          const int x0 = kx * awe::kTX, z0 = kz * TZ;
+          const int x0 = kx * T.tx, z0 = kz * TZ;
           const int lx = i - (x0 - kHalo), lz = k - (z0 - kHalo);
-          if (lx < 0 || lx >= awe::kTX + 2 * kHalo || lz < 0 || lz >= TZ + 2 * kHalo) continue;
+          if (lx < 0 || lx >= T.tx + 2 * kHalo || lz < 0 || lz >= TZ + 2 * kHalo) continue;
           InjPoint e = ip;
           e.lx = lx;
           e.lz = lz;
@@ -437,24 +439,58 @@ awe_status upload_tiling(awe_plan* P, Tiling& T) {
   return AWE_OK;
 }
 
+// Two-level kernels exist for 8, 16, 24 and 32 rows (2D).
+bool two_level_rows(int tz) { return tz == 8 || tz == 16 || tz == 24 || tz == 32; }
+
+bool fused_ok(const awe_plan* P, int bit) {
+  const int tz = bit == AWE_FUSE_FORWARD ? P->fw.tz : P->rv.tz;
+  return P->ndim == 2 && (P->fuse2 & bit) && two_level_rows(tz);
+}
+
+// Does a direction in two-level mode also launch one-level kernels?  The levels of a 16-bit store
+// (quantised one level late) and the forward steps of a checkpointed gradient.
+bool one_level_too(const awe_plan* P, int bit) {
+  return (P->store.mode == AWE_STORE_FULL && P->store.prec != AWE_PREC_FP32) ||
+         (bit == AWE_FUSE_FORWARD && P->store.mode == AWE_STORE_CHECKPOINT);
+}
+
 // Shot groups and the tilings of the directions in `dirs` (bit 0 forward, bit 1 adjoint; the
-// groups change both, so a change of groups rebuilds both), built and uploaded.
+// groups change both, so a change of groups rebuilds both), built and uploaded: those of the kernels
+// the direction's calls can launch.
 awe_status rebuild(awe_plan* P, int dirs) {
   awe_status st = build_groups(P);
   if (st != AWE_OK) return st;
-  for (Tiling* T : {&P->fw, &P->rv}) {
-    if (!(dirs & (T == &P->fw ? 1 : 2))) continue;
-    if ((st = build_tiling(P, *T)) != AWE_OK) return st;
-    if ((st = upload_tiling(P, *T)) != AWE_OK) return st;
+  for (int bit : {AWE_FUSE_FORWARD, AWE_FUSE_ADJOINT}) {
+    if (!(dirs & bit)) continue;
+    Tiling& one = bit == AWE_FUSE_FORWARD ? P->fw : P->rv;
+    Tiling& two = bit == AWE_FUSE_FORWARD ? P->fw2 : P->rv2;
+    two.tx = awe::kTX2;
+    two.tz = one.tz;
+    const bool fused = fused_ok(P, bit);
+    for (Tiling* T : {&one, &two}) {
+      if (T == &two ? fused : !fused || one_level_too(P, bit)) {
+        if ((st = build_tiling(P, *T)) != AWE_OK) return st;
+        if ((st = upload_tiling(P, *T)) != AWE_OK) return st;
+      } else if (T->dev) {
+        (void)hipFree(T->dev);
+        T->dev = nullptr;
+      }
+    }
   }
   return AWE_OK;
 }
 
-// Launch arguments on the tables of tiling T (P->fw for forward solves and Born modelling,
-// P->rv for adjoint steps).
-awe::StepArgs base_args(const awe_plan* P, const Tiling& T, void* ws) {
+// The tables of a direction for calls that read no tiles.
+const Tiling& any_tiling(const awe_plan* P, int bit) {
+  if (bit == AWE_FUSE_FORWARD) return P->fw.dev ? P->fw : P->fw2;
+  return P->rv.dev ? P->rv : P->rv2;
+}
+
+// Launch arguments of a direction (AWE_FUSE_FORWARD: forward solves and Born modelling, AWE_FUSE_ADJOINT:
+// adjoint steps); each step puts its own tiling's tables in.
+awe::StepArgs base_args(const awe_plan* P, int bit, void* ws) {
   awe::StepArgs a{};
-  a.t = T.tab;
+  a.t = any_tiling(P, bit).tab;
   a.ws = static_cast<unsigned char*>(ws);
   a.ndim = P->ndim;
   a.nbl = P->nbl;
@@ -624,6 +660,7 @@ struct ProfRun {
 
 // Launch geometry of the current group at global step n on tiling T.
 void set_group(const awe_plan* P, const Tiling& T, awe::StepArgs& a, int n) {
+  a.t = T.tab;
   a.step = n;
   a.ntiles = T.g_active[P->cur][n];
   a.tile_base = T.g_tile0[P->cur];
@@ -657,32 +694,27 @@ awe_status step_adj(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s) {
   return AWE_OK;
 }
 
-// Two levels per launch (2D): forward levels n, n+1; adjoint levels n, n-1.
-awe_status step_fwd2(awe_plan* P, awe::StepArgs& a, int n, int store, hipStream_t s) {
-  set_group(P, P->fw, a, n + 1);
+// Two levels per launch (2D): forward levels n, n+1; adjoint levels n, n-1.  single: level n alone.
+awe_status step_fwd2(awe_plan* P, awe::StepArgs& a, int n, int store, hipStream_t s, bool single = false) {
+  const int last = single ? n : n + 1;
+  set_group(P, P->fw2, a, last);
   a.step = n;
+  a.single = single;
   if (a.ntiles <= 0) return AWE_OK;
-  if (awe_status st = check_step(P, P->fw, a, n, n + 1, "two-level forward step")) return st;
+  if (awe_status st = check_step(P, P->fw2, a, n, last, "two-level forward step")) return st;
   ProfScope ps(P, 0, s);
-  AWE_HIP(awe::launch_fwd2d2(a, P->fw.tz, store, s));
+  AWE_HIP(awe::launch_fwd2d2(a, P->fw2.tz, store, s));
   return AWE_OK;
 }
 
-awe_status step_adj2(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s) {
-  set_group(P, P->rv, a, n);
+awe_status step_adj2(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s, bool single = false) {
+  set_group(P, P->rv2, a, n);
+  a.single = single;
   if (a.ntiles <= 0) return AWE_OK;
-  if (awe_status st = check_step(P, P->rv, a, n - 1, n, "two-level adjoint step")) return st;
+  if (awe_status st = check_step(P, P->rv2, a, single ? n : n - 1, n, "two-level adjoint step")) return st;
   ProfScope ps(P, 1, s);
-  AWE_HIP(awe::launch_adj2d2(a, P->rv.tz, s));
+  AWE_HIP(awe::launch_adj2d2(a, P->rv2.tz, s));
   return AWE_OK;
-}
-
-// Two-level kernels exist for 8, 16, 24 and 32 rows (2D).
-bool two_level_rows(int tz) { return tz == 8 || tz == 16 || tz == 24 || tz == 32; }
-
-bool fused_ok(const awe_plan* P, int bit) {
-  const int tz = bit == AWE_FUSE_FORWARD ? P->fw.tz : P->rv.tz;
-  return P->ndim == 2 && (P->fuse2 & bit) && two_level_rows(tz);
 }
 
 // Forward levels 1..nsteps: one single step first when the count is odd, then pairs.
@@ -695,7 +727,7 @@ awe_status forward_loop(awe_plan* P, awe::StepArgs& a, int store, hipStream_t s)
   ProfRun run(P, s, 0);
   int n = 1;
   if (fuse && (P->nsteps & 1)) {
-    if ((st = step_fwd(P, a, 1, store, s)) != AWE_OK) return st;
+    if ((st = step_fwd2(P, a, 1, store, s, true)) != AWE_OK) return st;
     n = 2;
   }
   for (; n <= P->nsteps; n += fuse ? 2 : 1) {
@@ -713,7 +745,7 @@ awe_status adjoint_loop(awe_plan* P, awe::StepArgs& a, hipStream_t s) {
   ProfRun run(P, s, 1);
   int n = P->nsteps;
   if (fuse && (P->nsteps & 1)) {
-    if ((st = step_adj(P, a, n, s)) != AWE_OK) return st;
+    if ((st = step_adj2(P, a, n, s, true)) != AWE_OK) return st;
     n -= 1;
   }
   for (; n >= 1; n -= fuse ? 2 : 1) {
@@ -816,9 +848,10 @@ awe_status run_actions(awe_plan* P, awe::StepArgs& fa, awe::StepArgs& aa, size_t
       case awe::kReverse: {
         // a pair of reversals x, x-1 from one state runs as one two-level launch when the
         // adjoint fusion is on (both levels are read from the current state)
-        const bool two = fused_ok(P, AWE_FUSE_ADJOINT) && i + 1 < end && x >= 2 &&
-                         P->sched[3 * (i + 1)] == awe::kReverse && P->sched[3 * (i + 1) + 1] == x - 1;
-        awe_status st = two ? step_adj2(P, aa, x, s) : step_adj(P, aa, x, s);
+        const bool fused = fused_ok(P, AWE_FUSE_ADJOINT);
+        const bool two = fused && i + 1 < end && x >= 2 && P->sched[3 * (i + 1)] == awe::kReverse &&
+                         P->sched[3 * (i + 1) + 1] == x - 1;
+        awe_status st = fused ? step_adj2(P, aa, x, s, !two) : step_adj(P, aa, x, s);
         if (st != AWE_OK) return st;
         if (two) ++i;
         break;
@@ -1286,8 +1319,8 @@ awe_status awe_plan_workspace_size(const awe_plan* plan, size_t* bytes) {
 void awe_plan_destroy(awe_plan* plan) {
   if (!plan) return;
   for (hipEvent_t e : plan->prof_ev) (void)hipEventDestroy(e);
-  if (plan->fw.dev) (void)hipFree(plan->fw.dev);
-  if (plan->rv.dev) (void)hipFree(plan->rv.dev);
+  for (const Tiling* T : {&plan->fw, &plan->rv, &plan->fw2, &plan->rv2})
+    if (T->dev) (void)hipFree(T->dev);
   if (plan->chk_dev) (void)hipFree(plan->chk_dev);
   delete plan;
 }
@@ -1397,9 +1430,9 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
                                               (long long)P->sd[i].nt * awe::kScaleSlots * 4, s))
             return fail_out(hip_fail(e, "autotune fill"));
       }
-      awe::StepArgs fa = base_args(P, P->fw, ws);
+      awe::StepArgs fa = base_args(P, AWE_FUSE_FORWARD, ws);
       fa.q = q;
-      awe::StepArgs aa = base_args(P, P->rv, ws);
+      awe::StepArgs aa = base_args(P, AWE_FUSE_ADJOINT, ws);
       aa.dd = dd;
       aa.image_src = img;
       if (probed) {
@@ -1520,15 +1553,17 @@ awe_status awe_plan_set_groups(awe_plan* P, int32_t ngroups, int32_t* actual) {
 awe_status awe_plan_set_fusion(awe_plan* P, int32_t mode) {
   if (!P) return fail(AWE_ERR_INVALID_ARG, "plan is NULL");
   if (mode < 0 || mode > AWE_FUSE_BOTH) return fail(AWE_ERR_INVALID_ARG, "fusion mode must be 0..3");
+  const int changed = mode ^ P->fuse2;
   P->fuse2 = mode;
   // two-level kernels exist for 8, 16, 24 and 32 rows
-  awe_status st = AWE_OK;
   for (int bit : {AWE_FUSE_FORWARD, AWE_FUSE_ADJOINT}) {
     Tiling& T = bit == AWE_FUSE_FORWARD ? P->fw : P->rv;
-    if ((mode & bit) && !two_level_rows(T.tz))
-      if ((st = awe_plan_set_tiles_dir(P, bit, T.tz < 24 ? 16 : 32, T.ty, T.bz)) != AWE_OK) return st;
+    awe_status st = AWE_OK;
+    if ((mode & bit) && !two_level_rows(T.tz)) st = awe_plan_set_tiles_dir(P, bit, T.tz < 24 ? 16 : 32, T.ty, T.bz);
+    else if (changed & bit) st = rebuild(P, bit);
+    if (st != AWE_OK) return st;
   }
-  return st;
+  return AWE_OK;
 }
 
 awe_status awe_profile_enable(awe_plan* P, int64_t max_launches, int32_t stride) {
@@ -1590,12 +1625,12 @@ awe_status awe_forward(awe_plan* P, const float* m, const float* q, float* d, in
   const bool store = keep && (P->store.mode == AWE_STORE_FULL || P->store.mode == AWE_STORE_CHECKPOINT);
   P->kept_ws = nullptr;
   if ((st = prepare(P, m, ws, true, false, s)) != AWE_OK) return st;
-  awe::StepArgs a = base_args(P, P->fw, ws);
+  awe::StepArgs a = base_args(P, AWE_FUSE_FORWARD, ws);
   a.q = q;
   a.d = d;
   const int G = (int)P->g_nshot.size();
   if (store && P->store.mode == AWE_STORE_CHECKPOINT) {
-    awe::StepArgs aa = base_args(P, P->rv, ws);  // no adjoint step runs before the first reverse
+    awe::StepArgs aa = base_args(P, AWE_FUSE_ADJOINT, ws);  // no adjoint step runs before the first reverse
     for (P->cur = 0; P->cur < G; ++P->cur)
       if ((st = run_actions(P, a, aa, 0, P->sched_first_reverse, s)) != AWE_OK) return st;
   } else {
@@ -1640,9 +1675,9 @@ awe_status awe_backward(awe_plan* P, const float* m, const float* q, const float
   if (g)
     for (int i = 0; i < P->nshot; ++i)
       if ((st = fill(P, w, P->sd[i].acc, P->sd[i].npts * 8, s, "accumulator")) != AWE_OK) return st;
-  awe::StepArgs fa = base_args(P, P->fw, ws);
+  awe::StepArgs fa = base_args(P, AWE_FUSE_FORWARD, ws);
   fa.q = q;
-  awe::StepArgs aa = base_args(P, P->rv, ws);
+  awe::StepArgs aa = base_args(P, AWE_FUSE_ADJOINT, ws);
   aa.dd = dd;
   aa.v = v;
   if (P->store.mode == AWE_STORE_FULL) {
@@ -1659,7 +1694,7 @@ awe_status awe_backward(awe_plan* P, const float* m, const float* q, const float
   }
   if (v) AWE_HIP(awe::launch_src_last(aa, P->nshot, s));
   if (g)
-    AWE_HIP(awe::launch_grad_reduce(P->rv.tab, (int)P->wins.size(), P->max_win_npts, w, g,
+    AWE_HIP(awe::launch_grad_reduce(any_tiling(P, AWE_FUSE_ADJOINT).tab, (int)P->wins.size(), P->max_win_npts, w, g,
                                     -1.0 / (P->dt * P->dt), s));
   if ((P->checks & AWE_CHECK_OUTPUTS) && (g || v) &&
       (st = screen(P, {{g, true, kPerWindow, "g", false}, {v, false, kPerShotQ, "v", false}}, s)) != AWE_OK)
@@ -1711,7 +1746,7 @@ awe_status awe_gradient_probed(awe_plan* P, const float* m, const float* q, cons
   for (int i = 0; i < P->nshot; ++i)
     if ((st = fill(P, wsb, P->sd[i].store, (long long)r * 2 * P->sd[i].npts * 8, s, "probe sums")) != AWE_OK) return st;
   // forward sweep: B_j += C[j][k] (u^k - 2u^{k-1} + u^{k-2}) in the step kernels
-  awe::StepArgs a = base_args(P, P->fw, ws);
+  awe::StepArgs a = base_args(P, AWE_FUSE_FORWARD, ws);
   a.q = q;
   a.d = d;
   a.probe_c = C;
@@ -1721,7 +1756,7 @@ awe_status awe_gradient_probed(awe_plan* P, const float* m, const float* q, cons
     if ((st = forward_loop(P, a, awe::kStoreProbe, s)) != AWE_OK) return st;
   if (d) AWE_HIP(awe::launch_gather_last(a, P->nshot, P->total_recs, 0, s));
   // reverse sweep: A_j += C[j][k] w^k in the adjoint step kernels
-  awe::StepArgs aa = base_args(P, P->rv, ws);
+  awe::StepArgs aa = base_args(P, AWE_FUSE_ADJOINT, ws);
   aa.dd = dd;
   aa.v = v;
   aa.image_src = awe::kImgProbe;
@@ -1731,7 +1766,7 @@ awe_status awe_gradient_probed(awe_plan* P, const float* m, const float* q, cons
   for (P->cur = 0; P->cur < (int)P->g_nshot.size(); ++P->cur)
     if ((st = adjoint_loop(P, aa, s)) != AWE_OK) return st;
   if (v) AWE_HIP(awe::launch_src_last(aa, P->nshot, s));
-  AWE_HIP(awe::launch_probe_reduce(P->rv.tab, (int)P->wins.size(), P->max_win_npts, wsb, r, w, g,
+  AWE_HIP(awe::launch_probe_reduce(any_tiling(P, AWE_FUSE_ADJOINT).tab, (int)P->wins.size(), P->max_win_npts, wsb, r, w, g,
                                    -1.0 / (P->dt * P->dt), s));
   if ((P->checks & AWE_CHECK_OUTPUTS) &&
       (st = screen(P, {{g, true, kPerWindow, "g", false}, {v, false, kPerShotQ, "v", false},
@@ -1751,7 +1786,7 @@ awe_status awe_adjoint(awe_plan* P, const float* m, const float* dd, float* v, v
     return st;
   P->kept_ws = nullptr;
   if ((st = prepare(P, m, ws, false, true, s)) != AWE_OK) return st;
-  awe::StepArgs a = base_args(P, P->rv, ws);
+  awe::StepArgs a = base_args(P, AWE_FUSE_ADJOINT, ws);
   a.dd = dd;
   a.v = v;
   a.image_src = awe::kImgNone;
@@ -1775,7 +1810,7 @@ awe_status awe_born(awe_plan* P, const float* m, const float* q, const float* dm
     return st;
   P->kept_ws = nullptr;
   if ((st = prepare(P, m, ws, true, true, s)) != AWE_OK) return st;
-  awe::StepArgs a = base_args(P, P->fw, ws);
+  awe::StepArgs a = base_args(P, AWE_FUSE_FORWARD, ws);
   a.q = q;
   a.dm = dm;
   a.d = dd;
@@ -1786,14 +1821,16 @@ awe_status awe_born(awe_plan* P, const float* m, const float* q, const float* dm
     ProfRun run(P, s, 2);
     for (int n = 1; n <= P->nsteps;) {
       const bool two = fuse && (n > 1 || !(P->nsteps & 1));
-      set_group(P, P->fw, a, two ? n + 1 : n);
+      const Tiling& T = fuse ? P->fw2 : P->fw;
+      set_group(P, T, a, two ? n + 1 : n);
       a.step = n;
+      a.single = !two;
       if (a.ntiles > 0) {
-        if ((st = check_step(P, P->fw, a, n, two ? n + 1 : n, "Born step")) != AWE_OK) return st;
+        if ((st = check_step(P, T, a, n, two ? n + 1 : n, "Born step")) != AWE_OK) return st;
         ProfScope ps(P, 2, s);
-        if (P->ndim == 3) AWE_HIP(awe::launch_born3d(a, P->fw.ty, P->fw.bz, s));
-        else if (two) AWE_HIP(awe::launch_born2d2(a, P->fw.tz, s));
-        else AWE_HIP(awe::launch_born2d(a, P->fw.tz, s));
+        if (P->ndim == 3) AWE_HIP(awe::launch_born3d(a, T.ty, T.bz, s));
+        else if (fuse) AWE_HIP(awe::launch_born2d2(a, T.tz, s));
+        else AWE_HIP(awe::launch_born2d(a, T.tz, s));
       }
       n += two ? 2 : 1;
     }

@@ -12,7 +12,8 @@
 namespace awe {
 
 constexpr int kThreads = 256;   // 4 wave64 per workgroup
-constexpr int kTX = 64;         // 2D tile width: one wavefront spans the tile row
+constexpr int kTX = 64;         // tile width: one wavefront spans the tile row (one column per lane)
+constexpr int kTX2 = 128;       // tile width of the 2D two-level kernels (two columns per lane)
 constexpr int kHalo = 4;        // stencil radius (8th order)
 constexpr int kPitch = 64;      // workspace rows are padded to a multiple of 64 elements, so
                                 // that every 64-column row segment starts on a 256-byte line
@@ -138,6 +139,7 @@ struct StepArgs {
   int shot_base;             // first position in t.order of the group (per-shot kernels)
   int rs_level;              // global state restored by reference from FP32 slot rs_slot
   int rs_slot;               //   (kNoLevel: none); see fwd_level
+  int single;                // two-level kernels: produce level `step` alone
   int st_slot;               // 2D forward: also write (u^k, u^{k-1}) into this FP32 slot (-1: no)
   int nbl;
   int store_prec;            // Prec of the kept wavefield (FULL store / checkpoint slots)
@@ -208,7 +210,8 @@ hipError_t launch_fwd2d(const StepArgs& a, int tz, int store, hipStream_t stream
 // Quantise the last forward level u^{nt-1} of every shot into the scaled FULL store.
 hipError_t launch_store_last(const StepArgs& a, int nshot, long long max_npts, hipStream_t stream);
 hipError_t launch_adj2d(const StepArgs& a, int tz, hipStream_t stream);
-// Two 2D steps per launch (levels step, step+1 forward; step, step-1 adjoint); tz 8, 16 or 32.
+// Two 2D steps per launch (levels step, step+1 forward; step, step-1 adjoint); tz 8, 16, 24 or 32,
+// on tiles kTX2 wide.
 hipError_t launch_fwd2d2(const StepArgs& a, int tz, int store, hipStream_t stream);
 hipError_t launch_adj2d2(const StepArgs& a, int tz, hipStream_t stream);
 hipError_t launch_born2d(const StepArgs& a, int tz, hipStream_t stream);

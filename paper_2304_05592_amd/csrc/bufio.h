@@ -105,6 +105,14 @@ __device__ __forceinline__ unsigned short ldp16_nt(const Planes& f, int voff, in
   return ldb16_nt(f.r, voff, slice_off(f, z));
 }
 __device__ __forceinline__ double ldp64(const Planes& f, int voff, int z) { return ldb64(f.r, voff, slice_off(f, z)); }
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f64x2 ldp64x2(const Planes& f, int voff, int z) {
+  return __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(f.r, voff, slice_off(f, z), 0));
+}
+__device__ __forceinline__ void stb64x2(brsrc r, f64x2 v, int voff, int soff) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, v), r, voff,
+                                         soff, 0);
+}
 __device__ __forceinline__ double ldp64_nt(const Planes& f, int voff, int z) {
   return ldb64_nt(f.r, voff, slice_off(f, z));
 }

@@ -160,6 +160,10 @@ __device__ __forceinline__ float step_incr(float u, float um2, float cfv, float 
   return cfv * (lap - eta * (u - um2));
 }
 
+// Source term weight * sample, fused explicitly: left to the compiler, a product hoisted out of the
+// source's condition would be rounded by itself in some kernels and not in others.
+__device__ __forceinline__ float add_source(float lap, float w, float q) { return __builtin_fmaf(w, q, lap); }
+
 template <int TZ>
 __device__ __forceinline__ float lap_at(const float (*L)[T2<TZ>::W], int lr, int lc,
                                         const float* c) {
@@ -276,7 +280,7 @@ __global__ __launch_bounds__(T2<TZ>::NT) void fwd2d_kernel(StepArgs a) {
     const int bx = x - src_i, bz = z - src_k;
     if ((unsigned)bx < 2u && (unsigned)bz < 2u) {
       const int w = bx + 2 * bz;
-      lap += (w == 0 ? sw0 : w == 1 ? sw1 : w == 2 ? sw2 : sw3) * qk;
+      lap = add_source(lap, w == 0 ? sw0 : w == 1 ? sw1 : w == 2 ? sw2 : sw3, qk);
     }
     const int dz = border_dist(z, nz, a.nbl);
     const float eta = a.eta_dt * (float)(dx * dx + dz * dz);
@@ -474,7 +478,7 @@ __global__ __launch_bounds__(T2<TZ>::NT) void born2d_kernel(StepArgs a) {
     const int bx = x - src_i, bz = z - src_k;
     if ((unsigned)bx < 2u && (unsigned)bz < 2u) {
       const int w = bx + 2 * bz;
-      lap += (w == 0 ? sw0 : w == 1 ? sw1 : w == 2 ? sw2 : sw3) * qk;
+      lap = add_source(lap, w == 0 ? sw0 : w == 1 ? sw1 : w == 2 ? sw2 : sw3, qk);
     }
     const float incr = pcf[i] * (lap - eta * (u - pu2[i]));
     stb(ruo, (u + u - pu2[i]) + incr, cx, zo);
@@ -487,102 +491,245 @@ __global__ __launch_bounds__(T2<TZ>::NT) void born2d_kernel(StepArgs a) {
 }
 
 // ------------------------------------------------------------------------------ two steps per launch
-// Level n-1 is staged with an 8-cell halo (LDS L1); the first step computes level n on the
-// tile plus a 4-cell halo (LDS LE: everything the second step's stencil needs), the second
-// step computes level n+1 (forward) or n-1 (adjoint) on the tile.  Both steps do exactly the
-// arithmetic of the one-step kernels, in the same order, so results are bitwise identical;
-// HBM traffic per two steps falls from 2 x (3 reads + 1 write) to 3 reads + 2 writes.
+// A tile of TZ rows x 128 columns.  Level n-1 is staged with an 8-cell halo (LDS L1); the first
+// step computes level n on the tile plus a 4-cell halo (LDS LE: everything the second step's
+// stencil needs), the second step computes level n+1 (forward) or n-1 (adjoint) on the tile.  Both
+// steps do exactly the arithmetic of the one-step kernels, in the same order, so results are
+// bitwise identical; HBM traffic per two steps falls from 2 x (3 reads + 1 write) to 3 reads +
+// 2 writes.
+//
+// These kernels issue vector instructions most of their time (a launch without a store, its fields
+// in the last-level cache, ran at the vector units' rate with 93 lane-operations per point and
+// level), so the work per point is cut: a lane owns two adjacent columns (8-byte global and LDS
+// accesses, one set of address and row work for two points) and RA or RB consecutive rows, whose
+// z-neighbours it reads from LDS once (N + 8 reads for N rows instead of 9 N); along x a difference
+// u(b) - u(a) that serves the stencils of both points is formed once.  A row of the tile is one
+// wave, so row offsets stay wave-uniform.  Rows are kept apart for the scheduler: mixed, they took 125
+// registers instead of 80 (24-row forward) and lost more to occupancy than they gained.
+// Measured, 16 shots of 730 x 421, per launch of two levels, against one column per lane on tiles of
+// 64 columns: forward without store 23.4 -> 20.9 us, with FP32 store 24.7 -> 22.9, reverse with
+// imaging 41.4 -> 39.3.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ f32x2 ldp2(const Planes& f, int voff, int z) {
+  return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(f.r, voff, slice_off(f, z), 0));
+}
+__device__ __forceinline__ f32x2 ldp2_nt(const Planes& f, int voff, int z) {
+  return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(f.r, voff, slice_off(f, z), kNT));
+}
+__device__ __forceinline__ f32x2 ldp2_at(const Planes& f, int off) {
+  return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(f.r, off, f.nzv > 0 ? 0 : kZOOB, 0));
+}
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void stb2(brsrc r, f32x2 v, int voff, int soff) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
+}
+__device__ __forceinline__ void stb2_nt(brsrc r, f32x2 v, int voff, int soff) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, kNT);
+}
+
 template <int TZ>
 struct F2 {
-  static constexpr int W1 = kTX + 4 * kHalo;      // 80: level n-1 with an 8-cell halo
+  static constexpr int W1 = kTX2 + 4 * kHalo;     // 144: level n-1 with an 8-cell halo
   static constexpr int H1 = TZ + 4 * kHalo;
-  static constexpr int WE = kTX + 2 * kHalo;      // 72: first-step level on tile + 4
+  static constexpr int WE = kTX2 + 2 * kHalo;     // 136: first-step level on tile + 4
   static constexpr int HE = TZ + 2 * kHalo;
-  static constexpr int NW = TZ >= 16 ? 8 : 4;    // waves per workgroup
+  static constexpr int NW = 8;                    // waves per workgroup
   static constexpr int NT = 64 * NW;
-  static constexpr int RPT = TZ / NW;                // tile rows per thread
-  static_assert(TZ % NW == 0, "tile rows must split evenly over the waves");
-  // first-step points of a thread: NB in the 64 body columns (one wave per row, aligned
-  // 256-byte rows), NH in the 4 + 4 side columns of every row
-  static constexpr int NB = HE / NW;
-  static_assert(HE % NW == 0, "extended rows must split evenly over the waves");
-  static constexpr int NH = (2 * kHalo * HE + NT - 1) / NT;
-  static constexpr int NS = NB + NH;
+  static constexpr int RA = HE / NW;              // first-step rows of a wave (128 body columns)
+  static constexpr int RB = TZ / NW;              // second-step rows of a wave
+  static_assert(HE % NW == 0 && TZ % NW == 0, "rows must split evenly over the waves");
+  // column pairs in the halo columns: NSE of the first step (4 + 4 columns of HE rows), NS1 of the
+  // staged level (8 + 8 columns of H1 rows); thread t takes pair t
+  static constexpr int NSE = HE * kHalo, NS1 = H1 * 2 * kHalo;
+  static constexpr int MS1 = (NS1 + NT - 1) / NT;
+  static_assert(NSE <= NT, "one halo pair per thread");
 };
 
-// Slot i of this thread among the first-step points (row r, column c of the WE x HE region);
-// false for an unused slot (its r, c are then a valid point, not to be written).
+// Row and column of pair e of the halo columns of a region with HW halo columns per side.
+template <int HW>
+__device__ __forceinline__ void side_pair(int e, int* r, int* c) {
+  *r = e / HW;
+  const int k = 2 * (e - *r * HW);
+  *c = k < HW ? k : kTX2 + k;
+}
+
+// Level n-1 with an 8-cell halo: rows z0-8 .. z0+TZ+7, whole rows per wave plus the halo pairs.
+// Issue before the other prefetches, commit to LDS (see Staged).
 template <int TZ>
-__device__ __forceinline__ bool ext_slot(int i, int* r, int* c) {
+struct Tile8 {
   using G = F2<TZ>;
-  if (i < G::NB) {       // body slots: every row of the extended region is a whole wave's row
-    *r = wave_id() + i * G::NW;
-    *c = kHalo + (int)(threadIdx.x & 63);
-    return true;
-  }
-  const int e0 = (int)threadIdx.x + (i - G::NB) * G::NT;
-  const int e = min(e0, 2 * kHalo * G::HE - 1);
-  *r = e / (2 * kHalo);
-  const int cc = e - *r * (2 * kHalo);
-  *c = cc < kHalo ? cc : kTX + cc;
-  return e0 < 2 * kHalo * G::HE;
-}
+  static constexpr int NB = G::H1 / G::NW;
+  static_assert(G::H1 % G::NW == 0, "staged rows must split evenly over the waves");
+  f32x2 vb[NB], vh[G::MS1];
 
-template <int TZ>
-using Side8 = SideHalo<F2<TZ>::NT, F2<TZ>::H1, 2 * kHalo>;
-
-// Level n-1 with an 8-cell halo (two-step kernels): issue, then commit to LDS.
-template <int TZ>
-using Tile8 = Staged<F2<TZ>::NT, F2<TZ>::NW, F2<TZ>::H1, 2 * kHalo>;
-
-template <int TZ>
-__device__ __forceinline__ void tile8_issue(Tile8<TZ>& t, const Planes& f, int cx, const int (&ho)[Side8<TZ>::NH],
-                                            int z0) {
-  stage_issue<F2<TZ>::NT, F2<TZ>::NW, F2<TZ>::H1, 2 * kHalo>(t, f, cx, ho, z0);
-}
-
-template <int TZ>
-__device__ __forceinline__ void tile8_commit(float (*L)[F2<TZ>::W1], const Tile8<TZ>& t) {
-  stage_commit<F2<TZ>::NT, F2<TZ>::NW, F2<TZ>::H1, 2 * kHalo, F2<TZ>::W1>(L, t);
-}
-
-// Plane offsets of this thread's first-step points that lie in the 4 + 4 side columns (the
-// extended slots past the NB body slots); kOOB outside the grid or for an unused slot.
-template <int TZ>
-__device__ __forceinline__ void ext_offsets(int (&eo)[F2<TZ>::NH], int nx, int nz, int px, int x0, int z0) {
-  using G = F2<TZ>;
+  __device__ __forceinline__ void issue(const Planes& f, int cx, int x0, int z0, int nx, int nz, int px) {
+    const int wv = wave_id();
 #pragma unroll
-  for (int i = 0; i < G::NH; ++i) {
-    int r, c;
-    const bool ok = ext_slot<TZ>(G::NB + i, &r, &c);
-    eo[i] = ok ? col_off(x0 - kHalo + c, z0 - kHalo + r, nx, nz, px, 4) : kOOB;
+    for (int i = 0; i < NB; ++i) vb[i] = ldp2(f, cx, z0 - 2 * kHalo + wv + i * G::NW);
+#pragma unroll
+    for (int i = 0; i < G::MS1; ++i) {
+      int r, c;
+      side_pair<2 * kHalo>(min((int)threadIdx.x + i * G::NT, G::NS1 - 1), &r, &c);
+      vh[i] = ldp2_at(f, col_off(x0 - 2 * kHalo + c, z0 - 2 * kHalo + r, nx, nz, px, 4));
+    }
+  }
+  __device__ __forceinline__ void commit(float (*L)[G::W1]) const {
+    const int lane = threadIdx.x & 63, wv = wave_id();
+#pragma unroll
+    for (int i = 0; i < NB; ++i) *reinterpret_cast<f32x2*>(&L[wv + i * G::NW][2 * kHalo + 2 * lane]) = vb[i];
+    // unconditional: threads past the last pair write that pair again (see stage_commit)
+#pragma unroll
+    for (int i = 0; i < G::MS1; ++i) {
+      int r, c;
+      side_pair<2 * kHalo>(min((int)threadIdx.x + i * G::NT, G::NS1 - 1), &r, &c);
+      *reinterpret_cast<f32x2*>(&L[r][c]) = vh[i];
+    }
+  }
+};
+
+// Laplacians of the column pair at p (an LDS array of row stride W) in N consecutive rows, p at
+// the first; u receives the centre values.  The order of each sum is that of lap_ptr; along x a
+// difference is formed once for the two points it belongs to ((a - u) + (b - u) = (b - u) - (u - a)).
+template <int N, int W>
+__device__ __forceinline__ void lap_pairs(const float* p, f32x2 (&lap)[N], f32x2 (&u)[N], const float* c) {
+  f32x2 P[N + 2 * kHalo];
+#pragma unroll
+  for (int i = 0; i < N + 2 * kHalo; ++i) P[i] = *reinterpret_cast<const f32x2*>(p + (i - kHalo) * W);
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    __builtin_amdgcn_sched_barrier(0);   // one row after the other
+    const float* q = p + n * W;
+    float X[2 * kHalo + 2];        // columns x-4 .. x+5
+#pragma unroll
+    for (int k = 0; k < 2 * kHalo + 2; k += 2) {
+      const f32x2 v = k == kHalo ? P[n + kHalo] : *reinterpret_cast<const f32x2*>(q + k - kHalo);
+      X[k] = v.x;
+      X[k + 1] = v.y;
+    }
+    u[n] = P[n + kHalo];
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int r = kHalo; r >= 1; --r) {
+      float D[2 * kHalo + 2];      // D[k] = X[k + r] - X[k] at k = 4, 5 and r to their left
+#pragma unroll
+      for (int k = kHalo - r; k < kHalo + 2; ++k) D[k] = X[k + r] - X[k];
+      s0 += c[r] * (D[kHalo] - D[kHalo - r]);
+      s0 += c[r] * ((P[n + kHalo - r].x - P[n + kHalo].x) + (P[n + kHalo + r].x - P[n + kHalo].x));
+      s1 += c[r] * (D[kHalo + 1] - D[kHalo + 1 - r]);
+      s1 += c[r] * ((P[n + kHalo - r].y - P[n + kHalo].y) + (P[n + kHalo + r].y - P[n + kHalo].y));
+    }
+    lap[n] = f32x2{s0, s1};
   }
 }
 
-// Load of a first-step point: body slots read the row z0-4+r (wave-uniform) at column offset cx,
-// side slots their own offset.
-template <int TZ>
-__device__ __forceinline__ float ld_ext(const Planes& f, int i, int cx, const int (&eo)[F2<TZ>::NH], int z0) {
-  using G = F2<TZ>;
-  if (i < G::NB) return ldp(f, cx, z0 - kHalo + wave_id() + i * G::NW);
-  return ldp_at(f, eo[i - G::NB]);
+// eta / dt of a column pair (dx2: the columns' squared border distances) at row z.
+struct Damp {
+  float x0, x1;
+  __device__ __forceinline__ Damp(int x, int nx, int nbl) {
+    x0 = (float)border_dist(x, nx, nbl);
+    x1 = (float)border_dist(x + 1, nx, nbl);
+    x0 *= x0;
+    x1 *= x1;
+  }
+};
+
+// One update of a column pair: (increment, new level).  The sum of the squared distances is the
+// integers' sum bit for bit (both far below 2^24).
+__device__ __forceinline__ void step_pair(f32x2 u, f32x2 um2, f32x2 cf, f32x2 lap, const Damp& d, int dz, float eta_dt,
+                                          f32x2* incr, f32x2* un) {
+  const float fz = (float)dz * (float)dz;
+  incr->x = step_incr(u.x, um2.x, cf.x, lap.x, eta_dt * (d.x0 + fz));
+  incr->y = step_incr(u.y, um2.y, cf.y, lap.y, eta_dt * (d.x1 + fz));
+  un->x = (u.x + u.x - um2.x) + incr->x;
+  un->y = (u.y + u.y - um2.y) + incr->y;
+}
+
+// Source term of a column pair at (x, z).
+struct Source {
+  int i, k;
+  float w0, w1, w2, w3;
+  __device__ __forceinline__ explicit Source(const ShotDev& S)
+      : i(S.src_i), k(S.src_k), w0(S.src_w[0]), w1(S.src_w[1]), w2(S.src_w[2]), w3(S.src_w[3]) {}
+  __device__ __forceinline__ void add(f32x2* lap, int x, int z, float q) const {
+    if ((unsigned)(z - k) < 2u) {
+      const float a = z == k ? w0 : w2, b = z == k ? w1 : w3;
+      if (x == i) {
+        lap->x = add_source(lap->x, a, q);
+        lap->y = add_source(lap->y, b, q);
+      } else if (x == i - 1) {
+        lap->y = add_source(lap->y, a, q);
+      } else if (x == i + 1) {
+        lap->x = add_source(lap->x, b, q);
+      }
+    }
+  }
+};
+
+// probe_add for a column pair: the pair's sums j are adjacent (16 bytes; x is even, and a pair's
+// second column may lie in the row's padding, whose terms are zero).
+__device__ __forceinline__ void probe_add2(double* sum, int r, const float* c1, f32x2 v1, bool t1, const float* c2,
+                                           f32x2 v2, bool t2, long long pitch) {
+  constexpr int kGroup = 4;   // sums in flight: as many bytes as probe_add's
+  for (int j0 = 0; j0 < r; j0 += kGroup) {
+    f64x2 t[kGroup];
+    const int n = min(r - j0, kGroup);
+    f64x2* s = reinterpret_cast<f64x2*>(sum + j0 * 64);
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u)
+      if (u < n) t[u] = __builtin_nontemporal_load(s + u * 32);
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u)
+      if (u < n) {
+        if (t1) {
+          const double c = c1[(j0 + u) * pitch];
+          t[u].x += c * (double)v1.x;
+          t[u].y += c * (double)v1.y;
+        }
+        if (t2) {
+          const double c = c2[(j0 + u) * pitch];
+          t[u].x += c * (double)v2.x;
+          t[u].y += c * (double)v2.y;
+        }
+      }
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u)
+      if (u < n) __builtin_nontemporal_store(t[u], s + u * 32);
+  }
+}
+
+template <int W>
+__device__ __forceinline__ float interp_at(const float (*L)[W], int R, int C, const float* w) {
+  return w[0] * L[R][C] + w[1] * L[R][C + 1] + w[2] * L[R + 1][C] + w[3] * L[R + 1][C + 1];
+}
+
+// Samples the tile's receivers from an LDS level whose cell (0, 0) is the grid point (zl, xl).
+template <int NT, int W>
+__device__ __forceinline__ void gather(const StepArgs& a, const TileDev& T, const ShotDev& S, const float (*L)[W],
+                                       int zl, int xl, int level) {
+  for (int t = threadIdx.x; t < T.gat_count; t += NT) {
+    const RecDev R = a.t.recs[T.gat_begin + t];
+    a.d[S.d + (long long)level * S.nrec + R.r] = interp_at<W>(L, R.k - zl, R.i - xl, R.w);
+  }
 }
 
 // Forward: levels k and k+1 (k = step - off); SK = kStoreNone, kStoreF32 or kStoreProbe (both
 // levels' increments added to the probe sums in one FP64 read-modify-write, level k first).
+// a.single: level k alone.
 template <int TZ, int SK>
 __global__ __launch_bounds__(F2<TZ>::NT) void fwd2d2_kernel(StepArgs a) {
   using G = F2<TZ>;
   constexpr bool PRB = SK == kStoreProbe;
-  __shared__ float L1[G::H1][G::W1];
-  __shared__ float LE[G::HE][G::WE];
-  __shared__ float INC1[PRB ? TZ : 1][kTX];  // probe: level k's increment on the tile
+  constexpr int RA = G::RA, RB = G::RB;
+  __shared__ __align__(16) float L1[G::H1][G::W1];
+  __shared__ __align__(16) float LE[G::HE][G::WE];
+  __shared__ __align__(16) float INC1[PRB ? TZ : 1][kTX2];  // probe: level k's increment on the tile
   const int tid = xcd_tile(blockIdx.x, a.ntiles);
   const TileDev T = a.t.tiles[a.tile_base + tid];
   const ShotDev& S = a.t.shots[T.shot];
   const int k = a.step - S.off;
   const bool act1 = k >= 1 && k <= S.nt - 1;
-  const bool act2 = k + 1 >= 1 && k + 1 <= S.nt - 1;
+  const bool act2 = !a.single && k + 1 >= 1 && k + 1 <= S.nt - 1;
   if (!act1 && !act2) return;
   const int nx = S.nx, nz = S.nz, px = S.px;
   const int row4 = 4 * px;
@@ -597,137 +744,140 @@ __global__ __launch_bounds__(F2<TZ>::NT) void fwd2d2_kernel(StepArgs a) {
   const brsrc ro1 = make_rsrc(fbuf(a.ws, S, fwd_buf(k)), act1 ? nz * row4 : 0);
   const brsrc ro2 = make_rsrc(fbuf(a.ws, S, fwd_buf(k + 1)), act2 ? nz * row4 : 0);
   float* st = reinterpret_cast<float*>(a.ws + S.store);
-  const brsrc rs1 = make_rsrc(st + (long long)(SK == kStoreF32 ? k : 0) * npts,
+  const brsrc rs1 = make_rsrc(st + (long long)(SK == kStoreF32 && act1 ? k : 0) * npts,
                               SK == kStoreF32 && act1 ? nz * row4 : 0);
-  const brsrc rs2 = make_rsrc(st + (long long)(SK == kStoreF32 ? k + 1 : 0) * npts,
+  const brsrc rs2 = make_rsrc(st + (long long)(SK == kStoreF32 && act2 ? k + 1 : 0) * npts,
                               SK == kStoreF32 && act2 ? nz * row4 : 0);
   const int lane = threadIdx.x & 63, wv = wave_id();
-  const int x = T.x0 + lane;
+  const int x = T.x0 + 2 * lane;
   const int cx = x < nx ? 4 * x : kOOB;
+  const int zE = T.z0 - kHalo;           // row 0 of the first-step region
 
-  // the level k-1 tile first, then level k-2 and coef of this thread's extended points and coef
+  // the level k-1 tile first, then level k-2 and coef of this thread's first-step points and coef
   // of its tile points
-  int ho[Side8<TZ>::NH];
-  side_offsets<G::NT, G::H1, 2 * kHalo>(ho, nx, nz, px, T.x0, T.z0);
   Tile8<TZ> tile;
-  tile8_issue<TZ>(tile, u1, cx, ho, T.z0);
-  int eo[G::NH];
-  ext_offsets<TZ>(eo, nx, nz, px, T.x0, T.z0);
-  float pm2[G::NS], pcf[G::NS], tcf[G::RPT];
+  tile.issue(u1, cx, T.x0, T.z0, nx, nz, px);
+  f32x2 pm2[RA], pcf[RA], tcf[RB];
 #pragma unroll
-  for (int i = 0; i < G::NS; ++i) {
-    pm2[i] = ld_ext<TZ>(u2, i, cx, eo, T.z0);
-    pcf[i] = ld_ext<TZ>(cf, i, cx, eo, T.z0);
+  for (int i = 0; i < RA; ++i) {
+    pm2[i] = ldp2(u2, cx, zE + wv * RA + i);
+    pcf[i] = ldp2(cf, cx, zE + wv * RA + i);
   }
+  const bool side = (int)threadIdx.x < G::NSE;
+  int sr, sc;
+  side_pair<kHalo>(min((int)threadIdx.x, G::NSE - 1), &sr, &sc);
+  const int sx = T.x0 - kHalo + sc, sz = zE + sr;
+  const int so = side ? col_off(sx, sz, nx, nz, px, 4) : kOOB;
+  const f32x2 sm2 = ldp2_at(u2, so), scf = ldp2_at(cf, so);
 #pragma unroll
-  for (int i = 0; i < G::RPT; ++i) tcf[i] = ldp(cf, cx, T.z0 + wv * G::RPT + i);
-  tile8_commit<TZ>(L1, tile);
+  for (int i = 0; i < RB; ++i) tcf[i] = ldp2(cf, cx, T.z0 + wv * RB + i);
+  tile.commit(L1);
   __syncthreads();
 
-  if (act1 && a.d != nullptr) {
-    for (int t = threadIdx.x; t < T.gat_count; t += G::NT) {
-      const RecDev R = a.t.recs[T.gat_begin + t];
-      const int C = R.i - T.x0 + 2 * kHalo, Rw = R.k - T.z0 + 2 * kHalo;
-      a.d[S.d + (long long)(k - 1) * S.nrec + R.r] =
-          R.w[0] * L1[Rw][C] + R.w[1] * L1[Rw][C + 1] + R.w[2] * L1[Rw + 1][C] + R.w[3] * L1[Rw + 1][C + 1];
-    }
-  }
+  if (act1 && a.d != nullptr) gather<G::NT, G::W1>(a, T, S, L1, T.z0 - 2 * kHalo, T.x0 - 2 * kHalo, k - 1);
   // shot fields used after stores, in registers (see fwd2d_kernel)
-  const int src_i = S.src_i, src_k = S.src_k;
-  const float sw0 = S.src_w[0], sw1 = S.src_w[1], sw2 = S.src_w[2], sw3 = S.src_w[3];
-  auto src_weight = [&](int w) { return w == 0 ? sw0 : w == 1 ? sw1 : w == 2 ? sw2 : sw3; };
-  // first step: level k on the tile + 4-cell halo (zero outside the grid)
-  const float q1 = act1 ? a.q[S.q + k - 1] : 0.f;
+  const Source src(S);
+  const float q1 = act1 ? a.q[S.q + k - 1] : 0.f, q2 = act2 ? a.q[S.q + k] : 0.f;
+  const Damp damp(x, nx, a.nbl);
+  // first step: level k on the tile + 4-cell halo (zero outside the grid, where u, u^{k-2} and coef
+  // read 0)
+  {
+    f32x2 lap[RA], u[RA];
+    lap_pairs<RA, G::W1>(&L1[wv * RA + kHalo][2 * kHalo + 2 * lane], lap, u, a.c);
 #pragma unroll
-  for (int i = 0; i < G::NS; ++i) {
-    int r, c;
-    if (!ext_slot<TZ>(i, &r, &c)) continue;
-    const int z = T.z0 - kHalo + r, xx = T.x0 - kHalo + c;
-    float v = 0.f, incr = 0.f;
-    if ((unsigned)z < (unsigned)nz && (unsigned)xx < (unsigned)nx) {
-      const float* pc = &L1[r + kHalo][c + kHalo];
-      const float u = pc[0];
-      float lap = lap_ptr(pc, G::W1, a.c);
-      const int bx = xx - src_i, bz = z - src_k;
-      if (act1 && (unsigned)bx < 2u && (unsigned)bz < 2u) lap += src_weight(bx + 2 * bz) * q1;
-      const int dx = border_dist(xx, nx, a.nbl), dz = border_dist(z, nz, a.nbl);
-      const float eta = a.eta_dt * (float)(dx * dx + dz * dz);
-      incr = step_incr(u, pm2[i], pcf[i], lap, eta);
-      v = (u + u - pm2[i]) + incr;
+    for (int i = 0; i < RA; ++i) {
+      const int r = wv * RA + i, z = zE + r;
+      if (act1) src.add(&lap[i], x, z, q1);
+      f32x2 incr, v;
+      step_pair(u[i], pm2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &v);
+      // rows of the tile store level k (the others' stores drop)
+      const int zo = (unsigned)(r - kHalo) < (unsigned)TZ && z < nz ? z * row4 : kZOOB;
+      stb2(ro1, v, cx, zo);
+      if (SK == kStoreF32) stb2_nt(rs1, v, cx, zo);
+      if (PRB && (unsigned)(r - kHalo) < (unsigned)TZ) *reinterpret_cast<f32x2*>(&INC1[r - kHalo][2 * lane]) = incr;
+      *reinterpret_cast<f32x2*>(&LE[r][kHalo + 2 * lane]) = v;
     }
-    // body slots on tile rows store level k (wave-uniform condition; columns outside drop)
-    if (i < G::NB && r >= kHalo && r < kHalo + TZ) {
-      stb(ro1, v, cx, z * row4);
-      if (SK == kStoreF32) stb_nt(rs1, v, cx, z * row4);
-      if (PRB) INC1[r - kHalo][c - kHalo] = incr;
-    }
-    LE[r][c] = v;
+  }
+  if (side) {
+    f32x2 lap[1], u[1], incr, v;
+    lap_pairs<1, G::W1>(&L1[sr + kHalo][sc + kHalo], lap, u, a.c);
+    if (act1) src.add(&lap[0], sx, sz, q1);
+    step_pair(u[0], sm2, scf, lap[0], Damp(sx, nx, a.nbl), border_dist(sz, nz, a.nbl), a.eta_dt, &incr, &v);
+    *reinterpret_cast<f32x2*>(&LE[sr][sc]) = v;
   }
   __syncthreads();
 
-  if (act2 && a.d != nullptr) {
-    for (int t = threadIdx.x; t < T.gat_count; t += G::NT) {
-      const RecDev R = a.t.recs[T.gat_begin + t];
-      const int C = R.i - T.x0 + kHalo, Rw = R.k - T.z0 + kHalo;
-      a.d[S.d + (long long)k * S.nrec + R.r] =
-          R.w[0] * LE[Rw][C] + R.w[1] * LE[Rw][C + 1] + R.w[2] * LE[Rw + 1][C] + R.w[3] * LE[Rw + 1][C + 1];
-    }
-  }
+  if (act2 && a.d != nullptr) gather<G::NT, G::WE>(a, T, S, LE, zE, T.x0 - kHalo, k);
   if (!act2 && !PRB) return;  // probe: level k's increments are still to be added
   // second step: level k+1 on the tile (every lane computes; stores outside the grid drop, as
   // do those of an inactive level k+1)
-  const float q2 = act2 ? a.q[S.q + k] : 0.f;
-  const int dx = border_dist(x, nx, a.nbl);
   double* pb = PRB ? reinterpret_cast<double*>(a.ws + S.store) : nullptr;
   const float* pc1 = PRB ? a.probe_c + k : nullptr;
   const float* pc2 = PRB ? a.probe_c + k + 1 : nullptr;
+  f32x2 lap[RB], u[RB];
+  lap_pairs<RB, G::WE>(&LE[wv * RB + kHalo][kHalo + 2 * lane], lap, u, a.c);
 #pragma unroll
-  for (int i = 0; i < G::RPT; ++i) {
-    const int lr = wv * G::RPT + i;
-    const int z = T.z0 + lr;
-    const float* pc = &LE[lr + kHalo][lane + kHalo];
-    const float u = pc[0];
-    const float um2 = L1[lr + 2 * kHalo][lane + 2 * kHalo];
-    float lap = lap_ptr(pc, G::WE, a.c);
-    const int bx = x - src_i, bz = z - src_k;
-    if ((unsigned)bx < 2u && (unsigned)bz < 2u) lap += src_weight(bx + 2 * bz) * q2;
-    const int dz = border_dist(z, nz, a.nbl);
-    const float eta = a.eta_dt * (float)(dx * dx + dz * dz);
-    const float incr = step_incr(u, um2, tcf[i], lap, eta);
-    const float un = (u + u - um2) + incr;
-    stb(ro2, un, cx, z * row4);
-    if (SK == kStoreF32) stb_nt(rs2, un, cx, z * row4);
-    if (PRB && x < nx && z < nz) {
+  for (int i = 0; i < RB; ++i) {
+    const int lr = wv * RB + i, z = T.z0 + lr;
+    const f32x2 um2 = *reinterpret_cast<const f32x2*>(&L1[lr + 2 * kHalo][2 * kHalo + 2 * lane]);
+    src.add(&lap[i], x, z, q2);
+    f32x2 incr, un;
+    step_pair(u[i], um2, tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &un);
+    const int zo = z * row4;
+    stb2(ro2, un, cx, zo);
+    if (SK == kStoreF32) stb2_nt(rs2, un, cx, zo);
+    if (PRB && z < nz) {
       // the same two FP64 additions, in the same order, as two one-level launches
-      const long long p = (long long)z * px + x;
-      probe_add(probe_sums(pb, p, a.probe_r), a.probe_r, pc1, (double)INC1[lr][lane], act1, pc2, (double)incr, act2,
-                a.probe_pitch);
+      const f32x2 i1 = *reinterpret_cast<const f32x2*>(&INC1[lr][2 * lane]);
+      if (x < nx)
+        probe_add2(probe_sums(pb, (long long)z * px + x, a.probe_r), a.probe_r, pc1, i1, act1, pc2, incr, act2,
+                   a.probe_pitch);
     }
+  }
+}
+
+// Residual injected at the points [begin, begin + count) of a tile's list, into LDS at the points'
+// tile coordinates.
+template <int NT, int W>
+__device__ __forceinline__ void inject(const StepArgs& a, const InjPoint* pts, int begin, int count, const float* dd,
+                                       float (*L)[W]) {
+  for (int t = threadIdx.x; t < count; t += NT) {
+    const InjPoint Pt = pts[begin + t];
+    float sum = 0.f;
+    for (int e = 0; e < Pt.e_count; ++e) {
+      const InjEntry E = a.t.inj_ent[Pt.e_begin + e];
+      sum += E.w * dd[E.r];
+    }
+    L[Pt.lz][Pt.lx] = sum;
   }
 }
 
 // Adjoint: levels j and j-1 (j = step - off), receiver residual injected in both steps,
 // imaging of both steps accumulated (in step order) into one FP64 read-modify-write.
-// IMG = kImgNone, kImgFull32 or kImgProbe (both levels added to the probe sums A_j in one FP64
-// read-modify-write, level j first).
+// IMG = kImgNone, kImgFull32, kImgBuffers or kImgProbe (both levels added to the probe sums A_j in
+// one FP64 read-modify-write, level j first).  a.single: level j alone.
+//
+// The injected residual takes no LDS of its own: the first step's lies where the point's new level
+// goes (LE), which its own thread reads before it writes; the second step's in L1, of which the
+// second step needs only its own points' values, held in registers by then.
 template <int TZ, int IMG>
 __global__ __launch_bounds__(F2<TZ>::NT) void adj2d2_kernel(StepArgs a) {
   using G = F2<TZ>;
+  constexpr int RA = G::RA, RB = G::RB;
   // kImgBuffers: the two levels come from the recomputed forward buffers (or the slot restored
   // by reference) instead of the FULL store, as in a checkpointed gradient's paired reversals
   constexpr bool IBUF = IMG == kImgBuffers;
   constexpr bool IACC = IMG == kImgFull32 || IBUF;
-  __shared__ float L1[G::H1][G::W1];
-  __shared__ float LE[G::HE][G::WE];
-  __shared__ float INJ1[G::HE][G::WE];
-  __shared__ float INJ2[TZ][kTX];
-  __shared__ float INC1[TZ][kTX];
+  constexpr bool PRB = IMG == kImgProbe;
+  __shared__ __align__(16) float L1[G::H1][G::W1];
+  __shared__ __align__(16) float LE[G::HE][G::WE];
+  __shared__ __align__(16) float INC1[IACC ? TZ : 1][kTX2];
   const int tid = xcd_tile(blockIdx.x, a.ntiles);
   const TileDev T = a.t.tiles[a.tile_base + tid];
   const ShotDev& S = a.t.shots[T.shot];
   const int j = a.step - S.off;
   const bool act1 = j >= 1 && j <= S.nt - 1;
-  const bool act2 = j - 1 >= 1 && j - 1 <= S.nt - 1;
+  const bool act2 = !a.single && j - 1 >= 1 && j - 1 <= S.nt - 1;
   if (!act1 && !act2) return;
   const int nx = S.nx, nz = S.nz, px = S.px;
   const int row4 = 4 * px;
@@ -746,142 +896,133 @@ __global__ __launch_bounds__(F2<TZ>::NT) void adj2d2_kernel(StepArgs a) {
   const Planes acc = planes(a.ws + S.acc, nz, IACC ? nz : 0, 2 * row4);
   const brsrc racc = make_rsrc(a.ws + S.acc, IACC ? 2 * nz * row4 : 0);
   const int lane = threadIdx.x & 63, wv = wave_id();
-  const int x = T.x0 + lane;
+  const int x = T.x0 + 2 * lane;
   const int cx = x < nx ? 4 * x : kOOB;
   const int cx8 = x < nx ? 8 * x : kOOB;
+  const int zE = T.z0 - kHalo;
   const bool inj1 = act1 && a.dd != nullptr && T.ext_count > 0;
   const bool inj2 = act2 && a.dd != nullptr && T.inj_count > 0;
 
-  int ho[Side8<TZ>::NH];
-  side_offsets<G::NT, G::H1, 2 * kHalo>(ho, nx, nz, px, T.x0, T.z0);
   Tile8<TZ> tile;
-  tile8_issue<TZ>(tile, w1, cx, ho, T.z0);
-  int eo[G::NH];
-  ext_offsets<TZ>(eo, nx, nz, px, T.x0, T.z0);
-  float pm2[G::NS], pcf[G::NS], tcf[G::RPT], pu1[G::RPT], pu2[G::RPT];
-  double pacc[G::RPT];
+  tile.issue(w1, cx, T.x0, T.z0, nx, nz, px);
+  f32x2 pm2[RA], pcf[RA], tcf[RB], pu1[RB], pu2[RB];
+  f64x2 pacc[RB];
 #pragma unroll
-  for (int i = 0; i < G::NS; ++i) {
-    pm2[i] = ld_ext<TZ>(w2, i, cx, eo, T.z0);
-    pcf[i] = ld_ext<TZ>(cf, i, cx, eo, T.z0);
-    int r, c;
-    if (inj1 && ext_slot<TZ>(i, &r, &c)) INJ1[r][c] = 0.f;
+  for (int i = 0; i < RA; ++i) {
+    const int r = wv * RA + i;
+    pm2[i] = ldp2(w2, cx, zE + r);
+    pcf[i] = ldp2(cf, cx, zE + r);
+    if (inj1) *reinterpret_cast<f32x2*>(&LE[r][kHalo + 2 * lane]) = f32x2{0.f, 0.f};
   }
+  const bool side = (int)threadIdx.x < G::NSE;
+  int sr, sc;
+  side_pair<kHalo>(min((int)threadIdx.x, G::NSE - 1), &sr, &sc);
+  const int sx = T.x0 - kHalo + sc, sz = zE + sr;
+  const int so = side ? col_off(sx, sz, nx, nz, px, 4) : kOOB;
+  const f32x2 sm2 = ldp2_at(w2, so), scf = ldp2_at(cf, so);
+  if (inj1 && side) *reinterpret_cast<f32x2*>(&LE[sr][sc]) = f32x2{0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < G::RPT; ++i) {
-    const int z = T.z0 + wv * G::RPT + i;
-    tcf[i] = ldp(cf, cx, z);
+  for (int i = 0; i < RB; ++i) {
+    const int z = T.z0 + wv * RB + i;
+    tcf[i] = ldp2(cf, cx, z);
     if (IACC) {
-      pu1[i] = ldp_nt(us1, cx, z);
-      pu2[i] = ldp_nt(us2, cx, z);
-      pacc[i] = ldp64(acc, cx8, z);
+      pu1[i] = ldp2_nt(us1, cx, z);
+      pu2[i] = ldp2_nt(us2, cx, z);
+      pacc[i] = ldp64x2(acc, cx8, z);
     }
-    if (inj2) INJ2[wv * G::RPT + i][lane] = 0.f;
   }
-  tile8_commit<TZ>(L1, tile);
+  tile.commit(L1);
   __syncthreads();
 
-  if (inj1 || inj2) {
-    if (inj1) {
-      const float* ddj = a.dd + S.d + (long long)j * S.nrec;
-      for (int t = threadIdx.x; t < T.ext_count; t += G::NT) {
-        const InjPoint Pt = a.t.ext_pts[T.ext_begin + t];
-        float sum = 0.f;
-        for (int e = 0; e < Pt.e_count; ++e) {
-          const InjEntry E = a.t.inj_ent[Pt.e_begin + e];
-          sum += E.w * ddj[E.r];
-        }
-        INJ1[Pt.lz][Pt.lx] = sum;
-      }
-    }
-    if (inj2) {
-      const float* ddj = a.dd + S.d + (long long)(j - 1) * S.nrec;
-      for (int t = threadIdx.x; t < T.inj_count; t += G::NT) {
-        const InjPoint Pt = a.t.inj_pts[T.inj_begin + t];
-        float sum = 0.f;
-        for (int e = 0; e < Pt.e_count; ++e) {
-          const InjEntry E = a.t.inj_ent[Pt.e_begin + e];
-          sum += E.w * ddj[E.r];
-        }
-        INJ2[Pt.lz][Pt.lx] = sum;
-      }
-    }
+  if (inj1) {
+    inject<G::NT, G::WE>(a, a.t.ext_pts, T.ext_begin, T.ext_count, a.dd + S.d + (long long)j * S.nrec, LE);
     __syncthreads();
   }
-  if (act1 && a.v != nullptr && a.tile_base + tid == S.src_tile && threadIdx.x == 0) {
-    const int C = S.src_i - T.x0 + 2 * kHalo, R = S.src_k - T.z0 + 2 * kHalo;
-    a.v[S.q + j] = S.src_w[0] * L1[R][C] + S.src_w[1] * L1[R][C + 1] + S.src_w[2] * L1[R + 1][C] +
-                   S.src_w[3] * L1[R + 1][C + 1];
-  }
-  // first step: level j on the tile + 4-cell halo (the loop has no early exit, so it unrolls
-  // completely and pm2 / pcf stay in registers)
+  const bool src_here = a.v != nullptr && a.tile_base + tid == S.src_tile && threadIdx.x == 0;
+  if (act1 && src_here)
+    a.v[S.q + j] = interp_at<G::W1>(L1, S.src_k - T.z0 + 2 * kHalo, S.src_i - T.x0 + 2 * kHalo, S.src_w);
+  const Damp damp(x, nx, a.nbl);
+  // first step: level j on the tile + 4-cell halo
+  {
+    f32x2 lap[RA], u[RA];
+    lap_pairs<RA, G::W1>(&L1[wv * RA + kHalo][2 * kHalo + 2 * lane], lap, u, a.c);
 #pragma unroll
-  for (int i = 0; i < G::NS; ++i) {
-    int r, c;
-    if (!ext_slot<TZ>(i, &r, &c)) continue;
-    const int z = T.z0 - kHalo + r, xx = T.x0 - kHalo + c;
-    float v = 0.f, incr = 0.f;
-    if ((unsigned)z < (unsigned)nz && (unsigned)xx < (unsigned)nx) {
-      const float* pc = &L1[r + kHalo][c + kHalo];
-      const float w = pc[0];
-      float lap = lap_ptr(pc, G::W1, a.c);
-      if (inj1) lap += INJ1[r][c];
-      const int dx = border_dist(xx, nx, a.nbl), dz = border_dist(z, nz, a.nbl);
-      const float eta = a.eta_dt * (float)(dx * dx + dz * dz);
-      incr = step_incr(w, pm2[i], pcf[i], lap, eta);
-      v = (w + w - pm2[i]) + incr;
+    for (int i = 0; i < RA; ++i) {
+      const int r = wv * RA + i, z = zE + r;
+      f32x2* le = reinterpret_cast<f32x2*>(&LE[r][kHalo + 2 * lane]);
+      if (inj1) {
+        const f32x2 s = *le;
+        lap[i].x += s.x;
+        lap[i].y += s.y;
+      }
+      f32x2 incr, v;
+      step_pair(u[i], pm2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &v);
+      const bool on = (unsigned)(r - kHalo) < (unsigned)TZ;
+      stb2(ro1, v, cx, on && z < nz ? z * row4 : kZOOB);
+      if (IACC && on) *reinterpret_cast<f32x2*>(&INC1[r - kHalo][2 * lane]) = incr;
+      *le = v;
     }
-    // body slots on tile rows: level j out, and its increment kept for the imaging
-    if (i < G::NB && r >= kHalo && r < kHalo + TZ) {
-      stb(ro1, v, cx, z * row4);
-      INC1[r - kHalo][c - kHalo] = incr;
-    }
-    LE[r][c] = v;
   }
+  if (side) {
+    f32x2 lap[1], u[1], incr, v;
+    lap_pairs<1, G::W1>(&L1[sr + kHalo][sc + kHalo], lap, u, a.c);
+    f32x2* le = reinterpret_cast<f32x2*>(&LE[sr][sc]);
+    if (inj1) {
+      const f32x2 s = *le;
+      lap[0].x += s.x;
+      lap[0].y += s.y;
+    }
+    step_pair(u[0], sm2, scf, lap[0], Damp(sx, nx, a.nbl), border_dist(sz, nz, a.nbl), a.eta_dt, &incr, &v);
+    *le = v;
+  }
+  f32x2 um2[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+    um2[i] = *reinterpret_cast<const f32x2*>(&L1[wv * RB + i + 2 * kHalo][2 * kHalo + 2 * lane]);
   __syncthreads();
 
-  if (act2 && a.v != nullptr && a.tile_base + tid == S.src_tile && threadIdx.x == 0) {
-    const int C = S.src_i - T.x0 + kHalo, R = S.src_k - T.z0 + kHalo;
-    a.v[S.q + j - 1] = S.src_w[0] * LE[R][C] + S.src_w[1] * LE[R][C + 1] + S.src_w[2] * LE[R + 1][C] +
-                       S.src_w[3] * LE[R + 1][C + 1];
+  if (inj2) {   // the tile's rows of L1 (cell (0, 0) = tile point (0, 0)) now take the second residual
+#pragma unroll
+    for (int i = 0; i < RB; ++i) *reinterpret_cast<f32x2*>(&L1[wv * RB + i][2 * lane]) = f32x2{0.f, 0.f};
+    __syncthreads();
+    inject<G::NT, G::W1>(a, a.t.inj_pts, T.inj_begin, T.inj_count, a.dd + S.d + (long long)(j - 1) * S.nrec, L1);
+    __syncthreads();
   }
+  if (act2 && src_here) a.v[S.q + j - 1] = interp_at<G::WE>(LE, S.src_k - zE, S.src_i - T.x0 + kHalo, S.src_w);
   // second step: level j-1 on the tile; imaging of both steps (every lane computes; outside
   // the grid the stores drop)
-  const int dx = border_dist(x, nx, a.nbl);
-  double* pa = IMG == kImgProbe ? reinterpret_cast<double*>(a.ws + S.store) + (long long)a.probe_r * S.npts
-                                : nullptr;
-  const float* pc1 = IMG == kImgProbe ? a.probe_c + j : nullptr;
-  const float* pc2 = IMG == kImgProbe ? a.probe_c + j - 1 : nullptr;
+  double* pa = PRB ? reinterpret_cast<double*>(a.ws + S.store) + (long long)a.probe_r * S.npts : nullptr;
+  const float* pc1 = PRB ? a.probe_c + j : nullptr;
+  const float* pc2 = PRB ? a.probe_c + j - 1 : nullptr;
+  if (!act2 && !IACC && !PRB) return;
+  f32x2 lap[RB], u[RB];
+  lap_pairs<RB, G::WE>(&LE[wv * RB + kHalo][kHalo + 2 * lane], lap, u, a.c);
 #pragma unroll
-  for (int i = 0; i < G::RPT; ++i) {
-    const int lr = wv * G::RPT + i;
-    const int z = T.z0 + lr;
-    double ac = IACC ? pacc[i] : 0.0;
-    if (IACC && act1) ac = ac + (double)pu1[i] * (double)INC1[lr][lane];
-    float wj = 0.f, wn = 0.f;  // probe: levels j and j-1 on the tile
-    if (act2) {
-      const float* pc = &LE[lr + kHalo][lane + kHalo];
-      const float w = pc[0];
-      const float wm2 = L1[lr + 2 * kHalo][lane + 2 * kHalo];
-      float lap = lap_ptr(pc, G::WE, a.c);
-      if (inj2) lap += INJ2[lr][lane];
-      const int dz = border_dist(z, nz, a.nbl);
-      const float eta = a.eta_dt * (float)(dx * dx + dz * dz);
-      const float incr = step_incr(w, wm2, tcf[i], lap, eta);
-      stb(ro2, (w + w - wm2) + incr, cx, z * row4);
-      if (IACC) ac = ac + (double)pu2[i] * (double)incr;
-      if (IMG == kImgProbe) {
-        wj = w;
-        wn = (w + w - wm2) + incr;
-      }
-    } else if (IMG == kImgProbe) {
-      wj = LE[lr + kHalo][lane + kHalo];
+  for (int i = 0; i < RB; ++i) {
+    const int lr = wv * RB + i, z = T.z0 + lr;
+    if (inj2) {
+      const f32x2 s = *reinterpret_cast<const f32x2*>(&L1[lr][2 * lane]);
+      lap[i].x += s.x;
+      lap[i].y += s.y;
     }
-    if (IACC) stb64(racc, ac, cx8, 2 * z * row4);
-    if (IMG == kImgProbe && x < nx && z < nz) {
+    f32x2 incr, wn;
+    step_pair(u[i], um2[i], tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &wn);
+    stb2(ro2, wn, cx, z * row4);
+    if (IACC) {
+      const f32x2 i1 = *reinterpret_cast<const f32x2*>(&INC1[lr][2 * lane]);
+      f64x2 ac = pacc[i];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        if (act1) ac[c] = ac[c] + (double)pu1[i][c] * (double)i1[c];
+        if (act2) ac[c] = ac[c] + (double)pu2[i][c] * (double)incr[c];
+      }
+      stb64x2(racc, ac, cx8, 2 * z * row4);
+    }
+    if (PRB && z < nz) {
       // the same two FP64 additions, in the same order, as two one-level launches
-      const long long p = (long long)z * px + x;
-      probe_add(probe_sums(pa, p, a.probe_r), a.probe_r, pc1, (double)wj, act1, pc2, (double)wn, act2, a.probe_pitch);
+      if (x < nx)
+        probe_add2(probe_sums(pa, (long long)z * px + x, a.probe_r), a.probe_r, pc1, u[i], act1, pc2, wn, act2,
+                   a.probe_pitch);
     }
   }
 }
@@ -890,20 +1031,21 @@ __global__ __launch_bounds__(F2<TZ>::NT) void adj2d2_kernel(StepArgs a) {
 // the arithmetic of born2d_kernel in the same order (so the results are bitwise those of two
 // one-level launches); samples (J dm)^{k-1} and (J dm)^k.  Per two levels the launch reads
 // u^{k-1}, u^{k-2}, du^{k-1}, du^{k-2}, coef and dm once and writes four levels: 40 B per point
-// instead of 2 x 32.
+// instead of 2 x 32.  a.single: level k alone.
 template <int TZ>
 __global__ __launch_bounds__(F2<TZ>::NT) void born2d2_kernel(StepArgs a) {
   using G = F2<TZ>;
-  __shared__ float L1U[G::H1][G::W1];
-  __shared__ float L1D[G::H1][G::W1];
-  __shared__ float LEU[G::HE][G::WE];
-  __shared__ float LED[G::HE][G::WE];
+  constexpr int RA = G::RA, RB = G::RB;
+  __shared__ __align__(16) float L1U[G::H1][G::W1];
+  __shared__ __align__(16) float L1D[G::H1][G::W1];
+  __shared__ __align__(16) float LEU[G::HE][G::WE];
+  __shared__ __align__(16) float LED[G::HE][G::WE];
   const int tid = xcd_tile(blockIdx.x, a.ntiles);
   const TileDev T = a.t.tiles[a.tile_base + tid];
   const ShotDev& S = a.t.shots[T.shot];
   const int k = a.step - S.off;
   const bool act1 = k >= 1 && k <= S.nt - 1;
-  const bool act2 = k + 1 >= 1 && k + 1 <= S.nt - 1;
+  const bool act2 = !a.single && k + 1 >= 1 && k + 1 <= S.nt - 1;
   if (!act1 && !act2) return;
   const int nx = S.nx, nz = S.nz, px = S.px;
   const int row4 = 4 * px;
@@ -920,113 +1062,114 @@ __global__ __launch_bounds__(F2<TZ>::NT) void born2d2_kernel(StepArgs a) {
   const brsrc do1 = make_rsrc(fbuf(a.ws, S, adj_buf(k)), act1 ? nz * row4 : 0);
   const brsrc do2 = make_rsrc(fbuf(a.ws, S, adj_buf(k + 1)), act2 ? nz * row4 : 0);
   const int lane = threadIdx.x & 63, wv = wave_id();
-  const int x = T.x0 + lane;
+  const int x = T.x0 + 2 * lane;
   const int cx = x < nx ? 4 * x : kOOB;
+  const int cx1 = x + 1 < nx ? 4 * x + 4 : kOOB;   // dm: rows of nx, one column at a time
+  const int zE = T.z0 - kHalo;
 
-  // the two level k-1 tiles first, then the first step's other inputs on its extended points
-  // (dm in the caller's rows of nx) and coef and dm of the tile points
-  int ho[Side8<TZ>::NH];
-  side_offsets<G::NT, G::H1, 2 * kHalo>(ho, nx, nz, px, T.x0, T.z0);
+  // the two level k-1 tiles first, then the first step's other inputs on its points and coef and
+  // dm of the tile points
   Tile8<TZ> tu, td;
-  tile8_issue<TZ>(tu, u1, cx, ho, T.z0);
-  tile8_issue<TZ>(td, d1, cx, ho, T.z0);
-  int eo[G::NH], eom[G::NH];
-  ext_offsets<TZ>(eo, nx, nz, px, T.x0, T.z0);
-  ext_offsets<TZ>(eom, nx, nz, nx, T.x0, T.z0);
-  float pu2[G::NS], pd2[G::NS], pcf[G::NS], pdm[G::NS], tcf[G::RPT], tdm[G::RPT];
+  tu.issue(u1, cx, T.x0, T.z0, nx, nz, px);
+  td.issue(d1, cx, T.x0, T.z0, nx, nz, px);
+  f32x2 pu2[RA], pd2[RA], pcf[RA], pdm[RA], tcf[RB], tdm[RB];
 #pragma unroll
-  for (int i = 0; i < G::NS; ++i) {
-    pu2[i] = ld_ext<TZ>(u2, i, cx, eo, T.z0);
-    pd2[i] = ld_ext<TZ>(d2, i, cx, eo, T.z0);
-    pcf[i] = ld_ext<TZ>(cf, i, cx, eo, T.z0);
-    pdm[i] = ld_ext<TZ>(dmp, i, cx, eom, T.z0);
+  for (int i = 0; i < RA; ++i) {
+    const int z = zE + wv * RA + i;
+    pu2[i] = ldp2(u2, cx, z);
+    pd2[i] = ldp2(d2, cx, z);
+    pcf[i] = ldp2(cf, cx, z);
+    pdm[i] = f32x2{ldp(dmp, cx, z), ldp(dmp, cx1, z)};
   }
+  const bool side = (int)threadIdx.x < G::NSE;
+  int sr, sc;
+  side_pair<kHalo>(min((int)threadIdx.x, G::NSE - 1), &sr, &sc);
+  const int sx = T.x0 - kHalo + sc, sz = zE + sr;
+  const int so = side ? col_off(sx, sz, nx, nz, px, 4) : kOOB;
+  const f32x2 su2 = ldp2_at(u2, so), sd2 = ldp2_at(d2, so), scf = ldp2_at(cf, so);
+  const f32x2 sdm = {ldp_at(dmp, side ? col_off(sx, sz, nx, nz, nx, 4) : kOOB),
+                     ldp_at(dmp, side ? col_off(sx + 1, sz, nx, nz, nx, 4) : kOOB)};
 #pragma unroll
-  for (int i = 0; i < G::RPT; ++i) {
-    tcf[i] = ldp(cf, cx, T.z0 + wv * G::RPT + i);
-    tdm[i] = ldp(dmp, cx, T.z0 + wv * G::RPT + i);
+  for (int i = 0; i < RB; ++i) {
+    const int z = T.z0 + wv * RB + i;
+    tcf[i] = ldp2(cf, cx, z);
+    tdm[i] = f32x2{ldp(dmp, cx, z), ldp(dmp, cx1, z)};
   }
-  tile8_commit<TZ>(L1U, tu);
-  tile8_commit<TZ>(L1D, td);
+  tu.commit(L1U);
+  td.commit(L1D);
   __syncthreads();
 
-  if (act1 && a.d != nullptr) {
-    for (int t = threadIdx.x; t < T.gat_count; t += G::NT) {
-      const RecDev R = a.t.recs[T.gat_begin + t];
-      const int C = R.i - T.x0 + 2 * kHalo, Rw = R.k - T.z0 + 2 * kHalo;
-      a.d[S.d + (long long)(k - 1) * S.nrec + R.r] =
-          R.w[0] * L1D[Rw][C] + R.w[1] * L1D[Rw][C + 1] + R.w[2] * L1D[Rw + 1][C] + R.w[3] * L1D[Rw + 1][C + 1];
+  if (act1 && a.d != nullptr) gather<G::NT, G::W1>(a, T, S, L1D, T.z0 - 2 * kHalo, T.x0 - 2 * kHalo, k - 1);
+  const Source src(S);   // in registers (see the forward kernel)
+  const float q1 = act1 ? a.q[S.q + k - 1] : 0.f, q2 = act2 ? a.q[S.q + k] : 0.f;
+  const Damp damp(x, nx, a.nbl);
+  // scattered field's source: -dm (u^k - 2u^{k-1} + u^{k-2}) / dt^2 = -dm incr / dt^2
+  auto scatter = [&](f32x2* lapd, f32x2 dm, f32x2 incr) {
+    lapd->x = lapd->x - dm.x * incr.x * a.inv_dt2;
+    lapd->y = lapd->y - dm.y * incr.y * a.inv_dt2;
+  };
+  // first step: levels k of u and du on the tile + 4-cell halo
+  {
+    f32x2 lap[RA], u[RA], inc[RA];
+    lap_pairs<RA, G::W1>(&L1U[wv * RA + kHalo][2 * kHalo + 2 * lane], lap, u, a.c);
+#pragma unroll
+    for (int i = 0; i < RA; ++i) {
+      const int r = wv * RA + i, z = zE + r;
+      if (act1) src.add(&lap[i], x, z, q1);
+      f32x2 v;
+      step_pair(u[i], pu2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &inc[i], &v);
+      stb2(uo1, v, cx, (unsigned)(r - kHalo) < (unsigned)TZ && z < nz ? z * row4 : kZOOB);
+      *reinterpret_cast<f32x2*>(&LEU[r][kHalo + 2 * lane]) = v;
+    }
+    lap_pairs<RA, G::W1>(&L1D[wv * RA + kHalo][2 * kHalo + 2 * lane], lap, u, a.c);
+#pragma unroll
+    for (int i = 0; i < RA; ++i) {
+      const int r = wv * RA + i, z = zE + r;
+      scatter(&lap[i], pdm[i], inc[i]);
+      f32x2 incd, v;
+      step_pair(u[i], pd2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incd, &v);
+      stb2(do1, v, cx, (unsigned)(r - kHalo) < (unsigned)TZ && z < nz ? z * row4 : kZOOB);
+      *reinterpret_cast<f32x2*>(&LED[r][kHalo + 2 * lane]) = v;
     }
   }
-  const int src_i = S.src_i, src_k = S.src_k;   // in registers (see the forward kernel)
-  const float sw0 = S.src_w[0], sw1 = S.src_w[1], sw2 = S.src_w[2], sw3 = S.src_w[3];
-  auto src_weight = [&](int w) { return w == 0 ? sw0 : w == 1 ? sw1 : w == 2 ? sw2 : sw3; };
-  // first step: levels k of u and du on the tile + 4-cell halo (zero outside the grid)
-  const float q1 = act1 ? a.q[S.q + k - 1] : 0.f;
-#pragma unroll
-  for (int i = 0; i < G::NS; ++i) {
-    int r, c;
-    if (!ext_slot<TZ>(i, &r, &c)) continue;
-    const int z = T.z0 - kHalo + r, xx = T.x0 - kHalo + c;
-    float v = 0.f, vd = 0.f;
-    if ((unsigned)z < (unsigned)nz && (unsigned)xx < (unsigned)nx) {
-      const int dx = border_dist(xx, nx, a.nbl), dz = border_dist(z, nz, a.nbl);
-      const float eta = a.eta_dt * (float)(dx * dx + dz * dz);
-      const float* pc = &L1U[r + kHalo][c + kHalo];
-      const float u = pc[0];
-      float lap = lap_ptr(pc, G::W1, a.c);
-      const int bx = xx - src_i, bz = z - src_k;
-      if (act1 && (unsigned)bx < 2u && (unsigned)bz < 2u) lap += src_weight(bx + 2 * bz) * q1;
-      const float incr = pcf[i] * (lap - eta * (u - pu2[i]));
-      v = (u + u - pu2[i]) + incr;
-      const float* pd = &L1D[r + kHalo][c + kHalo];
-      const float du = pd[0];
-      const float lapd = lap_ptr(pd, G::W1, a.c) - pdm[i] * incr * a.inv_dt2;
-      const float incd = pcf[i] * (lapd - eta * (du - pd2[i]));
-      vd = (du + du - pd2[i]) + incd;
-    }
-    // body slots on tile rows store levels k (wave-uniform condition; columns outside drop)
-    if (i < G::NB && r >= kHalo && r < kHalo + TZ) {
-      stb(uo1, v, cx, z * row4);
-      stb(do1, vd, cx, z * row4);
-    }
-    LEU[r][c] = v;
-    LED[r][c] = vd;
+  if (side) {
+    const Damp sdamp(sx, nx, a.nbl);
+    const int dz = border_dist(sz, nz, a.nbl);
+    f32x2 lap[1], u[1], incr, incd, v;
+    lap_pairs<1, G::W1>(&L1U[sr + kHalo][sc + kHalo], lap, u, a.c);
+    if (act1) src.add(&lap[0], sx, sz, q1);
+    step_pair(u[0], su2, scf, lap[0], sdamp, dz, a.eta_dt, &incr, &v);
+    *reinterpret_cast<f32x2*>(&LEU[sr][sc]) = v;
+    lap_pairs<1, G::W1>(&L1D[sr + kHalo][sc + kHalo], lap, u, a.c);
+    scatter(&lap[0], sdm, incr);
+    step_pair(u[0], sd2, scf, lap[0], sdamp, dz, a.eta_dt, &incd, &v);
+    *reinterpret_cast<f32x2*>(&LED[sr][sc]) = v;
   }
   __syncthreads();
 
-  if (act2 && a.d != nullptr) {
-    for (int t = threadIdx.x; t < T.gat_count; t += G::NT) {
-      const RecDev R = a.t.recs[T.gat_begin + t];
-      const int C = R.i - T.x0 + kHalo, Rw = R.k - T.z0 + kHalo;
-      a.d[S.d + (long long)k * S.nrec + R.r] =
-          R.w[0] * LED[Rw][C] + R.w[1] * LED[Rw][C + 1] + R.w[2] * LED[Rw + 1][C] + R.w[3] * LED[Rw + 1][C + 1];
-    }
-  }
+  if (act2 && a.d != nullptr) gather<G::NT, G::WE>(a, T, S, LED, zE, T.x0 - kHalo, k);
   if (!act2) return;
   // second step: levels k+1 on the tile (every lane computes; stores outside the grid drop)
-  const float q2 = a.q[S.q + k];
-  const int dx = border_dist(x, nx, a.nbl);
+  f32x2 lap[RB], u[RB], inc[RB];
+  lap_pairs<RB, G::WE>(&LEU[wv * RB + kHalo][kHalo + 2 * lane], lap, u, a.c);
 #pragma unroll
-  for (int i = 0; i < G::RPT; ++i) {
-    const int lr = wv * G::RPT + i;
-    const int z = T.z0 + lr;
-    const int dz = border_dist(z, nz, a.nbl);
-    const float eta = a.eta_dt * (float)(dx * dx + dz * dz);
-    const float* pc = &LEU[lr + kHalo][lane + kHalo];
-    const float u = pc[0];
-    const float um2 = L1U[lr + 2 * kHalo][lane + 2 * kHalo];
-    float lap = lap_ptr(pc, G::WE, a.c);
-    const int bx = x - src_i, bz = z - src_k;
-    if ((unsigned)bx < 2u && (unsigned)bz < 2u) lap += src_weight(bx + 2 * bz) * q2;
-    const float incr = tcf[i] * (lap - eta * (u - um2));
-    stb(uo2, (u + u - um2) + incr, cx, z * row4);
-    const float* pd = &LED[lr + kHalo][lane + kHalo];
-    const float du = pd[0];
-    const float dm2 = L1D[lr + 2 * kHalo][lane + 2 * kHalo];
-    const float lapd = lap_ptr(pd, G::WE, a.c) - tdm[i] * incr * a.inv_dt2;
-    const float incd = tcf[i] * (lapd - eta * (du - dm2));
-    stb(do2, (du + du - dm2) + incd, cx, z * row4);
+  for (int i = 0; i < RB; ++i) {
+    const int lr = wv * RB + i, z = T.z0 + lr;
+    const f32x2 um2 = *reinterpret_cast<const f32x2*>(&L1U[lr + 2 * kHalo][2 * kHalo + 2 * lane]);
+    src.add(&lap[i], x, z, q2);
+    f32x2 v;
+    step_pair(u[i], um2, tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &inc[i], &v);
+    stb2(uo2, v, cx, z * row4);
+  }
+  lap_pairs<RB, G::WE>(&LED[wv * RB + kHalo][kHalo + 2 * lane], lap, u, a.c);
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    const int lr = wv * RB + i, z = T.z0 + lr;
+    const f32x2 dm2 = *reinterpret_cast<const f32x2*>(&L1D[lr + 2 * kHalo][2 * kHalo + 2 * lane]);
+    scatter(&lap[i], tdm[i], inc[i]);
+    f32x2 incd, v;
+    step_pair(u[i], dm2, tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incd, &v);
+    stb2(do2, v, cx, z * row4);
   }
 }
 

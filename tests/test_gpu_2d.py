@@ -408,3 +408,30 @@ def test_kernel_timing_counts_every_step_launch_of_a_checkpointed_gradient():
     _sync()
     launches = (nt - 1) // 2 + (nt - 1) % 2
     assert prof["forward"][0] == launches and prof["adjoint"][0] == launches, prof
+
+
+@pytest.mark.parametrize("tz", [8, 16, 24, 32])
+def test_two_level_tiles_at_their_column_edges_are_bitwise_the_one_level_path(tz):
+    """Windows one column short of, exactly and one column past one and two 128-column tiles (odd
+    widths end in half a column pair), with depths on both sides of a tile row edge, sources beside a tile
+    edge and receivers across it: gradient, F^T dd, traces and Born traces of the two-level kernels are
+    bitwise those of the one-level kernels (the same arithmetic per point)."""
+    nbl = 5
+    for nz, widths in ((tz - 2 * nbl if tz > 2 * nbl + 4 else 25 - 2 * nbl, [117, 118, 119]), (39, [246, 247, 13])):
+        wl = W.small_2d(nz=nz + 2, nbl=nbl, windows=widths, T_per_shot=[60.0, 47.0, 53.0], nrec=29)
+        for s in wl.shots:   # base nodes in the last column of the first tile
+            s.src[0] = min((127 - nbl + 0.4) * wl.h, (widths[s.window] - 3) * wl.h)
+        dds = _residuals(wl)
+        dms = [W.random_field(wl.comp_shape(w), 23 + w, 2.0) * 0.01 for w in range(wl.nwindow)]
+        outs = []
+        for fuse in (A.FUSE_BOTH, A.FUSE_NONE):
+            plan = make_plan(wl, storage=A.Storage(A.STORE_FULL))
+            plan.set_tiles(tz=tz)
+            plan.set_fusion(fuse)
+            m, q = gpu_inputs(wl, plan)
+            g, v, d = plan.gradient(m, q, plan.pack(dds, "d"), v=True, d=True)
+            b = plan.born(m, q, plan.pack(dms, "m"))
+            _sync()
+            outs.append([t.cpu() for t in (g, v, d, b)])
+        for a, b in zip(*outs):
+            assert torch.equal(a, b) and torch.isfinite(a).all() and a.abs().max() > 0
