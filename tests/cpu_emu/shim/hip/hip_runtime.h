@@ -51,6 +51,7 @@ inline void __syncthreads() { ::emu::syncthreads(); }
 inline int __builtin_amdgcn_readfirstlane(int v) { return v; }
 inline unsigned __builtin_amdgcn_readfirstlane(unsigned v) { return v; }
 #define __builtin_amdgcn_s_waitcnt(x) ((void)(x))
+#define __builtin_amdgcn_sched_barrier(x) ((void)(x))
 
 template <class T>
 inline T __shfl_xor(T v, int mask, int width = 64) {
@@ -138,6 +139,18 @@ inline void __builtin_amdgcn_raw_buffer_store_b16(unsigned short v, __amdgpu_buf
 inline void __builtin_amdgcn_raw_buffer_store_b64(emu_u32x2 v, __amdgpu_buffer_rsrc_t r, int voff, int soff, int aux) {
   (void)aux;
   if (char* p = ::emu::buffer_at(r, voff, soff, 8)) std::memcpy(p, &v, 8);
+}
+
+typedef unsigned emu_u32x4 __attribute__((ext_vector_type(4)));
+inline emu_u32x4 __builtin_amdgcn_raw_buffer_load_b128(__amdgpu_buffer_rsrc_t r, int voff, int soff, int aux) {
+  (void)aux;
+  emu_u32x4 v = {0u, 0u, 0u, 0u};
+  if (char* p = ::emu::buffer_at(r, voff, soff, 16)) std::memcpy(&v, p, 16);
+  return v;
+}
+inline void __builtin_amdgcn_raw_buffer_store_b128(emu_u32x4 v, __amdgpu_buffer_rsrc_t r, int voff, int soff, int aux) {
+  (void)aux;
+  if (char* p = ::emu::buffer_at(r, voff, soff, 16)) std::memcpy(p, &v, 16);
 }
 
 // ---------------------------------------------------------------- runtime
