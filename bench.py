@@ -517,7 +517,7 @@ def bench_c2(args):
     run.release()
     single = None
     if not args.no_single:
-        r1 = GradientRunner(wl, [0], A.Storage(A.STORE_FULL), autotune=False)
+        r1 = GradientRunner(wl, [0], A.Storage(A.STORE_FULL), tiles={"tz": 32, "atz": 16, "fusion": 0})
         s1, _ = r1.run(max(1, min(args.steps, 2)), 1, use_graph=False, profile=False)
         single = {"value": round(r1.points / s1 / 1e9, 3), "ms_per_step": round(s1 * 1e3, 2), "shots": 1,
                   "form": "one shot, one launch per time step, no graph"}

@@ -89,6 +89,9 @@ struct awe_plan {
   int nshot = 0, max_nt = 0, nsteps = 0;
   int fuse2 = 0;          // 2D: two time levels per launch where the storage allows
                           // (bit 0: forward solves, bit 1: reverse sweeps)
+  // shapes not set by the caller or the autotuner follow default_shapes
+  bool auto_rows[2] = {true, true};  // tile rows (2D) / column blocks (3D): forward, adjoint
+  bool auto_fuse = true;
   Tiling fw, rv;          // launch shapes of forward solves / adjoint steps
   Tiling fw2, rv2;        // their tables for the two-level kernels, whose tiles are wider (rows: fw.tz, rv.tz)
   std::vector<awe_shot> shots;
@@ -454,12 +457,48 @@ bool one_level_too(const awe_plan* P, int bit) {
          (bit == AWE_FUSE_FORWARD && P->store.mode == AWE_STORE_CHECKPOINT);
 }
 
+// Launch shapes of the directions the caller has not set, from the storage and the work of a launch
+// (the largest shot group's).
+//
+// 2D: two levels per launch, except for CHECKPOINT storage, whose launches stay one level each unless
+// asked otherwise, and for a 16-bit FULL store, whose kernels are one-level.  Two levels won at every
+// size timed: one shot of 281 x 181 2.3 -> 1.4 ms forward; one shot of 730 x 421 (1200 samples) 10.6 ->
+// 8.0 ms gradient; 24 shots of 592 x 336 (600 samples) 27.5 -> 19.7.  Tile rows follow the count of
+// 24-row tiles n: few tiles are bound by the chain of one tile, so its rows are cut; many by the
+// halo, so they grow.  us per launch, forward with store / reverse, at 8, 16, 24, 32 rows:
+//   n = 24:   4.6, 5.4, 6.1, 6.7    /  5.7, 6.7, 7.8, 8.9
+//   n = 108:  6.2, 5.9, 6.6, 7.4    /  7.4, 7.4, 8.5, 9.8
+//   n = 450:  11.5, 9.7, 9.4, 10.7  /  15.2, 13.5, 13.2, 14.9
+//   n = 900:  17.6, 15.9, 15.5, 16.0 / 26.7, 24.4, 24.6, 23.2
+//   n = 1800: 31.6, 25.2, 24.5, 26.8 / 50.0, 42.8, 41.3, 40.2
+// Probe sums, which dwarf the fields' traffic, prefer few rows at every size: 8 shots of 730 x 421 with 8
+// probes (400 samples) take 28.5, 29.9, 32.5, 34.6 ms.
+void default_shapes(awe_plan* P) {
+  if (P->ndim != 2) return;
+  const bool one_level = P->store.mode == AWE_STORE_CHECKPOINT ||
+                         (P->store.mode == AWE_STORE_FULL && P->store.prec != AWE_PREC_FP32);
+  if (P->auto_fuse) P->fuse2 = one_level ? AWE_FUSE_NONE : AWE_FUSE_BOTH;
+  long long n = 0;
+  for (size_t g = 0; g < P->g_shot0.size(); ++g) {
+    long long t = 0;
+    for (int i = 0; i < P->g_nshot[g]; ++i) {
+      const ShotDev& d = P->sd[P->order[P->g_shot0[g] + i]];
+      t += (long long)((d.nx + awe::kTX2 - 1) / awe::kTX2) * ((d.nz + 23) / 24);
+    }
+    n = std::max(n, t);
+  }
+  if (P->store.mode == AWE_STORE_PROBED) n = 0;
+  if (P->auto_rows[0]) P->fw.tz = !(P->fuse2 & AWE_FUSE_FORWARD) ? 32 : n < 64 ? 8 : n < 384 ? 16 : 24;
+  if (P->auto_rows[1]) P->rv.tz = !(P->fuse2 & AWE_FUSE_ADJOINT) ? 16 : n < 144 ? 8 : n < 512 ? 16 : 32;
+}
+
 // Shot groups and the tilings of the directions in `dirs` (bit 0 forward, bit 1 adjoint; the
 // groups change both, so a change of groups rebuilds both), built and uploaded: those of the kernels
 // the direction's calls can launch.
 awe_status rebuild(awe_plan* P, int dirs) {
   awe_status st = build_groups(P);
   if (st != AWE_OK) return st;
+  default_shapes(P);
   for (int bit : {AWE_FUSE_FORWARD, AWE_FUSE_ADJOINT}) {
     if (!(dirs & bit)) continue;
     Tiling& one = bit == AWE_FUSE_FORWARD ? P->fw : P->rv;
@@ -954,6 +993,7 @@ bool apply_tune_entry(awe_plan* P, const TuneEntry& e, awe_status* st) {
   P->rv.ty = e.rv[1];
   P->rv.bz = e.rv[2];
   P->fuse2 = e.fusion;
+  P->auto_fuse = P->auto_rows[0] = P->auto_rows[1] = false;
   P->kept_ws = nullptr;
   *st = rebuild(P, 3);
   return true;
@@ -1266,11 +1306,8 @@ awe_status awe_plan_create(const awe_problem* prob, const awe_storage* store, aw
     delete P;
     return st;
   }
-  // default launch shapes (the fastest measured on MI355X for the 2D and 3D workloads; the
-  // autotuner or awe_plan_set_tiles choose others): 2D 32-row forward and 16-row adjoint
-  // tiles; 3D 64 x 8 column blocks with 128-plane z-blocks forward, 64 x 16 with 64 adjoint
-  P->fw.tz = 32;
-  P->rv.tz = 16;
+  // default launch shapes (the autotuner or awe_plan_set_tiles choose others): 2D by
+  // default_shapes; 3D 64 x 8 column blocks with 128-plane z-blocks forward, 64 x 16 with 64 adjoint
   P->fw.ty = 8;
   P->fw.bz = 128;
   P->rv.ty = 16;
@@ -1352,6 +1389,7 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
       return AWE_OK;
     }
   }
+  P->auto_fuse = P->auto_rows[0] = P->auto_rows[1] = false;
   // one candidate list per direction; the forward probe times forward levels only, the adjoint
   // probe adjoint levels only, so each direction keeps its own fastest shape
   struct Cand { int tz, ty, bz, fuse; };
@@ -1528,6 +1566,7 @@ awe_status awe_plan_set_tiles_dir(awe_plan* P, int32_t dirs, int32_t tz, int32_t
   if (bz < 0) return fail(AWE_ERR_INVALID_ARG, "bz must be >= 0");
   for (Tiling* T : {&P->fw, &P->rv}) {
     if (!(dirs & (T == &P->fw ? 1 : 2))) continue;
+    P->auto_rows[T == &P->fw ? 0 : 1] = false;
     T->tz = tz;
     T->ty = ty;
     T->bz = bz;
@@ -1555,6 +1594,7 @@ awe_status awe_plan_set_fusion(awe_plan* P, int32_t mode) {
   if (mode < 0 || mode > AWE_FUSE_BOTH) return fail(AWE_ERR_INVALID_ARG, "fusion mode must be 0..3");
   const int changed = mode ^ P->fuse2;
   P->fuse2 = mode;
+  P->auto_fuse = false;
   // two-level kernels exist for 8, 16, 24 and 32 rows
   for (int bit : {AWE_FUSE_FORWARD, AWE_FUSE_ADJOINT}) {
     Tiling& T = bit == AWE_FUSE_FORWARD ? P->fw : P->rv;
