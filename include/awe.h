@@ -300,7 +300,7 @@ awe_status awe_checkpoint_schedule(int32_t nsteps, int32_t nslots, int32_t* acti
  * solves (and Born modelling) and one for its adjoint steps (reverse sweeps and awe_adjoint); the
  * autotuner chooses each separately.  Candidates: 2D 8, 16, 24, 32 or 64 rows of 64 columns, and -
  * where the storage mode allows it - 8, 16, 24 or 32 rows with two time levels per launch (see
- * awe_plan_set_fusion); 3D 64 x {4, 8, 16} columns with z-blocks of the full depth, of 128, 64 or
+ * awe_plan_set_fusion); 3D bricks of 64 x 8 x 8 points (ty = 8, bz = 8, the default) and 64 x {4, 8, 16} columns with z-blocks of the full depth, of 128, 64 or
  * 32 planes, and of the depth split evenly in 2 to 8 (rounded up to an even plane count).  The forward probe times the last probe_steps forward levels of the sweep (storing
  * the wavefield when the plan keeps one in FP32), the adjoint probe the last probe_steps adjoint
  * levels (with imaging when the plan keeps a wavefield; with PROBED storage both probes add to

@@ -102,6 +102,7 @@ struct awe_plan {
   // last-level cache.
   std::vector<int> order;
   std::vector<int> g_shot0, g_nshot;
+  std::vector<long long> g_pts;   // workspace points of the group's shots
   int groups_req = 0;             // 0: automatic
   int cur = 0;                    // group of the launches being issued
   // per group: the state restored by reference (FP32 slots) when its actions stopped
@@ -139,6 +140,7 @@ namespace {
 // per launch so that a launch still fills the chip.
 constexpr long long kGroupBytes = 160LL << 20;
 constexpr long long kMinGroupPoints = 8LL << 20;
+constexpr long long kLastLevelCache = 256LL << 20;
 
 struct Interp {
   int base[3];     // x, y, z base node
@@ -215,7 +217,11 @@ awe_status build_groups(awe_plan* P) {
   }
   const int G = (int)P->g_shot0.size();
   P->g_nshot.assign(G, 0);
-  for (int g = 0; g < G; ++g) P->g_nshot[g] = (g + 1 < G ? P->g_shot0[g + 1] : P->nshot) - P->g_shot0[g];
+  P->g_pts.assign(G, 0);
+  for (int g = 0; g < G; ++g) {
+    P->g_nshot[g] = (g + 1 < G ? P->g_shot0[g + 1] : P->nshot) - P->g_shot0[g];
+    for (int i = 0; i < P->g_nshot[g]; ++i) P->g_pts[g] += P->sd[order[P->g_shot0[g] + i]].npts;
+  }
   const double hd = std::pow(P->h, P->ndim);
   for (int s = 0; s < P->nshot; ++s) {
     Interp I;
@@ -711,6 +717,7 @@ awe_status step_fwd(awe_plan* P, awe::StepArgs& a, int n, int store, hipStream_t
   if (a.ntiles <= 0) return AWE_OK;
   if (awe_status st = check_step(P, P->fw, a, n, n, "forward step")) return st;
   ProfScope ps(P, 0, s);
+  a.stream = 16 * P->g_pts[P->cur] > kLastLevelCache;   // u^{k-1}, u^{k-2}, coef, u^k
   if (P->ndim == 2) AWE_HIP(awe::launch_fwd2d(a, P->fw.tz, store, s));
   else AWE_HIP(awe::launch_fwd3d(a, P->fw.ty, P->fw.bz, store, s));
   return AWE_OK;
@@ -724,11 +731,13 @@ awe_status step_adj(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s) {
       P->rv.g_inj0[P->cur] + P->rv.g_ninj[P->cur] > (int)P->rv.inj_pts.size())
     return launch_fault("receiver injection: touched points outside the table");
   ProfScope ps(P, 1, s);
+  a.stream = (a.image_src == awe::kImgNone ? 16 : 24) * P->g_pts[P->cur] > kLastLevelCache;  // and the accumulator
   if (P->ndim == 2) {
     AWE_HIP(awe::launch_adj2d(a, P->rv.tz, s));
   } else {
     AWE_HIP(awe::launch_adj3d(a, P->rv.ty, P->rv.bz, s));
-    AWE_HIP(awe::launch_inj3d(a, P->rv.g_inj0[P->cur], P->rv.g_ninj[P->cur], s));
+    if (!awe::bricks3d(P->rv.ty, P->rv.bz))
+      AWE_HIP(awe::launch_inj3d(a, P->rv.g_inj0[P->cur], P->rv.g_ninj[P->cur], s));
   }
   return AWE_OK;
 }
@@ -1307,11 +1316,9 @@ awe_status awe_plan_create(const awe_problem* prob, const awe_storage* store, aw
     return st;
   }
   // default launch shapes (the autotuner or awe_plan_set_tiles choose others): 2D by
-  // default_shapes; 3D 64 x 8 column blocks with 128-plane z-blocks forward, 64 x 16 with 64 adjoint
-  P->fw.ty = 8;
-  P->fw.bz = 128;
-  P->rv.ty = 16;
-  P->rv.bz = 64;
+  // default_shapes; 3D bricks, the fastest at every size timed (see adj3b_kernel)
+  P->fw.ty = P->rv.ty = 8;
+  P->fw.bz = P->rv.bz = 8;
   if ((st = rebuild(P, 3)) != AWE_OK) {
     awe_plan_destroy(P);
     return st;
@@ -1412,6 +1419,7 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
       const int b = ((nz + k - 1) / k + 1) & ~1;
       if (b >= 16 && std::find(bzs.begin(), bzs.end(), b) == bzs.end()) bzs.push_back(b);
     }
+    cands.push_back({32, 8, 8, 0});   // bricks
     for (int ty : {4, 8, 16})
       for (int bz : bzs) cands.push_back({32, ty, bz, 0});
   }

@@ -140,6 +140,7 @@ struct StepArgs {
   int rs_level;              // global state restored by reference from FP32 slot rs_slot
   int rs_slot;               //   (kNoLevel: none); see fwd_level
   int single;                // two-level kernels: produce level `step` alone
+  int stream;                // 3D bricks: a step's fields exceed the last-level cache
   int st_slot;               // 2D forward: also write (u^k, u^{k-1}) into this FP32 slot (-1: no)
   int nbl;
   int store_prec;            // Prec of the kept wavefield (FULL store / checkpoint slots)
@@ -217,6 +218,9 @@ hipError_t launch_adj2d2(const StepArgs& a, int tz, hipStream_t stream);
 hipError_t launch_born2d(const StepArgs& a, int tz, hipStream_t stream);
 // Two Born steps per launch (levels step, step+1); tz 8, 16, 24 or 32.
 hipError_t launch_born2d2(const StepArgs& a, int tz, hipStream_t stream);
+// 3D steps on 64 x ty columns and z-blocks of bz planes; bricks3d shapes run the brick kernels, whose
+// adjoint step injects the residual itself (no launch_inj3d).
+bool bricks3d(int ty, int bz);
 hipError_t launch_fwd3d(const StepArgs& a, int ty, int bz, int store, hipStream_t stream);
 hipError_t launch_adj3d(const StepArgs& a, int ty, int bz, hipStream_t stream);
 hipError_t launch_born3d(const StepArgs& a, int ty, int bz, hipStream_t stream);

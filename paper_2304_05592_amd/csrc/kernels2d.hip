@@ -306,7 +306,7 @@ __global__ __launch_bounds__(T2<TZ>::NT) void fwd2d_kernel(StepArgs a) {
       probe_add(probe_sums(pb, p, a.probe_r), a.probe_r, pc, (double)incr, true, nullptr, 0.0, false, a.probe_pitch);
     }
   }
-  if (S16) block_max_to_slot(lmax, scl, k);
+  if (S16) block_max_to_slot<false>(lmax, scl, k);
 }
 
 // ------------------------------------------------------------------------------ adjoint

@@ -1,6 +1,9 @@
 // 3D time-step kernels for gfx950: forward, adjoint with imaging, Born, and the adjoint's
 // receiver injection.
 //
+// Two forms: bricks of 64 x 8 x 8 points (shape ty = 8, bz = 8, the default of forward and adjoint
+// steps; described at their kernels) and the z-march of every other shape and of Born steps:
+//
 // A workgroup (4 x wave64) owns a 64 x TY column block of (x, y) and marches along z over
 // [z0, z0 + bz).  Each thread keeps a 9-deep register queue of its columns' values along z
 // (one new plane read per step, coalesced 256-byte rows), writes the current plane into a
@@ -47,6 +50,10 @@ __device__ __forceinline__ float interp8(const float* f, const ShotDev& S, int i
          w[4] * f[p + pxy] + w[5] * f[p + pxy + 1] + w[6] * f[p + pxy + px] +
          w[7] * f[p + pxy + px + 1];
 }
+
+// Source term weight * sample, fused explicitly (a product hoisted out of the source's condition
+// would be rounded by itself in some kernels and not in others).
+__device__ __forceinline__ float add_source(float lap, float w, float q) { return __builtin_fmaf(w, q, lap); }
 
 // Column block 64 x TY: 4 waves up to TY = 8, 8 waves for TY = 16 (two y-rows per thread).
 template <int TY>
@@ -263,7 +270,7 @@ void fwd3d_kernel(StepArgs a, int bzlen) {
       float lap = lap3<TY>(P[b], Q[c], ly, lane, a.c);
       const int bx = x - src_i, by = y - src_j, bzz = z - src_k;
       if ((unsigned)bx < 2u && (unsigned)by < 2u && (unsigned)bzz < 2u)
-        lap += src_weight(bx + 2 * by + 4 * bzz) * qk;
+        lap = add_source(lap, src_weight(bx + 2 * by + 4 * bzz), qk);
       const int dy = border_dist(y, ny, a.nbl);
       const float eta = a.eta_dt * (float)(dx * dx + dy * dy + dz * dz);
       const float u = Q[c][4];
@@ -304,7 +311,7 @@ void fwd3d_kernel(StepArgs a, int bzlen) {
     plane(z, hA, qA, u2A, cfA, hB, qB, u2B, cfB);
     if (z + 1 < zend) plane(z + 1, hB, qB, u2B, cfB, hA, qA, u2A, cfA);
   }
-  if (S16) block_max_to_slot(lmax, scl, k);
+  if (S16) block_max_to_slot<true>(lmax, scl, k);
 }
 
 // ------------------------------------------------------------------------------ adjoint
@@ -474,9 +481,10 @@ __global__ void inj3d_kernel(StepArgs a, int first, int count) {
     const InjEntry E = a.t.inj_ent[Pt.e_begin + e];
     s += E.w * ddj[E.r];
   }
-  const float add = reinterpret_cast<const float*>(a.ws + S.coef)[Pt.p] * s;
+  const float coef = reinterpret_cast<const float*>(a.ws + S.coef)[Pt.p];
+  const float add = coef * s;
   float* w = fbuf(a.ws, S, adj_buf(j));
-  w[Pt.p] += add;
+  w[Pt.p] = __builtin_fmaf(coef, s, w[Pt.p]);   // fused explicitly, as in the brick kernel
   if (a.image_src == kImgProbe) {
     // A_j holds C[j][level] times the step's value before injection: add C[j][level] times the
     // injected part (the sums are linear in w^j)
@@ -494,6 +502,262 @@ __global__ void inj3d_kernel(StepArgs a, int first, int count) {
           level_scale(reinterpret_cast<const float*>(a.ws + S.scale), j);
     double* acc = reinterpret_cast<double*>(a.ws + S.acc);
     acc[Pt.p] += (double)u * (double)add;
+  }
+}
+
+// ------------------------------------------------------------------------------ bricks
+// Forward and adjoint steps on bricks of 64 x 8 x 8 points: the march above needs two to three
+// microseconds per plane when there are too few blocks to hide its barrier and load latency, so a
+// grid that cannot fill the chip with long marches is cut into bricks instead.  A workgroup (8
+// waves) issues every load of its brick at once - wave w the columns of y-row w over 16 planes,
+// one halo row of the 8 planes and the x-halo of plane w - and then computes its 8 planes from LDS
+// (x and y neighbours) and registers (z neighbours) behind a single barrier.  The price is the halo
+// re-read (u^{k-1} 3.1 times, from the caches).  The adjoint injects its residual here as well, with
+// the roundings of inj3d_kernel, instead of in a launch of its own.
+// Measured, us per level, march (best of all blocks) -> bricks: see default_shapes.
+constexpr int kBY = 8, kBZ = 8;           // brick rows (one per wave) and planes
+constexpr int kBT = 64 * kBY;
+constexpr int kBH = kBY + 2 * kHalo;      // 16 LDS rows
+constexpr int kBW = kTX + 2 * kHalo;      // 72 LDS columns
+
+// This thread's share of a brick of level f: its own column over the planes z0-4 .. z0+11 (Q), one
+// row of the y-halo over the brick's planes, one point of the x-halo.
+struct BrickLoad {
+  float Q[kBZ + 2 * kHalo], yh[kBZ], xh;
+  int hr, xr, xc;                          // LDS row of yh; row and column of xh
+
+  __device__ __forceinline__ void issue(const Planes& f, const TileDev& T, int cv, int nx, int ny, int px) {
+    const int lane = threadIdx.x & 63, w = wave_id();
+    hr = w < kHalo ? w : w + kBY;
+    const int cvh = col_off(T.x0 + lane, T.y0 - kHalo + hr, nx, ny, px, 4);
+    xr = kHalo + (lane >> 3);
+    xc = (lane & 7) < kHalo ? (lane & 7) : kTX + (lane & 7);
+    const int cvx = col_off(T.x0 - kHalo + xc, T.y0 - kHalo + xr, nx, ny, px, 4);
+#pragma unroll
+    for (int t = 0; t < kBZ + 2 * kHalo; ++t) Q[t] = ldp(f, cv, T.z0 - kHalo + t);
+#pragma unroll
+    for (int t = 0; t < kBZ; ++t) yh[t] = ldp(f, cvh, T.z0 + t);
+    xh = ldp(f, cvx, T.z0 + w);
+  }
+  __device__ __forceinline__ void commit(float (*P)[kBH][kBW]) const {
+    const int lane = threadIdx.x & 63, w = wave_id();
+#pragma unroll
+    for (int t = 0; t < kBZ; ++t) P[t][w + kHalo][lane + kHalo] = Q[t + kHalo];
+#pragma unroll
+    for (int t = 0; t < kBZ; ++t) P[t][hr][lane + kHalo] = yh[t];
+    P[w][xr][xc] = xh;
+  }
+};
+
+// Laplacian at plane t of the brick (the sum's order is lap3's).
+__device__ __forceinline__ float lap_brick(const float (*P)[kBH][kBW], const float (&Q)[kBZ + 2 * kHalo], int t,
+                                           const float* c) {
+  const float* p = &P[t][wave_id() + kHalo][(threadIdx.x & 63) + kHalo];
+  const float u = Q[t + kHalo];
+  float s = 0.f;
+#pragma unroll
+  for (int r = kHalo; r >= 1; --r) {
+    s += c[r] * ((p[-r] - u) + (p[r] - u));
+    s += c[r] * ((p[-r * kBW] - u) + (p[r * kBW] - u));
+    s += c[r] * ((Q[t + kHalo - r] - u) + (Q[t + kHalo + r] - u));
+  }
+  return s;
+}
+
+template <int SK, bool NT>
+__global__ __launch_bounds__(kBT) void fwd3b_kernel(StepArgs a) {
+  __shared__ float P[kBZ][kBH][kBW];
+  const int tid = xcd_tile(blockIdx.x, a.ntiles);
+  const TileDev T = a.t.tiles[a.tile_base + tid];
+  const ShotDev& S = a.t.shots[T.shot];
+  const int k = a.step - S.off;
+  if (k < 1 || k >= S.nt) return;
+  const int nx = S.nx, ny = S.ny, nz = S.nz, px = S.px;
+  const long long plane4 = 4LL * px * ny;
+  // levels below 1 are zero and are not read (see fwd3d_kernel)
+  const float* u1p = fwd_level(a, S, k - 1);
+  const Planes u1 = planes(u1p, nz, k >= 2 ? nz : 0, plane4);
+  const Planes u2 = planes(fwd_level(a, S, k - 2), nz, k >= 3 ? nz : 0, plane4);
+  const Planes cf = planes(a.ws + S.coef, nz, nz, plane4);
+  const brsrc rout = make_rsrc(fbuf(a.ws, S, fwd_buf(k)), (int)(nz * plane4));
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const int x = T.x0 + lane, y = T.y0 + w;
+  const int cv = col_off(x, y, nx, ny, px, 4), cv2 = col_off(x, y, nx, ny, px, 2);
+
+  BrickLoad B;
+  B.issue(u1, T, cv, nx, ny, px);
+  float pu2[kBZ], pcf[kBZ];
+#pragma unroll
+  for (int t = 0; t < kBZ; ++t) {
+    pu2[t] = NT ? ldp_nt(u2, cv, T.z0 + t) : ldp(u2, cv, T.z0 + t);
+    pcf[t] = NT ? ldp_nt(cf, cv, T.z0 + t) : ldp(cf, cv, T.z0 + t);
+  }
+  if (a.d != nullptr) {
+    for (int t = threadIdx.x; t < T.gat_count; t += kBT) {
+      const RecDev R = a.t.recs[T.gat_begin + t];
+      a.d[S.d + (long long)(k - 1) * S.nrec + R.r] = k >= 2 ? interp8(u1p, S, R.i, R.j, R.k, R.w) : 0.f;
+    }
+  }
+  const float qk = a.q[S.q + k - 1];
+  const int src_k = S.src_k;
+  const bool src_col = (unsigned)(x - S.src_i) < 2u && (unsigned)(y - S.src_j) < 2u;
+  const int sc = src_col ? (x - S.src_i) + 2 * (y - S.src_j) : 0;
+  const float sw0 = S.src_w[sc], sw1 = S.src_w[sc + 4];
+  // FULL store: level k (FP32) or level k-1 (16 bits, quantised once its scale is complete)
+  constexpr bool S16 = SK == kStoreBF16 || SK == kStoreFP16;
+  const brsrc rst = SK == kStoreF32
+      ? make_rsrc(reinterpret_cast<float*>(a.ws + S.store) + (long long)k * S.npts, (int)(nz * plane4))
+      : make_rsrc_uniform(reinterpret_cast<unsigned short*>(a.ws + S.store) + (long long)(k - 1) * S.npts,
+                          S16 ? (int)(nz * plane4 / 2) : 0);
+  float* scl = S16 ? reinterpret_cast<float*>(a.ws + S.scale) : nullptr;
+  const float inv_prev = S16 && k >= 2 ? inv_scale(level_scale(scl, k - 1)) : 0.f;
+  double* pb = SK == kStoreProbe ? reinterpret_cast<double*>(a.ws + S.store) : nullptr;
+  const float* pcol = SK == kStoreProbe ? a.probe_c + k : nullptr;
+  const long long plane_pts = (long long)px * ny;
+  // squared distances are sums of small integers, exact in float
+  const float dx = (float)border_dist(x, nx, a.nbl), dy = (float)border_dist(y, ny, a.nbl);
+  const float dxy = dx * dx + dy * dy;
+  B.commit(P);
+  __syncthreads();
+
+  float lmax = 0.f;
+#pragma unroll
+  for (int t = 0; t < kBZ; ++t) {
+    // every lane computes; the stores of points outside the grid are dropped
+    const int z = T.z0 + t;
+    float lap = lap_brick(P, B.Q, t, a.c);
+    if ((unsigned)(z - src_k) < 2u && src_col) lap = add_source(lap, z == src_k ? sw0 : sw1, qk);
+    const float dz = (float)border_dist(z, nz, a.nbl);
+    const float eta = a.eta_dt * (dxy + dz * dz);
+    const float u = B.Q[t + kHalo];
+    const float incr = pcf[t] * (lap - eta * (u - pu2[t]));
+    const float un = (u + u - pu2[t]) + incr;
+    const int zo = z < nz ? z * (int)plane4 : kZOOB;
+    if (NT) stb_nt(rout, un, cv, zo);
+    else stb(rout, un, cv, zo);
+    if (SK == kStoreF32) stb_nt(rst, un, cv, zo);
+    if (S16) {
+      lmax = fmaxf(lmax, fabsf(un));
+      if (k >= 2) stb16_nt(rst, enc16(u * inv_prev, SK == kStoreBF16), cv2, z < nz ? zo / 2 : kZOOB);
+    }
+    if (SK == kStoreProbe && cv != kOOB && z < nz)
+      probe_add(probe_sums(pb, z * plane_pts + (cv >> 2), a.probe_r), a.probe_r, pcol, (double)incr, true, nullptr, 0.0,
+                false, a.probe_pitch);
+  }
+  if (S16) block_max_to_slot<true>(lmax, scl, k);
+}
+
+template <int IMG, bool NT>
+__global__ __launch_bounds__(kBT) void adj3b_kernel(StepArgs a) {
+  __shared__ float P[kBZ][kBH][kBW];
+  const int tid = xcd_tile(blockIdx.x, a.ntiles);
+  const TileDev T = a.t.tiles[a.tile_base + tid];
+  const ShotDev& S = a.t.shots[T.shot];
+  const int j = a.step - S.off;
+  if (j < 1 || j >= S.nt) return;
+  const int nx = S.nx, ny = S.ny, nz = S.nz, px = S.px;
+  const long long plane4 = 4LL * px * ny;
+  const float* w1p = fbuf(a.ws, S, adj_buf(j + 1));
+  const Planes w1 = planes(w1p, nz, nz, plane4);
+  const Planes w2 = planes(fbuf(a.ws, S, adj_buf(j + 2)), nz, nz, plane4);
+  const Planes cf = planes(a.ws + S.coef, nz, nz, plane4);
+  const brsrc rout = make_rsrc(fbuf(a.ws, S, adj_buf(j)), (int)(nz * plane4));
+  const void* ubase = IMG == kImgBuffers ? (const void*)fwd_level(a, S, j)
+                      : IMG == kImgFull32 ? (const void*)(reinterpret_cast<const float*>(a.ws + S.store) + (long long)j * S.npts)
+                      : (const void*)(reinterpret_cast<const unsigned short*>(a.ws + S.store) + (long long)j * S.npts);
+  constexpr bool I16 = IMG == kImgFullBF16 || IMG == kImgFullFP16;
+  constexpr bool IACC = IMG != kImgNone && IMG != kImgProbe;  // imaging into the FP64 accumulator
+  const Planes uj = planes(ubase, nz, IACC ? nz : 0, I16 ? plane4 / 2 : plane4);
+  const float usc = I16 ? level_scale(reinterpret_cast<const float*>(a.ws + S.scale), j) : 1.f;
+  const Planes acc = planes(a.ws + S.acc, nz, IACC ? nz : 0, 2 * plane4);
+  const brsrc racc = make_rsrc(a.ws + S.acc, IACC ? (int)(nz * 2 * plane4) : 0);
+  double* pa = IMG == kImgProbe ? reinterpret_cast<double*>(a.ws + S.store) + (long long)a.probe_r * S.npts : nullptr;
+  const float* pcol = IMG == kImgProbe ? a.probe_c + j : nullptr;
+  const long long plane_pts = (long long)px * ny;
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const int x = T.x0 + lane, y = T.y0 + w;
+  const int cv = col_off(x, y, nx, ny, px, 4), cvu = col_off(x, y, nx, ny, px, I16 ? 2 : 4);
+  const int cv8 = col_off(x, y, nx, ny, px, 8);
+
+  BrickLoad B;
+  B.issue(w1, T, cv, nx, ny, px);
+  float pw2[kBZ], pcf[kBZ], pu[kBZ];
+  double pacc[kBZ];
+#pragma unroll
+  for (int t = 0; t < kBZ; ++t) {
+    const int z = T.z0 + t;
+    pw2[t] = NT ? ldp_nt(w2, cv, z) : ldp(w2, cv, z);
+    pcf[t] = NT ? ldp_nt(cf, cv, z) : ldp(cf, cv, z);
+    pu[t] = 0.f;
+    pacc[t] = 0.0;
+    if (I16) pu[t] = dec16(ldp16_nt(uj, cvu, z), IMG == kImgFullBF16) * usc;
+    else if (IMG == kImgFull32) pu[t] = ldp_nt(uj, cvu, z);
+    else if (IACC) pu[t] = ldp(uj, cvu, z);
+    if (IACC) pacc[t] = NT ? ldp64_nt(acc, cv8, z) : ldp64(acc, cv8, z);
+  }
+  if (a.v != nullptr && a.tile_base + tid == S.src_tile && threadIdx.x == 0)
+    a.v[S.q + j] = interp8(w1p, S, S.src_i, S.src_j, S.src_k, S.src_w);
+  const float dx = (float)border_dist(x, nx, a.nbl), dy = (float)border_dist(y, ny, a.nbl);
+  const float dxy = dx * dx + dy * dy;
+  B.commit(P);
+  __syncthreads();
+
+  float wn[kBZ];
+#pragma unroll
+  for (int t = 0; t < kBZ; ++t) {
+    const int z = T.z0 + t;
+    __builtin_amdgcn_sched_barrier(0);   // one plane after the other: interleaved they take 185 registers
+    const float lap = lap_brick(P, B.Q, t, a.c);
+    const float dz = (float)border_dist(z, nz, a.nbl);
+    const float eta = a.eta_dt * (dxy + dz * dz);
+    const float u = B.Q[t + kHalo];
+    const float incr = pcf[t] * (lap - eta * (u - pw2[t]));
+    wn[t] = (u + u - pw2[t]) + incr;
+    if (IACC) pacc[t] = pacc[t] + (double)pu[t] * (double)incr;
+  }
+  float add[kBZ] = {}, wi[kBZ];            // probe: the injected part, and the level before it
+#pragma unroll
+  for (int t = 0; t < kBZ; ++t) wi[t] = wn[t];
+  const bool inj = a.dd != nullptr && T.inj_count > 0;
+  if (inj) {
+    // w^j += coef P_r^T dd^j at the touched points, as inj3d_kernel does after the march: the sums go
+    // through the brick's LDS
+    const float* ddj = a.dd + S.d + (long long)j * S.nrec;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kBZ; ++t) P[t][w][lane] = 0.f;
+    __syncthreads();
+    for (int i = threadIdx.x; i < T.inj_count; i += kBT) {
+      const InjPoint Pt = a.t.inj_pts[T.inj_begin + i];
+      float s = 0.f;
+      for (int e = 0; e < Pt.e_count; ++e) {
+        const InjEntry E = a.t.inj_ent[Pt.e_begin + e];
+        s += E.w * ddj[E.r];
+      }
+      P[Pt.lz][Pt.ly][Pt.lx] = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kBZ; ++t) {
+      const float s = P[t][w][lane];
+      if (s != 0.f) {
+        add[t] = pcf[t] * s;
+        wn[t] = __builtin_fmaf(pcf[t], s, wn[t]);
+        if (IACC) pacc[t] = pacc[t] + (double)pu[t] * (double)add[t];
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < kBZ; ++t) {
+    const int z = T.z0 + t;
+    const int zo = z < nz ? z * (int)plane4 : kZOOB;
+    if (NT) stb_nt(rout, wn[t], cv, zo);
+    else stb(rout, wn[t], cv, zo);
+    if (IACC && NT) stb64_nt(racc, pacc[t], cv8, z < nz ? 2 * zo : kZOOB);
+    if (IACC && !NT) stb64(racc, pacc[t], cv8, z < nz ? 2 * zo : kZOOB);
+    if (IMG == kImgProbe && cv != kOOB && z < nz)
+      probe_add(probe_sums(pa, z * plane_pts + (cv >> 2), a.probe_r), a.probe_r, pcol, (double)wi[t], true, pcol,
+                (double)add[t], inj && add[t] != 0.f, a.probe_pitch);
   }
 }
 
@@ -601,7 +865,7 @@ __global__ __launch_bounds__(T3<TY>::NT) void born3d_kernel(StepArgs a, int bzle
       float lap = lap3<TY>(PU[b], QU[c], ly, lane, a.c);
       const int bx = x - src_i, by = y - src_j, bzz = z - src_k;
       if ((unsigned)bx < 2u && (unsigned)by < 2u && (unsigned)bzz < 2u)
-        lap += src_weight(bx + 2 * by + 4 * bzz) * qk;
+        lap = add_source(lap, src_weight(bx + 2 * by + 4 * bzz), qk);
       const float u = QU[c][4];
       const float incr = pcf[c] * (lap - eta * (u - pu2[c]));
       stb(ruo, (u + u - pu2[c]) + incr, cv[c], zo);
@@ -662,11 +926,44 @@ hipError_t adj3d_ty(const StepArgs& a, int bz, hipStream_t s) {
 
 }  // namespace
 
+namespace {
+template <bool NT>
+hipError_t fwd3b(const StepArgs& a, int store, hipStream_t s) {
+  switch (store) {
+    case kStoreNone: fwd3b_kernel<kStoreNone, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    case kStoreF32: fwd3b_kernel<kStoreF32, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    case kStoreBF16: fwd3b_kernel<kStoreBF16, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    case kStoreFP16: fwd3b_kernel<kStoreFP16, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    case kStoreProbe: fwd3b_kernel<kStoreProbe, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <bool NT>
+hipError_t adj3b(const StepArgs& a, hipStream_t s) {
+  switch (a.image_src) {
+    case kImgNone: adj3b_kernel<kImgNone, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    case kImgFull32: adj3b_kernel<kImgFull32, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    case kImgBuffers: adj3b_kernel<kImgBuffers, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    case kImgFullBF16: adj3b_kernel<kImgFullBF16, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    case kImgFullFP16: adj3b_kernel<kImgFullFP16, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    case kImgProbe: adj3b_kernel<kImgProbe, NT><<<a.ntiles, kBT, 0, s>>>(a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+}  // namespace
+
+// The shape 8 x 8 runs on bricks.
+bool bricks3d(int ty, int bz) { return ty == kBY && bz == kBZ; }
+
 // bz <= 0 means one block spans the whole depth of every shot.
 static int zlen(int bz) { return bz > 0 ? bz : 0x7fffffff; }
 
 hipError_t launch_fwd3d(const StepArgs& a, int ty, int bz, int store, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
+  if (bricks3d(ty, bz)) return a.stream ? fwd3b<true>(a, store, s) : fwd3b<false>(a, store, s);
   switch (ty) {
     case 4: return fwd3d_ty<4>(a, zlen(bz), store, s);
     case 8: return fwd3d_ty<8>(a, zlen(bz), store, s);
@@ -677,6 +974,7 @@ hipError_t launch_fwd3d(const StepArgs& a, int ty, int bz, int store, hipStream_
 
 hipError_t launch_adj3d(const StepArgs& a, int ty, int bz, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
+  if (bricks3d(ty, bz)) return a.stream ? adj3b<true>(a, s) : adj3b<false>(a, s);
   switch (ty) {
     case 4: return adj3d_ty<4>(a, zlen(bz), s);
     case 8: return adj3d_ty<8>(a, zlen(bz), s);

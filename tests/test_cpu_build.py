@@ -116,3 +116,14 @@ def test_probed_gradient_on_the_cpu_build(emu_lib):
     assert res["rademacher"] <= 1e-5 and res["identity"] <= 1e-5 and res["identity_vs_exact"] <= 1e-5
     assert res["shape_invariant"]
     assert res["rademacher3d"] <= 1e-5 and res["shape_invariant3d"]
+
+
+def test_3d_bricks_on_the_cpu_build(emu_lib):
+    """3D steps on bricks against the z-march, on a grid with remainders on every axis, under
+    AddressSanitizer with the host launch checks on: bitwise, every storage that runs on them."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_bricks.py")], emu_lib, timeout=600)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    print(res)
+    assert all(res["bitwise"].values())

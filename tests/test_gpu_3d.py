@@ -121,3 +121,25 @@ def test_3d_shot_groups_do_not_change_results():
         torch.cuda.synchronize()
         outs.append([t.cpu() for t in (g, v, d)])
     assert all(torch.equal(a, b) for a, b in zip(outs[1], outs[0]))
+
+
+@pytest.mark.parametrize("prec", [A.PREC_FP32, A.PREC_BF16, A.PREC_FP16], ids=["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("n", [(8, 7, 55), (9, 8, 56), (7, 13, 121)], ids=["16x15x63", "17x16x64", "15x21x129"])
+def test_3d_bricks_are_bitwise_the_march(n, prec):
+    """Bricks of 64 x 8 x 8 (shape ty = 8, bz = 8) at their edges - one brick and one plane, row or column
+    more or less - against the z-march: gradient, F^T dd, traces and F^T dd alone are bitwise the same (the
+    same arithmetic per point, the injected residual rounded as by the march's separate pass)."""
+    wl = W.small_3d(n=n, nbl=4, T=60.0, nrec_side=6, nshot=2)
+    dd = [W.synthetic_residual(s.nt, len(s.rec), wl.dt, wl.f0, 5 + i) for i, s in enumerate(wl.shots)]
+    outs = []
+    for ty, bz in ((8, 8), (16, 64)):
+        plan = make_plan(wl, storage=A.Storage(A.STORE_FULL, 0, prec))
+        plan.set_tiles(ty=ty, bz=bz)
+        m, q = gpu_inputs(wl, plan)
+        ddt = plan.pack(dd, "d")
+        g, v, d = plan.gradient(m, q, ddt, v=True, d=True)
+        va = plan.adjoint(m, ddt)
+        torch.cuda.synchronize()
+        outs.append([t.cpu() for t in (g, v, d, va)])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b) and torch.isfinite(a).all() and a.abs().max() > 0
