@@ -463,20 +463,46 @@ bool one_level_too(const awe_plan* P, int bit) {
          (bit == AWE_FUSE_FORWARD && P->store.mode == AWE_STORE_CHECKPOINT);
 }
 
-// Launch shapes of the directions the caller has not set, from the storage and the work of a launch
-// (the largest shot group's).
+// Tiles w columns wide and 24 rows high of a launch (the largest shot group's).
+long long tiles24(const awe_plan* P, int w) {
+  long long n = 0;
+  for (size_t g = 0; g < P->g_shot0.size(); ++g) {
+    long long t = 0;
+    for (int i = 0; i < P->g_nshot[g]; ++i) {
+      const ShotDev& d = P->sd[P->order[P->g_shot0[g] + i]];
+      t += (long long)((d.nx + w - 1) / w) * ((d.nz + 23) / 24);
+    }
+    n = std::max(n, t);
+  }
+  return n;
+}
+
+// Width of the two-level kernels' tiles: 128 columns (two per lane) cost 8 % less per column than 64 (one
+// per lane) forward and 5 % less in reverse, but more of them hang over the right edge, and a launch
+// of few tiles is bound by the chain of one.  us per launch, forward with store / reverse, 64 and 128
+// wide, best rows of each: one shot of 281 x 181 4.0, 4.6 / 4.8, 5.5; one of 730 x 421 (n128 = 108)
+// 5.5, 5.8 / 6.8, 7.2; one of 1104 x 592 (225) 6.9, 6.8 / 8.7, 8.9; four of 730 x 421 (432) 10.1, 9.2 / 13.0,
+// 12.8; sixteen 24.3, 23.3 / 39.2, 38.0; 17 of 262 x 559 (384 instead of 320 columns) 15.5, 18.2 / 25.6, 28.1.
+bool wide_tiles(const awe_plan* P, int bit) {
+  const long long n128 = tiles24(P, 128), n64 = tiles24(P, 64);
+  return n128 >= 220 && n64 * (bit == AWE_FUSE_FORWARD ? 1.08 : 1.05) >= 2.0 * n128;
+}
+
+// Launch shapes of the directions the caller has not set, from the storage and the work of a launch.
 //
 // 2D: two levels per launch, except for CHECKPOINT storage, whose launches stay one level each unless
 // asked otherwise, and for a 16-bit FULL store, whose kernels are one-level.  Two levels won at every
-// size timed: one shot of 281 x 181 2.3 -> 1.4 ms forward; one shot of 730 x 421 (1200 samples) 10.6 ->
-// 8.0 ms gradient; 24 shots of 592 x 336 (600 samples) 27.5 -> 19.7.  Tile rows follow the count of
-// 24-row tiles n: few tiles are bound by the chain of one tile, so its rows are cut; many by the
-// halo, so they grow.  us per launch, forward with store / reverse, at 8, 16, 24, 32 rows:
-//   n = 24:   4.6, 5.4, 6.1, 6.7    /  5.7, 6.7, 7.8, 8.9
-//   n = 108:  6.2, 5.9, 6.6, 7.4    /  7.4, 7.4, 8.5, 9.8
-//   n = 450:  11.5, 9.7, 9.4, 10.7  /  15.2, 13.5, 13.2, 14.9
-//   n = 900:  17.6, 15.9, 15.5, 16.0 / 26.7, 24.4, 24.6, 23.2
-//   n = 1800: 31.6, 25.2, 24.5, 26.8 / 50.0, 42.8, 41.3, 40.2
+// size timed: one shot of 281 x 181 2.3 -> 1.2 ms forward; one shot of 730 x 421 (1200 samples) 10.6 ->
+// 7.4 ms gradient; 24 shots of 592 x 336 (600 samples) 27.5 -> 18.
+// Tile rows follow the number of tiles: few are bound by the chain of one tile, so its rows are cut;
+// many by the halo, so they grow.  us per launch, forward with store / reverse, at 8, 16, 24, 32 rows:
+//   64 wide, n =   40:  4.0, 4.4, 4.9, 5.5     /  4.8, 5.6, 6.2, 7.2
+//   64 wide, n =  160:  5.0, 4.8, 5.3, 5.9     /  6.0, 6.3, 6.9, 7.8
+//   64 wide, n =  216:  6.3, 6.0, 5.5, 6.1     /  7.2, 7.2, 6.8, 7.8
+//   64 wide, n =  560:  10.6, 8.4, 8.3, 8.0    /  12.0, 10.1, 10.1, 10.6
+//   64 wide, n = 2560:  33.8, 23.3, 19.8, 19.3 /  44.1, 35.2, 33.9, 33.2
+//  128 wide, n =  432:  10.8, 9.6, 9.2, 10.5   /  14.9, 12.8, 14.1, 15.0
+//  128 wide, n = 1728:  32.0, 25.0, 23.3, 26.5 /  47.6, 39.6, 38.0, 40.7
 // Probe sums, which dwarf the fields' traffic, prefer few rows at every size: 8 shots of 730 x 421 with 8
 // probes (400 samples) take 28.5, 29.9, 32.5, 34.6 ms.
 void default_shapes(awe_plan* P) {
@@ -484,18 +510,18 @@ void default_shapes(awe_plan* P) {
   const bool one_level = P->store.mode == AWE_STORE_CHECKPOINT ||
                          (P->store.mode == AWE_STORE_FULL && P->store.prec != AWE_PREC_FP32);
   if (P->auto_fuse) P->fuse2 = one_level ? AWE_FUSE_NONE : AWE_FUSE_BOTH;
-  long long n = 0;
-  for (size_t g = 0; g < P->g_shot0.size(); ++g) {
-    long long t = 0;
-    for (int i = 0; i < P->g_nshot[g]; ++i) {
-      const ShotDev& d = P->sd[P->order[P->g_shot0[g] + i]];
-      t += (long long)((d.nx + awe::kTX2 - 1) / awe::kTX2) * ((d.nz + 23) / 24);
-    }
-    n = std::max(n, t);
-  }
-  if (P->store.mode == AWE_STORE_PROBED) n = 0;
-  if (P->auto_rows[0]) P->fw.tz = !(P->fuse2 & AWE_FUSE_FORWARD) ? 32 : n < 64 ? 8 : n < 384 ? 16 : 24;
-  if (P->auto_rows[1]) P->rv.tz = !(P->fuse2 & AWE_FUSE_ADJOINT) ? 16 : n < 144 ? 8 : n < 512 ? 16 : 32;
+  const bool probed = P->store.mode == AWE_STORE_PROBED;
+  const long long n64 = tiles24(P, 64), n128 = tiles24(P, 128);
+  if (P->auto_rows[0])
+    P->fw.tz = !(P->fuse2 & AWE_FUSE_FORWARD) ? 32
+               : probed ? 8
+               : wide_tiles(P, AWE_FUSE_FORWARD) ? 24
+               : n64 < 100 ? 8 : n64 < 200 ? 16 : n64 < 500 ? 24 : 32;
+  if (P->auto_rows[1])
+    P->rv.tz = !(P->fuse2 & AWE_FUSE_ADJOINT) ? 16
+               : probed ? 8
+               : wide_tiles(P, AWE_FUSE_ADJOINT) ? (n128 < 600 ? 16 : 24)
+               : n64 < 200 ? 8 : n64 < 800 ? 24 : 32;
 }
 
 // Shot groups and the tilings of the directions in `dirs` (bit 0 forward, bit 1 adjoint; the
@@ -509,7 +535,7 @@ awe_status rebuild(awe_plan* P, int dirs) {
     if (!(dirs & bit)) continue;
     Tiling& one = bit == AWE_FUSE_FORWARD ? P->fw : P->rv;
     Tiling& two = bit == AWE_FUSE_FORWARD ? P->fw2 : P->rv2;
-    two.tx = awe::kTX2;
+    two.tx = wide_tiles(P, bit) ? 128 : 64;
     two.tz = one.tz;
     const bool fused = fused_ok(P, bit);
     for (Tiling* T : {&one, &two}) {
@@ -751,7 +777,7 @@ awe_status step_fwd2(awe_plan* P, awe::StepArgs& a, int n, int store, hipStream_
   if (a.ntiles <= 0) return AWE_OK;
   if (awe_status st = check_step(P, P->fw2, a, n, last, "two-level forward step")) return st;
   ProfScope ps(P, 0, s);
-  AWE_HIP(awe::launch_fwd2d2(a, P->fw2.tz, store, s));
+  AWE_HIP(awe::launch_fwd2d2(a, P->fw2.tx, P->fw2.tz, store, s));
   return AWE_OK;
 }
 
@@ -761,7 +787,7 @@ awe_status step_adj2(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s, bool s
   if (a.ntiles <= 0) return AWE_OK;
   if (awe_status st = check_step(P, P->rv2, a, single ? n : n - 1, n, "two-level adjoint step")) return st;
   ProfScope ps(P, 1, s);
-  AWE_HIP(awe::launch_adj2d2(a, P->rv2.tz, s));
+  AWE_HIP(awe::launch_adj2d2(a, P->rv2.tx, P->rv2.tz, s));
   return AWE_OK;
 }
 
@@ -1877,7 +1903,7 @@ awe_status awe_born(awe_plan* P, const float* m, const float* q, const float* dm
         if ((st = check_step(P, T, a, n, two ? n + 1 : n, "Born step")) != AWE_OK) return st;
         ProfScope ps(P, 2, s);
         if (P->ndim == 3) AWE_HIP(awe::launch_born3d(a, T.ty, T.bz, s));
-        else if (fuse) AWE_HIP(awe::launch_born2d2(a, T.tz, s));
+        else if (fuse) AWE_HIP(awe::launch_born2d2(a, T.tx, T.tz, s));
         else AWE_HIP(awe::launch_born2d(a, T.tz, s));
       }
       n += two ? 2 : 1;

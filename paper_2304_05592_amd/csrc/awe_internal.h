@@ -12,8 +12,8 @@
 namespace awe {
 
 constexpr int kThreads = 256;   // 4 wave64 per workgroup
-constexpr int kTX = 64;         // tile width: one wavefront spans the tile row (one column per lane)
-constexpr int kTX2 = 128;       // tile width of the 2D two-level kernels (two columns per lane)
+constexpr int kTX = 64;         // tile width: one wavefront spans the tile row (the 2D two-level kernels'
+                                // tiles are 64 or 128 wide)
 constexpr int kHalo = 4;        // stencil radius (8th order)
 constexpr int kPitch = 64;      // workspace rows are padded to a multiple of 64 elements, so
                                 // that every 64-column row segment starts on a 256-byte line
@@ -212,12 +212,12 @@ hipError_t launch_fwd2d(const StepArgs& a, int tz, int store, hipStream_t stream
 hipError_t launch_store_last(const StepArgs& a, int nshot, long long max_npts, hipStream_t stream);
 hipError_t launch_adj2d(const StepArgs& a, int tz, hipStream_t stream);
 // Two 2D steps per launch (levels step, step+1 forward; step, step-1 adjoint); tz 8, 16, 24 or 32,
-// on tiles kTX2 wide.
-hipError_t launch_fwd2d2(const StepArgs& a, int tz, int store, hipStream_t stream);
-hipError_t launch_adj2d2(const StepArgs& a, int tz, hipStream_t stream);
+// on tiles of tx columns (64, one column per lane, or 128, two).
+hipError_t launch_fwd2d2(const StepArgs& a, int tx, int tz, int store, hipStream_t stream);
+hipError_t launch_adj2d2(const StepArgs& a, int tx, int tz, hipStream_t stream);
 hipError_t launch_born2d(const StepArgs& a, int tz, hipStream_t stream);
 // Two Born steps per launch (levels step, step+1); tz 8, 16, 24 or 32.
-hipError_t launch_born2d2(const StepArgs& a, int tz, hipStream_t stream);
+hipError_t launch_born2d2(const StepArgs& a, int tx, int tz, hipStream_t stream);
 // 3D steps on 64 x ty columns and z-blocks of bz planes; bricks3d shapes run the brick kernels, whose
 // adjoint step injects the residual itself (no launch_inj3d).
 bool bricks3d(int ty, int bz);

@@ -500,201 +500,242 @@ __global__ __launch_bounds__(T2<TZ>::NT) void born2d_kernel(StepArgs a) {
 //
 // These kernels issue vector instructions most of their time (a launch without a store, its fields
 // in the last-level cache, ran at the vector units' rate with 93 lane-operations per point and
-// level), so the work per point is cut: a lane owns two adjacent columns (8-byte global and LDS
+// level), so the work per point is cut: a lane owns V adjacent columns (V = 2: 8-byte global and LDS
 // accesses, one set of address and row work for two points) and RA or RB consecutive rows, whose
 // z-neighbours it reads from LDS once (N + 8 reads for N rows instead of 9 N); along x a difference
-// u(b) - u(a) that serves the stencils of both points is formed once.  A row of the tile is one
+// u(b) - u(a) that serves the stencils of two of its points is formed once.  A row of the tile is one
 // wave, so row offsets stay wave-uniform.  Rows are kept apart for the scheduler: mixed, they took 125
-// registers instead of 80 (24-row forward) and lost more to occupancy than they gained.
-// Measured, 16 shots of 730 x 421, per launch of two levels, against one column per lane on tiles of
-// 64 columns: forward without store 23.4 -> 20.9 us, with FP32 store 24.7 -> 22.9, reverse with
-// imaging 41.4 -> 39.3.
-typedef float f32x2 __attribute__((ext_vector_type(2)));
+// registers instead of 80 (24-row forward, V = 2) and lost more to occupancy than they gained.
+// V = 1 (64-column tiles) wastes fewer columns where the width is no multiple of 128 and shortens the
+// chain of a small launch; wide_tiles holds the rule.
+// Measured, 16 shots of 730 x 421, us per launch of two levels, against one column and row at a time:
+// forward without store 23.4 -> 21.3 (V = 2), with FP32 store 24.7 -> 23.3, reverse with imaging 41.4 ->
+// 38.0; one shot of 281 x 181, against one level per launch twice: forward 7.4 -> 4.0.
+// V adjacent columns of a lane.
+template <int V>
+struct VecOf {
+  typedef float f32 __attribute__((ext_vector_type(V)));
+  typedef double f64 __attribute__((ext_vector_type(V)));
+};
+template <int V>
+using fv = typename VecOf<V>::f32;
+template <int V>
+using dv = typename VecOf<V>::f64;
 
-__device__ __forceinline__ f32x2 ldp2(const Planes& f, int voff, int z) {
-  return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(f.r, voff, slice_off(f, z), 0));
+template <int V, int AUX = 0>
+__device__ __forceinline__ fv<V> ldv(brsrc r, int voff, int soff) {
+  if constexpr (V == 2) return __builtin_bit_cast(fv<V>, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, AUX));
+  else return __builtin_bit_cast(fv<V>, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, AUX));
 }
-__device__ __forceinline__ f32x2 ldp2_nt(const Planes& f, int voff, int z) {
-  return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(f.r, voff, slice_off(f, z), kNT));
+template <int V, int AUX = 0>
+__device__ __forceinline__ fv<V> ldpv(const Planes& f, int voff, int z) {
+  return ldv<V, AUX>(f.r, voff, slice_off(f, z));
 }
-__device__ __forceinline__ f32x2 ldp2_at(const Planes& f, int off) {
-  return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(f.r, off, f.nzv > 0 ? 0 : kZOOB, 0));
+template <int V>
+__device__ __forceinline__ fv<V> ldpv_at(const Planes& f, int off) {
+  return ldv<V>(f.r, off, f.nzv > 0 ? 0 : kZOOB);
 }
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void stb2(brsrc r, f32x2 v, int voff, int soff) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
+template <int V, int AUX = 0>
+__device__ __forceinline__ void stv(brsrc r, fv<V> v, int voff, int soff) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  if constexpr (V == 2) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, voff, soff, AUX);
+  else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), r, voff, soff, AUX);
 }
-__device__ __forceinline__ void stb2_nt(brsrc r, f32x2 v, int voff, int soff) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, kNT);
+template <int V>
+__device__ __forceinline__ dv<V> ldpacc(const Planes& f, int voff, int z) {
+  if constexpr (V == 2) return ldp64x2(f, voff, z);
+  else return dv<V>{ldp64(f, voff, z)};
+}
+template <int V>
+__device__ __forceinline__ void stacc(brsrc r, dv<V> v, int voff, int soff) {
+  if constexpr (V == 2) stb64x2(r, v, voff, soff);
+  else stb64(r, v[0], voff, soff);
+}
+template <int V>
+__device__ __forceinline__ fv<V>& lds(float& p) {
+  return *reinterpret_cast<fv<V>*>(&p);
+}
+template <int V>
+__device__ __forceinline__ const fv<V>& lds(const float& p) {
+  return *reinterpret_cast<const fv<V>*>(&p);
 }
 
-template <int TZ>
+template <int TZ, int V>
 struct F2 {
-  static constexpr int W1 = kTX2 + 4 * kHalo;     // 144: level n-1 with an 8-cell halo
+  static constexpr int TX = 64 * V;
+  static constexpr int W1 = TX + 4 * kHalo;       // level n-1 with an 8-cell halo
   static constexpr int H1 = TZ + 4 * kHalo;
-  static constexpr int WE = kTX2 + 2 * kHalo;     // 136: first-step level on tile + 4
+  static constexpr int WE = TX + 2 * kHalo;       // first-step level on tile + 4
   static constexpr int HE = TZ + 2 * kHalo;
   static constexpr int NW = 8;                    // waves per workgroup
   static constexpr int NT = 64 * NW;
-  static constexpr int RA = HE / NW;              // first-step rows of a wave (128 body columns)
+  static constexpr int RA = HE / NW;              // first-step rows of a wave (body columns)
   static constexpr int RB = TZ / NW;              // second-step rows of a wave
   static_assert(HE % NW == 0 && TZ % NW == 0, "rows must split evenly over the waves");
-  // column pairs in the halo columns: NSE of the first step (4 + 4 columns of HE rows), NS1 of the
-  // staged level (8 + 8 columns of H1 rows); thread t takes pair t
-  static constexpr int NSE = HE * kHalo, NS1 = H1 * 2 * kHalo;
+  // groups of V columns in the halo columns: NSE of the first step (4 + 4 columns of HE rows), NS1 of
+  // the staged level (8 + 8 columns of H1 rows); thread t takes group t
+  static constexpr int NSE = HE * 2 * kHalo / V, NS1 = H1 * 4 * kHalo / V;
   static constexpr int MS1 = (NS1 + NT - 1) / NT;
-  static_assert(NSE <= NT, "one halo pair per thread");
+  static_assert(NSE <= NT, "one halo group per thread");
 };
 
-// Row and column of pair e of the halo columns of a region with HW halo columns per side.
-template <int HW>
-__device__ __forceinline__ void side_pair(int e, int* r, int* c) {
-  *r = e / HW;
-  const int k = 2 * (e - *r * HW);
-  *c = k < HW ? k : kTX2 + k;
+// Row and column of group e of the halo columns of a region with HW halo columns per side.
+template <int V, int HW>
+__device__ __forceinline__ void side_cols(int e, int* r, int* c) {
+  constexpr int N = 2 * HW / V;
+  *r = e / N;
+  const int k = V * (e - *r * N);
+  *c = k < HW ? k : 64 * V + k;
 }
 
-// Level n-1 with an 8-cell halo: rows z0-8 .. z0+TZ+7, whole rows per wave plus the halo pairs.
+// Level n-1 with an 8-cell halo: rows z0-8 .. z0+TZ+7, whole rows per wave plus the halo columns.
 // Issue before the other prefetches, commit to LDS (see Staged).
-template <int TZ>
+template <int TZ, int V>
 struct Tile8 {
-  using G = F2<TZ>;
+  using G = F2<TZ, V>;
   static constexpr int NB = G::H1 / G::NW;
   static_assert(G::H1 % G::NW == 0, "staged rows must split evenly over the waves");
-  f32x2 vb[NB], vh[G::MS1];
+  fv<V> vb[NB], vh[G::MS1];
 
   __device__ __forceinline__ void issue(const Planes& f, int cx, int x0, int z0, int nx, int nz, int px) {
     const int wv = wave_id();
 #pragma unroll
-    for (int i = 0; i < NB; ++i) vb[i] = ldp2(f, cx, z0 - 2 * kHalo + wv + i * G::NW);
+    for (int i = 0; i < NB; ++i) vb[i] = ldpv<V>(f, cx, z0 - 2 * kHalo + wv + i * G::NW);
 #pragma unroll
     for (int i = 0; i < G::MS1; ++i) {
       int r, c;
-      side_pair<2 * kHalo>(min((int)threadIdx.x + i * G::NT, G::NS1 - 1), &r, &c);
-      vh[i] = ldp2_at(f, col_off(x0 - 2 * kHalo + c, z0 - 2 * kHalo + r, nx, nz, px, 4));
+      side_cols<V, 2 * kHalo>(min((int)threadIdx.x + i * G::NT, G::NS1 - 1), &r, &c);
+      vh[i] = ldpv_at<V>(f, col_off(x0 - 2 * kHalo + c, z0 - 2 * kHalo + r, nx, nz, px, 4));
     }
   }
   __device__ __forceinline__ void commit(float (*L)[G::W1]) const {
     const int lane = threadIdx.x & 63, wv = wave_id();
 #pragma unroll
-    for (int i = 0; i < NB; ++i) *reinterpret_cast<f32x2*>(&L[wv + i * G::NW][2 * kHalo + 2 * lane]) = vb[i];
-    // unconditional: threads past the last pair write that pair again (see stage_commit)
+    for (int i = 0; i < NB; ++i) lds<V>(L[wv + i * G::NW][2 * kHalo + V * lane]) = vb[i];
+    // unconditional: threads past the last group write that group again (see stage_commit)
 #pragma unroll
     for (int i = 0; i < G::MS1; ++i) {
       int r, c;
-      side_pair<2 * kHalo>(min((int)threadIdx.x + i * G::NT, G::NS1 - 1), &r, &c);
-      *reinterpret_cast<f32x2*>(&L[r][c]) = vh[i];
+      side_cols<V, 2 * kHalo>(min((int)threadIdx.x + i * G::NT, G::NS1 - 1), &r, &c);
+      lds<V>(L[r][c]) = vh[i];
     }
   }
 };
 
-// Laplacians of the column pair at p (an LDS array of row stride W) in N consecutive rows, p at
+// Laplacians of the V columns at p (an LDS array of row stride W) in N consecutive rows, p at
 // the first; u receives the centre values.  The order of each sum is that of lap_ptr; along x a
-// difference is formed once for the two points it belongs to ((a - u) + (b - u) = (b - u) - (u - a)).
-template <int N, int W>
-__device__ __forceinline__ void lap_pairs(const float* p, f32x2 (&lap)[N], f32x2 (&u)[N], const float* c) {
-  f32x2 P[N + 2 * kHalo];
+// difference is formed once for the points it belongs to ((a - u) + (b - u) = (b - u) - (u - a)).
+template <int V, int N, int W>
+__device__ __forceinline__ void lap_rows(const float* p, fv<V> (&lap)[N], fv<V> (&u)[N], const float* c) {
+  fv<V> P[N + 2 * kHalo];
 #pragma unroll
-  for (int i = 0; i < N + 2 * kHalo; ++i) P[i] = *reinterpret_cast<const f32x2*>(p + (i - kHalo) * W);
+  for (int i = 0; i < N + 2 * kHalo; ++i) P[i] = lds<V>(p[(i - kHalo) * W]);
 #pragma unroll
   for (int n = 0; n < N; ++n) {
     __builtin_amdgcn_sched_barrier(0);   // one row after the other
     const float* q = p + n * W;
-    float X[2 * kHalo + 2];        // columns x-4 .. x+5
+    float X[2 * kHalo + V];        // columns x-4 .. x+V+3
 #pragma unroll
-    for (int k = 0; k < 2 * kHalo + 2; k += 2) {
-      const f32x2 v = k == kHalo ? P[n + kHalo] : *reinterpret_cast<const f32x2*>(q + k - kHalo);
-      X[k] = v.x;
-      X[k + 1] = v.y;
+    for (int k = 0; k < 2 * kHalo + V; k += V) {
+      const fv<V> v = k == kHalo ? P[n + kHalo] : lds<V>(q[k - kHalo]);
+#pragma unroll
+      for (int i = 0; i < V; ++i) X[k + i] = v[i];
     }
     u[n] = P[n + kHalo];
-    float s0 = 0.f, s1 = 0.f;
+    float s[V] = {};
 #pragma unroll
     for (int r = kHalo; r >= 1; --r) {
-      float D[2 * kHalo + 2];      // D[k] = X[k + r] - X[k] at k = 4, 5 and r to their left
+      float D[2 * kHalo + V];      // D[k] = X[k + r] - X[k] at the columns and r to their left
 #pragma unroll
-      for (int k = kHalo - r; k < kHalo + 2; ++k) D[k] = X[k + r] - X[k];
-      s0 += c[r] * (D[kHalo] - D[kHalo - r]);
-      s0 += c[r] * ((P[n + kHalo - r].x - P[n + kHalo].x) + (P[n + kHalo + r].x - P[n + kHalo].x));
-      s1 += c[r] * (D[kHalo + 1] - D[kHalo + 1 - r]);
-      s1 += c[r] * ((P[n + kHalo - r].y - P[n + kHalo].y) + (P[n + kHalo + r].y - P[n + kHalo].y));
+      for (int k = kHalo - r; k < kHalo + V; ++k) D[k] = X[k + r] - X[k];
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        s[i] += c[r] * (D[kHalo + i] - D[kHalo + i - r]);
+        s[i] += c[r] * ((P[n + kHalo - r][i] - P[n + kHalo][i]) + (P[n + kHalo + r][i] - P[n + kHalo][i]));
+      }
     }
-    lap[n] = f32x2{s0, s1};
+#pragma unroll
+    for (int i = 0; i < V; ++i) lap[n][i] = s[i];
   }
 }
 
-// eta / dt of a column pair (dx2: the columns' squared border distances) at row z.
+// Squared border distances of a lane's columns.
+template <int V>
 struct Damp {
-  float x0, x1;
+  float d2[V];
   __device__ __forceinline__ Damp(int x, int nx, int nbl) {
-    x0 = (float)border_dist(x, nx, nbl);
-    x1 = (float)border_dist(x + 1, nx, nbl);
-    x0 *= x0;
-    x1 *= x1;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const float d = (float)border_dist(x + i, nx, nbl);
+      d2[i] = d * d;
+    }
   }
 };
 
-// One update of a column pair: (increment, new level).  The sum of the squared distances is the
-// integers' sum bit for bit (both far below 2^24).
-__device__ __forceinline__ void step_pair(f32x2 u, f32x2 um2, f32x2 cf, f32x2 lap, const Damp& d, int dz, float eta_dt,
-                                          f32x2* incr, f32x2* un) {
+// One update of V columns at border distance dz: (increment, new level).  The sum of the squared distances
+// is the integers' sum bit for bit (both far below 2^24).
+template <int V>
+__device__ __forceinline__ void step_cols(fv<V> u, fv<V> um2, fv<V> cf, fv<V> lap, const Damp<V>& d, int dz,
+                                          float eta_dt, fv<V>* incr, fv<V>* un) {
   const float fz = (float)dz * (float)dz;
-  incr->x = step_incr(u.x, um2.x, cf.x, lap.x, eta_dt * (d.x0 + fz));
-  incr->y = step_incr(u.y, um2.y, cf.y, lap.y, eta_dt * (d.x1 + fz));
-  un->x = (u.x + u.x - um2.x) + incr->x;
-  un->y = (u.y + u.y - um2.y) + incr->y;
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    const float inc = step_incr(u[i], um2[i], cf[i], lap[i], eta_dt * (d.d2[i] + fz));
+    (*incr)[i] = inc;
+    (*un)[i] = (u[i] + u[i] - um2[i]) + inc;
+  }
 }
 
-// Source term of a column pair at (x, z).
+// Source term of the columns x, x + 1, ... at row z.
 struct Source {
   int i, k;
   float w0, w1, w2, w3;
   __device__ __forceinline__ explicit Source(const ShotDev& S)
       : i(S.src_i), k(S.src_k), w0(S.src_w[0]), w1(S.src_w[1]), w2(S.src_w[2]), w3(S.src_w[3]) {}
-  __device__ __forceinline__ void add(f32x2* lap, int x, int z, float q) const {
+  template <int V>
+  __device__ __forceinline__ void add(fv<V>* lap, int x, int z, float q) const {
     if ((unsigned)(z - k) < 2u) {
       const float a = z == k ? w0 : w2, b = z == k ? w1 : w3;
-      if (x == i) {
-        lap->x = add_source(lap->x, a, q);
-        lap->y = add_source(lap->y, b, q);
-      } else if (x == i - 1) {
-        lap->y = add_source(lap->y, a, q);
-      } else if (x == i + 1) {
-        lap->x = add_source(lap->x, b, q);
+      const int b0 = x - i;
+      if ((unsigned)(b0 + V - 1) < (unsigned)(V + 1)) {
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+          if ((unsigned)(b0 + c) < 2u) (*lap)[c] = add_source((*lap)[c], b0 + c == 0 ? a : b, q);
       }
     }
   }
 };
 
-// probe_add for a column pair: the pair's sums j are adjacent (16 bytes; x is even, and a pair's
-// second column may lie in the row's padding, whose terms are zero).
-__device__ __forceinline__ void probe_add2(double* sum, int r, const float* c1, f32x2 v1, bool t1, const float* c2,
-                                           f32x2 v2, bool t2, long long pitch) {
-  constexpr int kGroup = 4;   // sums in flight: as many bytes as probe_add's
+// probe_add for V columns: sum j of adjacent points is adjacent (x is a multiple of V, and a second
+// column may lie in the row's padding, whose terms are zero).
+template <int V>
+__device__ __forceinline__ void probe_cols(double* sum, int r, const float* c1, fv<V> v1, bool t1, const float* c2,
+                                           fv<V> v2, bool t2, long long pitch) {
+  constexpr int kGroup = kProbeGroup / V;   // as many bytes in flight as probe_add
   for (int j0 = 0; j0 < r; j0 += kGroup) {
-    f64x2 t[kGroup];
+    dv<V> t[kGroup];
     const int n = min(r - j0, kGroup);
-    f64x2* s = reinterpret_cast<f64x2*>(sum + j0 * 64);
+    dv<V>* s = reinterpret_cast<dv<V>*>(sum + j0 * 64);
 #pragma unroll
     for (int u = 0; u < kGroup; ++u)
-      if (u < n) t[u] = __builtin_nontemporal_load(s + u * 32);
+      if (u < n) t[u] = __builtin_nontemporal_load(s + u * (64 / V));
 #pragma unroll
     for (int u = 0; u < kGroup; ++u)
       if (u < n) {
         if (t1) {
           const double c = c1[(j0 + u) * pitch];
-          t[u].x += c * (double)v1.x;
-          t[u].y += c * (double)v1.y;
+#pragma unroll
+          for (int i = 0; i < V; ++i) t[u][i] += c * (double)v1[i];
         }
         if (t2) {
           const double c = c2[(j0 + u) * pitch];
-          t[u].x += c * (double)v2.x;
-          t[u].y += c * (double)v2.y;
+#pragma unroll
+          for (int i = 0; i < V; ++i) t[u][i] += c * (double)v2[i];
         }
       }
 #pragma unroll
     for (int u = 0; u < kGroup; ++u)
-      if (u < n) __builtin_nontemporal_store(t[u], s + u * 32);
+      if (u < n) __builtin_nontemporal_store(t[u], s + u * (64 / V));
   }
 }
 
@@ -716,14 +757,14 @@ __device__ __forceinline__ void gather(const StepArgs& a, const TileDev& T, cons
 // Forward: levels k and k+1 (k = step - off); SK = kStoreNone, kStoreF32 or kStoreProbe (both
 // levels' increments added to the probe sums in one FP64 read-modify-write, level k first).
 // a.single: level k alone.
-template <int TZ, int SK>
-__global__ __launch_bounds__(F2<TZ>::NT) void fwd2d2_kernel(StepArgs a) {
-  using G = F2<TZ>;
+template <int TZ, int V, int SK>
+__global__ __launch_bounds__((F2<TZ, V>::NT)) void fwd2d2_kernel(StepArgs a) {
+  using G = F2<TZ, V>;
   constexpr bool PRB = SK == kStoreProbe;
   constexpr int RA = G::RA, RB = G::RB;
   __shared__ __align__(16) float L1[G::H1][G::W1];
   __shared__ __align__(16) float LE[G::HE][G::WE];
-  __shared__ __align__(16) float INC1[PRB ? TZ : 1][kTX2];  // probe: level k's increment on the tile
+  __shared__ __align__(16) float INC1[PRB ? TZ : 1][G::TX];  // probe: level k's increment on the tile
   const int tid = xcd_tile(blockIdx.x, a.ntiles);
   const TileDev T = a.t.tiles[a.tile_base + tid];
   const ShotDev& S = a.t.shots[T.shot];
@@ -749,28 +790,28 @@ __global__ __launch_bounds__(F2<TZ>::NT) void fwd2d2_kernel(StepArgs a) {
   const brsrc rs2 = make_rsrc(st + (long long)(SK == kStoreF32 && act2 ? k + 1 : 0) * npts,
                               SK == kStoreF32 && act2 ? nz * row4 : 0);
   const int lane = threadIdx.x & 63, wv = wave_id();
-  const int x = T.x0 + 2 * lane;
+  const int x = T.x0 + V * lane;
   const int cx = x < nx ? 4 * x : kOOB;
   const int zE = T.z0 - kHalo;           // row 0 of the first-step region
 
   // the level k-1 tile first, then level k-2 and coef of this thread's first-step points and coef
   // of its tile points
-  Tile8<TZ> tile;
+  Tile8<TZ, V> tile;
   tile.issue(u1, cx, T.x0, T.z0, nx, nz, px);
-  f32x2 pm2[RA], pcf[RA], tcf[RB];
+  fv<V> pm2[RA], pcf[RA], tcf[RB];
 #pragma unroll
   for (int i = 0; i < RA; ++i) {
-    pm2[i] = ldp2(u2, cx, zE + wv * RA + i);
-    pcf[i] = ldp2(cf, cx, zE + wv * RA + i);
+    pm2[i] = ldpv<V>(u2, cx, zE + wv * RA + i);
+    pcf[i] = ldpv<V>(cf, cx, zE + wv * RA + i);
   }
   const bool side = (int)threadIdx.x < G::NSE;
   int sr, sc;
-  side_pair<kHalo>(min((int)threadIdx.x, G::NSE - 1), &sr, &sc);
+  side_cols<V, kHalo>(min((int)threadIdx.x, G::NSE - 1), &sr, &sc);
   const int sx = T.x0 - kHalo + sc, sz = zE + sr;
   const int so = side ? col_off(sx, sz, nx, nz, px, 4) : kOOB;
-  const f32x2 sm2 = ldp2_at(u2, so), scf = ldp2_at(cf, so);
+  const fv<V> sm2 = ldpv_at<V>(u2, so), scf = ldpv_at<V>(cf, so);
 #pragma unroll
-  for (int i = 0; i < RB; ++i) tcf[i] = ldp2(cf, cx, T.z0 + wv * RB + i);
+  for (int i = 0; i < RB; ++i) tcf[i] = ldpv<V>(cf, cx, T.z0 + wv * RB + i);
   tile.commit(L1);
   __syncthreads();
 
@@ -778,32 +819,32 @@ __global__ __launch_bounds__(F2<TZ>::NT) void fwd2d2_kernel(StepArgs a) {
   // shot fields used after stores, in registers (see fwd2d_kernel)
   const Source src(S);
   const float q1 = act1 ? a.q[S.q + k - 1] : 0.f, q2 = act2 ? a.q[S.q + k] : 0.f;
-  const Damp damp(x, nx, a.nbl);
+  const Damp<V> damp(x, nx, a.nbl);
   // first step: level k on the tile + 4-cell halo (zero outside the grid, where u, u^{k-2} and coef
   // read 0)
   {
-    f32x2 lap[RA], u[RA];
-    lap_pairs<RA, G::W1>(&L1[wv * RA + kHalo][2 * kHalo + 2 * lane], lap, u, a.c);
+    fv<V> lap[RA], u[RA];
+    lap_rows<V, RA, G::W1>(&L1[wv * RA + kHalo][2 * kHalo + V * lane], lap, u, a.c);
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
       const int r = wv * RA + i, z = zE + r;
-      if (act1) src.add(&lap[i], x, z, q1);
-      f32x2 incr, v;
-      step_pair(u[i], pm2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &v);
+      if (act1) src.add<V>(&lap[i], x, z, q1);
+      fv<V> incr, v;
+      step_cols<V>(u[i], pm2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &v);
       // rows of the tile store level k (the others' stores drop)
       const int zo = (unsigned)(r - kHalo) < (unsigned)TZ && z < nz ? z * row4 : kZOOB;
-      stb2(ro1, v, cx, zo);
-      if (SK == kStoreF32) stb2_nt(rs1, v, cx, zo);
-      if (PRB && (unsigned)(r - kHalo) < (unsigned)TZ) *reinterpret_cast<f32x2*>(&INC1[r - kHalo][2 * lane]) = incr;
-      *reinterpret_cast<f32x2*>(&LE[r][kHalo + 2 * lane]) = v;
+      stv<V>(ro1, v, cx, zo);
+      if (SK == kStoreF32) stv<V, kNT>(rs1, v, cx, zo);
+      if (PRB && (unsigned)(r - kHalo) < (unsigned)TZ) lds<V>(INC1[r - kHalo][V * lane]) = incr;
+      lds<V>(LE[r][kHalo + V * lane]) = v;
     }
   }
   if (side) {
-    f32x2 lap[1], u[1], incr, v;
-    lap_pairs<1, G::W1>(&L1[sr + kHalo][sc + kHalo], lap, u, a.c);
-    if (act1) src.add(&lap[0], sx, sz, q1);
-    step_pair(u[0], sm2, scf, lap[0], Damp(sx, nx, a.nbl), border_dist(sz, nz, a.nbl), a.eta_dt, &incr, &v);
-    *reinterpret_cast<f32x2*>(&LE[sr][sc]) = v;
+    fv<V> lap[1], u[1], incr, v;
+    lap_rows<V, 1, G::W1>(&L1[sr + kHalo][sc + kHalo], lap, u, a.c);
+    if (act1) src.add<V>(&lap[0], sx, sz, q1);
+    step_cols<V>(u[0], sm2, scf, lap[0], Damp<V>(sx, nx, a.nbl), border_dist(sz, nz, a.nbl), a.eta_dt, &incr, &v);
+    lds<V>(LE[sr][sc]) = v;
   }
   __syncthreads();
 
@@ -814,23 +855,23 @@ __global__ __launch_bounds__(F2<TZ>::NT) void fwd2d2_kernel(StepArgs a) {
   double* pb = PRB ? reinterpret_cast<double*>(a.ws + S.store) : nullptr;
   const float* pc1 = PRB ? a.probe_c + k : nullptr;
   const float* pc2 = PRB ? a.probe_c + k + 1 : nullptr;
-  f32x2 lap[RB], u[RB];
-  lap_pairs<RB, G::WE>(&LE[wv * RB + kHalo][kHalo + 2 * lane], lap, u, a.c);
+  fv<V> lap[RB], u[RB];
+  lap_rows<V, RB, G::WE>(&LE[wv * RB + kHalo][kHalo + V * lane], lap, u, a.c);
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     const int lr = wv * RB + i, z = T.z0 + lr;
-    const f32x2 um2 = *reinterpret_cast<const f32x2*>(&L1[lr + 2 * kHalo][2 * kHalo + 2 * lane]);
-    src.add(&lap[i], x, z, q2);
-    f32x2 incr, un;
-    step_pair(u[i], um2, tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &un);
+    const fv<V> um2 = lds<V>(L1[lr + 2 * kHalo][2 * kHalo + V * lane]);
+    src.add<V>(&lap[i], x, z, q2);
+    fv<V> incr, un;
+    step_cols<V>(u[i], um2, tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &un);
     const int zo = z * row4;
-    stb2(ro2, un, cx, zo);
-    if (SK == kStoreF32) stb2_nt(rs2, un, cx, zo);
+    stv<V>(ro2, un, cx, zo);
+    if (SK == kStoreF32) stv<V, kNT>(rs2, un, cx, zo);
     if (PRB && z < nz) {
       // the same two FP64 additions, in the same order, as two one-level launches
-      const f32x2 i1 = *reinterpret_cast<const f32x2*>(&INC1[lr][2 * lane]);
+      const fv<V> i1 = lds<V>(INC1[lr][V * lane]);
       if (x < nx)
-        probe_add2(probe_sums(pb, (long long)z * px + x, a.probe_r), a.probe_r, pc1, i1, act1, pc2, incr, act2,
+        probe_cols<V>(probe_sums(pb, (long long)z * px + x, a.probe_r), a.probe_r, pc1, i1, act1, pc2, incr, act2,
                    a.probe_pitch);
     }
   }
@@ -860,9 +901,9 @@ __device__ __forceinline__ void inject(const StepArgs& a, const InjPoint* pts, i
 // The injected residual takes no LDS of its own: the first step's lies where the point's new level
 // goes (LE), which its own thread reads before it writes; the second step's in L1, of which the
 // second step needs only its own points' values, held in registers by then.
-template <int TZ, int IMG>
-__global__ __launch_bounds__(F2<TZ>::NT) void adj2d2_kernel(StepArgs a) {
-  using G = F2<TZ>;
+template <int TZ, int V, int IMG>
+__global__ __launch_bounds__((F2<TZ, V>::NT)) void adj2d2_kernel(StepArgs a) {
+  using G = F2<TZ, V>;
   constexpr int RA = G::RA, RB = G::RB;
   // kImgBuffers: the two levels come from the recomputed forward buffers (or the slot restored
   // by reference) instead of the FULL store, as in a checkpointed gradient's paired reversals
@@ -871,7 +912,7 @@ __global__ __launch_bounds__(F2<TZ>::NT) void adj2d2_kernel(StepArgs a) {
   constexpr bool PRB = IMG == kImgProbe;
   __shared__ __align__(16) float L1[G::H1][G::W1];
   __shared__ __align__(16) float LE[G::HE][G::WE];
-  __shared__ __align__(16) float INC1[IACC ? TZ : 1][kTX2];
+  __shared__ __align__(16) float INC1[IACC ? TZ : 1][G::TX];
   const int tid = xcd_tile(blockIdx.x, a.ntiles);
   const TileDev T = a.t.tiles[a.tile_base + tid];
   const ShotDev& S = a.t.shots[T.shot];
@@ -896,41 +937,52 @@ __global__ __launch_bounds__(F2<TZ>::NT) void adj2d2_kernel(StepArgs a) {
   const Planes acc = planes(a.ws + S.acc, nz, IACC ? nz : 0, 2 * row4);
   const brsrc racc = make_rsrc(a.ws + S.acc, IACC ? 2 * nz * row4 : 0);
   const int lane = threadIdx.x & 63, wv = wave_id();
-  const int x = T.x0 + 2 * lane;
+  const int x = T.x0 + V * lane;
   const int cx = x < nx ? 4 * x : kOOB;
   const int cx8 = x < nx ? 8 * x : kOOB;
   const int zE = T.z0 - kHalo;
   const bool inj1 = act1 && a.dd != nullptr && T.ext_count > 0;
   const bool inj2 = act2 && a.dd != nullptr && T.inj_count > 0;
 
-  Tile8<TZ> tile;
+  // Imaging inputs: issued with the first step's, or - where the registers they would hold through it
+  // cost a workgroup per CU (100 instead of 79 at 24 rows of column pairs) - after it, behind the second
+  // step's arithmetic: 16 shots of 1104 x 592 84.9 -> 77.5 us per launch, of 730 x 421 40.1 -> 38.0;
+  // narrow or low tiles lose up to 7 % by it.
+  constexpr bool LATE = TZ >= (V == 2 ? 16 : 32);
+  fv<V> pu1[RB], pu2[RB];
+  dv<V> pacc[RB];
+  auto load_img = [&]() {
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      const int z = T.z0 + wv * RB + i;
+      pu1[i] = ldpv<V, kNT>(us1, cx, z);
+      pu2[i] = ldpv<V, kNT>(us2, cx, z);
+      pacc[i] = ldpacc<V>(acc, cx8, z);
+    }
+  };
+  Tile8<TZ, V> tile;
   tile.issue(w1, cx, T.x0, T.z0, nx, nz, px);
-  f32x2 pm2[RA], pcf[RA], tcf[RB], pu1[RB], pu2[RB];
-  f64x2 pacc[RB];
+  fv<V> pm2[RA], pcf[RA], tcf[RB];
 #pragma unroll
   for (int i = 0; i < RA; ++i) {
     const int r = wv * RA + i;
-    pm2[i] = ldp2(w2, cx, zE + r);
-    pcf[i] = ldp2(cf, cx, zE + r);
-    if (inj1) *reinterpret_cast<f32x2*>(&LE[r][kHalo + 2 * lane]) = f32x2{0.f, 0.f};
+    pm2[i] = ldpv<V>(w2, cx, zE + r);
+    pcf[i] = ldpv<V>(cf, cx, zE + r);
+    if (inj1) lds<V>(LE[r][kHalo + V * lane]) = fv<V>{};
   }
   const bool side = (int)threadIdx.x < G::NSE;
   int sr, sc;
-  side_pair<kHalo>(min((int)threadIdx.x, G::NSE - 1), &sr, &sc);
+  side_cols<V, kHalo>(min((int)threadIdx.x, G::NSE - 1), &sr, &sc);
   const int sx = T.x0 - kHalo + sc, sz = zE + sr;
   const int so = side ? col_off(sx, sz, nx, nz, px, 4) : kOOB;
-  const f32x2 sm2 = ldp2_at(w2, so), scf = ldp2_at(cf, so);
-  if (inj1 && side) *reinterpret_cast<f32x2*>(&LE[sr][sc]) = f32x2{0.f, 0.f};
+  const fv<V> sm2 = ldpv_at<V>(w2, so), scf = ldpv_at<V>(cf, so);
+  if (inj1 && side) lds<V>(LE[sr][sc]) = fv<V>{};
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     const int z = T.z0 + wv * RB + i;
-    tcf[i] = ldp2(cf, cx, z);
-    if (IACC) {
-      pu1[i] = ldp2_nt(us1, cx, z);
-      pu2[i] = ldp2_nt(us2, cx, z);
-      pacc[i] = ldp64x2(acc, cx8, z);
-    }
+    tcf[i] = ldpv<V>(cf, cx, z);
   }
+  if (IACC && !LATE) load_img();
   tile.commit(L1);
   __syncthreads();
 
@@ -941,49 +993,51 @@ __global__ __launch_bounds__(F2<TZ>::NT) void adj2d2_kernel(StepArgs a) {
   const bool src_here = a.v != nullptr && a.tile_base + tid == S.src_tile && threadIdx.x == 0;
   if (act1 && src_here)
     a.v[S.q + j] = interp_at<G::W1>(L1, S.src_k - T.z0 + 2 * kHalo, S.src_i - T.x0 + 2 * kHalo, S.src_w);
-  const Damp damp(x, nx, a.nbl);
+  const Damp<V> damp(x, nx, a.nbl);
   // first step: level j on the tile + 4-cell halo
   {
-    f32x2 lap[RA], u[RA];
-    lap_pairs<RA, G::W1>(&L1[wv * RA + kHalo][2 * kHalo + 2 * lane], lap, u, a.c);
+    fv<V> lap[RA], u[RA];
+    lap_rows<V, RA, G::W1>(&L1[wv * RA + kHalo][2 * kHalo + V * lane], lap, u, a.c);
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
       const int r = wv * RA + i, z = zE + r;
-      f32x2* le = reinterpret_cast<f32x2*>(&LE[r][kHalo + 2 * lane]);
+      fv<V>* le = &lds<V>(LE[r][kHalo + V * lane]);
       if (inj1) {
-        const f32x2 s = *le;
-        lap[i].x += s.x;
-        lap[i].y += s.y;
+        const fv<V> s = *le;
+        lap[i] += s;
       }
-      f32x2 incr, v;
-      step_pair(u[i], pm2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &v);
+      fv<V> incr, v;
+      step_cols<V>(u[i], pm2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &v);
       const bool on = (unsigned)(r - kHalo) < (unsigned)TZ;
-      stb2(ro1, v, cx, on && z < nz ? z * row4 : kZOOB);
-      if (IACC && on) *reinterpret_cast<f32x2*>(&INC1[r - kHalo][2 * lane]) = incr;
+      stv<V>(ro1, v, cx, on && z < nz ? z * row4 : kZOOB);
+      if (IACC && on) lds<V>(INC1[r - kHalo][V * lane]) = incr;
       *le = v;
     }
   }
   if (side) {
-    f32x2 lap[1], u[1], incr, v;
-    lap_pairs<1, G::W1>(&L1[sr + kHalo][sc + kHalo], lap, u, a.c);
-    f32x2* le = reinterpret_cast<f32x2*>(&LE[sr][sc]);
+    fv<V> lap[1], u[1], incr, v;
+    lap_rows<V, 1, G::W1>(&L1[sr + kHalo][sc + kHalo], lap, u, a.c);
+    fv<V>* le = &lds<V>(LE[sr][sc]);
     if (inj1) {
-      const f32x2 s = *le;
-      lap[0].x += s.x;
-      lap[0].y += s.y;
+      const fv<V> s = *le;
+      lap[0] += s;
     }
-    step_pair(u[0], sm2, scf, lap[0], Damp(sx, nx, a.nbl), border_dist(sz, nz, a.nbl), a.eta_dt, &incr, &v);
+    step_cols<V>(u[0], sm2, scf, lap[0], Damp<V>(sx, nx, a.nbl), border_dist(sz, nz, a.nbl), a.eta_dt, &incr, &v);
     *le = v;
   }
-  f32x2 um2[RB];
+  if (IACC && LATE) {
+    __builtin_amdgcn_sched_barrier(0);
+    load_img();
+  }
+  fv<V> um2[RB];
 #pragma unroll
   for (int i = 0; i < RB; ++i)
-    um2[i] = *reinterpret_cast<const f32x2*>(&L1[wv * RB + i + 2 * kHalo][2 * kHalo + 2 * lane]);
+    um2[i] = lds<V>(L1[wv * RB + i + 2 * kHalo][2 * kHalo + V * lane]);
   __syncthreads();
 
   if (inj2) {   // the tile's rows of L1 (cell (0, 0) = tile point (0, 0)) now take the second residual
 #pragma unroll
-    for (int i = 0; i < RB; ++i) *reinterpret_cast<f32x2*>(&L1[wv * RB + i][2 * lane]) = f32x2{0.f, 0.f};
+    for (int i = 0; i < RB; ++i) lds<V>(L1[wv * RB + i][V * lane]) = fv<V>{};
     __syncthreads();
     inject<G::NT, G::W1>(a, a.t.inj_pts, T.inj_begin, T.inj_count, a.dd + S.d + (long long)(j - 1) * S.nrec, L1);
     __syncthreads();
@@ -995,33 +1049,32 @@ __global__ __launch_bounds__(F2<TZ>::NT) void adj2d2_kernel(StepArgs a) {
   const float* pc1 = PRB ? a.probe_c + j : nullptr;
   const float* pc2 = PRB ? a.probe_c + j - 1 : nullptr;
   if (!act2 && !IACC && !PRB) return;
-  f32x2 lap[RB], u[RB];
-  lap_pairs<RB, G::WE>(&LE[wv * RB + kHalo][kHalo + 2 * lane], lap, u, a.c);
+  fv<V> lap[RB], u[RB];
+  lap_rows<V, RB, G::WE>(&LE[wv * RB + kHalo][kHalo + V * lane], lap, u, a.c);
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     const int lr = wv * RB + i, z = T.z0 + lr;
     if (inj2) {
-      const f32x2 s = *reinterpret_cast<const f32x2*>(&L1[lr][2 * lane]);
-      lap[i].x += s.x;
-      lap[i].y += s.y;
+      const fv<V> s = lds<V>(L1[lr][V * lane]);
+      lap[i] += s;
     }
-    f32x2 incr, wn;
-    step_pair(u[i], um2[i], tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &wn);
-    stb2(ro2, wn, cx, z * row4);
+    fv<V> incr, wn;
+    step_cols<V>(u[i], um2[i], tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &wn);
+    stv<V>(ro2, wn, cx, z * row4);
     if (IACC) {
-      const f32x2 i1 = *reinterpret_cast<const f32x2*>(&INC1[lr][2 * lane]);
-      f64x2 ac = pacc[i];
+      const fv<V> i1 = lds<V>(INC1[lr][V * lane]);
+      dv<V> ac = pacc[i];
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
+      for (int c = 0; c < V; ++c) {
         if (act1) ac[c] = ac[c] + (double)pu1[i][c] * (double)i1[c];
         if (act2) ac[c] = ac[c] + (double)pu2[i][c] * (double)incr[c];
       }
-      stb64x2(racc, ac, cx8, 2 * z * row4);
+      stacc<V>(racc, ac, cx8, 2 * z * row4);
     }
     if (PRB && z < nz) {
       // the same two FP64 additions, in the same order, as two one-level launches
       if (x < nx)
-        probe_add2(probe_sums(pa, (long long)z * px + x, a.probe_r), a.probe_r, pc1, u[i], act1, pc2, wn, act2,
+        probe_cols<V>(probe_sums(pa, (long long)z * px + x, a.probe_r), a.probe_r, pc1, u[i], act1, pc2, wn, act2,
                    a.probe_pitch);
     }
   }
@@ -1032,9 +1085,9 @@ __global__ __launch_bounds__(F2<TZ>::NT) void adj2d2_kernel(StepArgs a) {
 // one-level launches); samples (J dm)^{k-1} and (J dm)^k.  Per two levels the launch reads
 // u^{k-1}, u^{k-2}, du^{k-1}, du^{k-2}, coef and dm once and writes four levels: 40 B per point
 // instead of 2 x 32.  a.single: level k alone.
-template <int TZ>
-__global__ __launch_bounds__(F2<TZ>::NT) void born2d2_kernel(StepArgs a) {
-  using G = F2<TZ>;
+template <int TZ, int V>
+__global__ __launch_bounds__((F2<TZ, V>::NT)) void born2d2_kernel(StepArgs a) {
+  using G = F2<TZ, V>;
   constexpr int RA = G::RA, RB = G::RB;
   __shared__ __align__(16) float L1U[G::H1][G::W1];
   __shared__ __align__(16) float L1D[G::H1][G::W1];
@@ -1062,38 +1115,40 @@ __global__ __launch_bounds__(F2<TZ>::NT) void born2d2_kernel(StepArgs a) {
   const brsrc do1 = make_rsrc(fbuf(a.ws, S, adj_buf(k)), act1 ? nz * row4 : 0);
   const brsrc do2 = make_rsrc(fbuf(a.ws, S, adj_buf(k + 1)), act2 ? nz * row4 : 0);
   const int lane = threadIdx.x & 63, wv = wave_id();
-  const int x = T.x0 + 2 * lane;
+  const int x = T.x0 + V * lane;
   const int cx = x < nx ? 4 * x : kOOB;
-  const int cx1 = x + 1 < nx ? 4 * x + 4 : kOOB;   // dm: rows of nx, one column at a time
   const int zE = T.z0 - kHalo;
 
   // the two level k-1 tiles first, then the first step's other inputs on its points and coef and
   // dm of the tile points
-  Tile8<TZ> tu, td;
+  Tile8<TZ, V> tu, td;
   tu.issue(u1, cx, T.x0, T.z0, nx, nz, px);
   td.issue(d1, cx, T.x0, T.z0, nx, nz, px);
-  f32x2 pu2[RA], pd2[RA], pcf[RA], pdm[RA], tcf[RB], tdm[RB];
+  fv<V> pu2[RA], pd2[RA], pcf[RA], pdm[RA], tcf[RB], tdm[RB];
 #pragma unroll
   for (int i = 0; i < RA; ++i) {
     const int z = zE + wv * RA + i;
-    pu2[i] = ldp2(u2, cx, z);
-    pd2[i] = ldp2(d2, cx, z);
-    pcf[i] = ldp2(cf, cx, z);
-    pdm[i] = f32x2{ldp(dmp, cx, z), ldp(dmp, cx1, z)};
+    pu2[i] = ldpv<V>(u2, cx, z);
+    pd2[i] = ldpv<V>(d2, cx, z);
+    pcf[i] = ldpv<V>(cf, cx, z);
+    #pragma unroll
+    for (int c = 0; c < V; ++c) pdm[i][c] = ldp(dmp, x + c < nx ? 4 * (x + c) : kOOB, z);   // rows of nx
   }
   const bool side = (int)threadIdx.x < G::NSE;
   int sr, sc;
-  side_pair<kHalo>(min((int)threadIdx.x, G::NSE - 1), &sr, &sc);
+  side_cols<V, kHalo>(min((int)threadIdx.x, G::NSE - 1), &sr, &sc);
   const int sx = T.x0 - kHalo + sc, sz = zE + sr;
   const int so = side ? col_off(sx, sz, nx, nz, px, 4) : kOOB;
-  const f32x2 su2 = ldp2_at(u2, so), sd2 = ldp2_at(d2, so), scf = ldp2_at(cf, so);
-  const f32x2 sdm = {ldp_at(dmp, side ? col_off(sx, sz, nx, nz, nx, 4) : kOOB),
-                     ldp_at(dmp, side ? col_off(sx + 1, sz, nx, nz, nx, 4) : kOOB)};
+  const fv<V> su2 = ldpv_at<V>(u2, so), sd2 = ldpv_at<V>(d2, so), scf = ldpv_at<V>(cf, so);
+  fv<V> sdm;
+#pragma unroll
+  for (int c = 0; c < V; ++c) sdm[c] = ldp_at(dmp, side ? col_off(sx + c, sz, nx, nz, nx, 4) : kOOB);
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     const int z = T.z0 + wv * RB + i;
-    tcf[i] = ldp2(cf, cx, z);
-    tdm[i] = f32x2{ldp(dmp, cx, z), ldp(dmp, cx1, z)};
+    tcf[i] = ldpv<V>(cf, cx, z);
+    #pragma unroll
+    for (int c = 0; c < V; ++c) tdm[i][c] = ldp(dmp, x + c < nx ? 4 * (x + c) : kOOB, z);
   }
   tu.commit(L1U);
   td.commit(L1D);
@@ -1102,74 +1157,74 @@ __global__ __launch_bounds__(F2<TZ>::NT) void born2d2_kernel(StepArgs a) {
   if (act1 && a.d != nullptr) gather<G::NT, G::W1>(a, T, S, L1D, T.z0 - 2 * kHalo, T.x0 - 2 * kHalo, k - 1);
   const Source src(S);   // in registers (see the forward kernel)
   const float q1 = act1 ? a.q[S.q + k - 1] : 0.f, q2 = act2 ? a.q[S.q + k] : 0.f;
-  const Damp damp(x, nx, a.nbl);
+  const Damp<V> damp(x, nx, a.nbl);
   // scattered field's source: -dm (u^k - 2u^{k-1} + u^{k-2}) / dt^2 = -dm incr / dt^2
-  auto scatter = [&](f32x2* lapd, f32x2 dm, f32x2 incr) {
-    lapd->x = lapd->x - dm.x * incr.x * a.inv_dt2;
-    lapd->y = lapd->y - dm.y * incr.y * a.inv_dt2;
+  auto scatter = [&](fv<V>* lapd, fv<V> dm, fv<V> incr) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) (*lapd)[i] = (*lapd)[i] - dm[i] * incr[i] * a.inv_dt2;
   };
   // first step: levels k of u and du on the tile + 4-cell halo
   {
-    f32x2 lap[RA], u[RA], inc[RA];
-    lap_pairs<RA, G::W1>(&L1U[wv * RA + kHalo][2 * kHalo + 2 * lane], lap, u, a.c);
+    fv<V> lap[RA], u[RA], inc[RA];
+    lap_rows<V, RA, G::W1>(&L1U[wv * RA + kHalo][2 * kHalo + V * lane], lap, u, a.c);
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
       const int r = wv * RA + i, z = zE + r;
-      if (act1) src.add(&lap[i], x, z, q1);
-      f32x2 v;
-      step_pair(u[i], pu2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &inc[i], &v);
-      stb2(uo1, v, cx, (unsigned)(r - kHalo) < (unsigned)TZ && z < nz ? z * row4 : kZOOB);
-      *reinterpret_cast<f32x2*>(&LEU[r][kHalo + 2 * lane]) = v;
+      if (act1) src.add<V>(&lap[i], x, z, q1);
+      fv<V> v;
+      step_cols<V>(u[i], pu2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &inc[i], &v);
+      stv<V>(uo1, v, cx, (unsigned)(r - kHalo) < (unsigned)TZ && z < nz ? z * row4 : kZOOB);
+      lds<V>(LEU[r][kHalo + V * lane]) = v;
     }
-    lap_pairs<RA, G::W1>(&L1D[wv * RA + kHalo][2 * kHalo + 2 * lane], lap, u, a.c);
+    lap_rows<V, RA, G::W1>(&L1D[wv * RA + kHalo][2 * kHalo + V * lane], lap, u, a.c);
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
       const int r = wv * RA + i, z = zE + r;
       scatter(&lap[i], pdm[i], inc[i]);
-      f32x2 incd, v;
-      step_pair(u[i], pd2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incd, &v);
-      stb2(do1, v, cx, (unsigned)(r - kHalo) < (unsigned)TZ && z < nz ? z * row4 : kZOOB);
-      *reinterpret_cast<f32x2*>(&LED[r][kHalo + 2 * lane]) = v;
+      fv<V> incd, v;
+      step_cols<V>(u[i], pd2[i], pcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incd, &v);
+      stv<V>(do1, v, cx, (unsigned)(r - kHalo) < (unsigned)TZ && z < nz ? z * row4 : kZOOB);
+      lds<V>(LED[r][kHalo + V * lane]) = v;
     }
   }
   if (side) {
-    const Damp sdamp(sx, nx, a.nbl);
+    const Damp<V> sdamp(sx, nx, a.nbl);
     const int dz = border_dist(sz, nz, a.nbl);
-    f32x2 lap[1], u[1], incr, incd, v;
-    lap_pairs<1, G::W1>(&L1U[sr + kHalo][sc + kHalo], lap, u, a.c);
-    if (act1) src.add(&lap[0], sx, sz, q1);
-    step_pair(u[0], su2, scf, lap[0], sdamp, dz, a.eta_dt, &incr, &v);
-    *reinterpret_cast<f32x2*>(&LEU[sr][sc]) = v;
-    lap_pairs<1, G::W1>(&L1D[sr + kHalo][sc + kHalo], lap, u, a.c);
+    fv<V> lap[1], u[1], incr, incd, v;
+    lap_rows<V, 1, G::W1>(&L1U[sr + kHalo][sc + kHalo], lap, u, a.c);
+    if (act1) src.add<V>(&lap[0], sx, sz, q1);
+    step_cols<V>(u[0], su2, scf, lap[0], sdamp, dz, a.eta_dt, &incr, &v);
+    lds<V>(LEU[sr][sc]) = v;
+    lap_rows<V, 1, G::W1>(&L1D[sr + kHalo][sc + kHalo], lap, u, a.c);
     scatter(&lap[0], sdm, incr);
-    step_pair(u[0], sd2, scf, lap[0], sdamp, dz, a.eta_dt, &incd, &v);
-    *reinterpret_cast<f32x2*>(&LED[sr][sc]) = v;
+    step_cols<V>(u[0], sd2, scf, lap[0], sdamp, dz, a.eta_dt, &incd, &v);
+    lds<V>(LED[sr][sc]) = v;
   }
   __syncthreads();
 
   if (act2 && a.d != nullptr) gather<G::NT, G::WE>(a, T, S, LED, zE, T.x0 - kHalo, k);
   if (!act2) return;
   // second step: levels k+1 on the tile (every lane computes; stores outside the grid drop)
-  f32x2 lap[RB], u[RB], inc[RB];
-  lap_pairs<RB, G::WE>(&LEU[wv * RB + kHalo][kHalo + 2 * lane], lap, u, a.c);
+  fv<V> lap[RB], u[RB], inc[RB];
+  lap_rows<V, RB, G::WE>(&LEU[wv * RB + kHalo][kHalo + V * lane], lap, u, a.c);
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     const int lr = wv * RB + i, z = T.z0 + lr;
-    const f32x2 um2 = *reinterpret_cast<const f32x2*>(&L1U[lr + 2 * kHalo][2 * kHalo + 2 * lane]);
-    src.add(&lap[i], x, z, q2);
-    f32x2 v;
-    step_pair(u[i], um2, tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &inc[i], &v);
-    stb2(uo2, v, cx, z * row4);
+    const fv<V> um2 = lds<V>(L1U[lr + 2 * kHalo][2 * kHalo + V * lane]);
+    src.add<V>(&lap[i], x, z, q2);
+    fv<V> v;
+    step_cols<V>(u[i], um2, tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &inc[i], &v);
+    stv<V>(uo2, v, cx, z * row4);
   }
-  lap_pairs<RB, G::WE>(&LED[wv * RB + kHalo][kHalo + 2 * lane], lap, u, a.c);
+  lap_rows<V, RB, G::WE>(&LED[wv * RB + kHalo][kHalo + V * lane], lap, u, a.c);
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     const int lr = wv * RB + i, z = T.z0 + lr;
-    const f32x2 dm2 = *reinterpret_cast<const f32x2*>(&L1D[lr + 2 * kHalo][2 * kHalo + 2 * lane]);
+    const fv<V> dm2 = lds<V>(L1D[lr + 2 * kHalo][2 * kHalo + V * lane]);
     scatter(&lap[i], tdm[i], inc[i]);
-    f32x2 incd, v;
-    step_pair(u[i], dm2, tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incd, &v);
-    stb2(do2, v, cx, z * row4);
+    fv<V> incd, v;
+    step_cols<V>(u[i], dm2, tcf[i], lap[i], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incd, &v);
+    stv<V>(do2, v, cx, z * row4);
   }
 }
 
@@ -1201,24 +1256,24 @@ hipError_t adj2d_tz(const StepArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int TZ>
+template <int TZ, int V>
 hipError_t fwd2d2_tz(const StepArgs& a, int store, hipStream_t s) {
   switch (store) {
-    case kStoreNone: fwd2d2_kernel<TZ, kStoreNone><<<a.ntiles, F2<TZ>::NT, 0, s>>>(a); break;
-    case kStoreF32: fwd2d2_kernel<TZ, kStoreF32><<<a.ntiles, F2<TZ>::NT, 0, s>>>(a); break;
-    case kStoreProbe: fwd2d2_kernel<TZ, kStoreProbe><<<a.ntiles, F2<TZ>::NT, 0, s>>>(a); break;
+    case kStoreNone: fwd2d2_kernel<TZ, V, kStoreNone><<<a.ntiles, F2<TZ, V>::NT, 0, s>>>(a); break;
+    case kStoreF32: fwd2d2_kernel<TZ, V, kStoreF32><<<a.ntiles, F2<TZ, V>::NT, 0, s>>>(a); break;
+    case kStoreProbe: fwd2d2_kernel<TZ, V, kStoreProbe><<<a.ntiles, F2<TZ, V>::NT, 0, s>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-template <int TZ>
+template <int TZ, int V>
 hipError_t adj2d2_tz(const StepArgs& a, hipStream_t s) {
   switch (a.image_src) {
-    case kImgNone: adj2d2_kernel<TZ, kImgNone><<<a.ntiles, F2<TZ>::NT, 0, s>>>(a); break;
-    case kImgFull32: adj2d2_kernel<TZ, kImgFull32><<<a.ntiles, F2<TZ>::NT, 0, s>>>(a); break;
-    case kImgBuffers: adj2d2_kernel<TZ, kImgBuffers><<<a.ntiles, F2<TZ>::NT, 0, s>>>(a); break;
-    case kImgProbe: adj2d2_kernel<TZ, kImgProbe><<<a.ntiles, F2<TZ>::NT, 0, s>>>(a); break;
+    case kImgNone: adj2d2_kernel<TZ, V, kImgNone><<<a.ntiles, F2<TZ, V>::NT, 0, s>>>(a); break;
+    case kImgFull32: adj2d2_kernel<TZ, V, kImgFull32><<<a.ntiles, F2<TZ, V>::NT, 0, s>>>(a); break;
+    case kImgBuffers: adj2d2_kernel<TZ, V, kImgBuffers><<<a.ntiles, F2<TZ, V>::NT, 0, s>>>(a); break;
+    case kImgProbe: adj2d2_kernel<TZ, V, kImgProbe><<<a.ntiles, F2<TZ, V>::NT, 0, s>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1226,26 +1281,55 @@ hipError_t adj2d2_tz(const StepArgs& a, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_fwd2d2(const StepArgs& a, int tz, int store, hipStream_t s) {
-  if (a.ntiles <= 0) return hipSuccess;
+namespace {
+template <int V>
+hipError_t fwd2d2_v(const StepArgs& a, int tz, int store, hipStream_t s) {
   switch (tz) {
-    case 8: return fwd2d2_tz<8>(a, store, s);
-    case 16: return fwd2d2_tz<16>(a, store, s);
-    case 24: return fwd2d2_tz<24>(a, store, s);
-    case 32: return fwd2d2_tz<32>(a, store, s);
+    case 8: return fwd2d2_tz<8, V>(a, store, s);
+    case 16: return fwd2d2_tz<16, V>(a, store, s);
+    case 24: return fwd2d2_tz<24, V>(a, store, s);
+    case 32: return fwd2d2_tz<32, V>(a, store, s);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_adj2d2(const StepArgs& a, int tz, hipStream_t s) {
-  if (a.ntiles <= 0) return hipSuccess;
+template <int V>
+hipError_t adj2d2_v(const StepArgs& a, int tz, hipStream_t s) {
   switch (tz) {
-    case 8: return adj2d2_tz<8>(a, s);
-    case 16: return adj2d2_tz<16>(a, s);
-    case 24: return adj2d2_tz<24>(a, s);
-    case 32: return adj2d2_tz<32>(a, s);
+    case 8: return adj2d2_tz<8, V>(a, s);
+    case 16: return adj2d2_tz<16, V>(a, s);
+    case 24: return adj2d2_tz<24, V>(a, s);
+    case 32: return adj2d2_tz<32, V>(a, s);
   }
   return hipErrorInvalidValue;
+}
+
+template <int V>
+hipError_t born2d2_v(const StepArgs& a, int tz, hipStream_t s) {
+  switch (tz) {
+    case 8: born2d2_kernel<8, V><<<a.ntiles, F2<8, V>::NT, 0, s>>>(a); break;
+    case 16: born2d2_kernel<16, V><<<a.ntiles, F2<16, V>::NT, 0, s>>>(a); break;
+    case 24: born2d2_kernel<24, V><<<a.ntiles, F2<24, V>::NT, 0, s>>>(a); break;
+    case 32: born2d2_kernel<32, V><<<a.ntiles, F2<32, V>::NT, 0, s>>>(a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_fwd2d2(const StepArgs& a, int tx, int tz, int store, hipStream_t s) {
+  if (a.ntiles <= 0) return hipSuccess;
+  return tx == 64 ? fwd2d2_v<1>(a, tz, store, s) : tx == 128 ? fwd2d2_v<2>(a, tz, store, s) : hipErrorInvalidValue;
+}
+
+hipError_t launch_adj2d2(const StepArgs& a, int tx, int tz, hipStream_t s) {
+  if (a.ntiles <= 0) return hipSuccess;
+  return tx == 64 ? adj2d2_v<1>(a, tz, s) : tx == 128 ? adj2d2_v<2>(a, tz, s) : hipErrorInvalidValue;
+}
+
+hipError_t launch_born2d2(const StepArgs& a, int tx, int tz, hipStream_t s) {
+  if (a.ntiles <= 0) return hipSuccess;
+  return tx == 64 ? born2d2_v<1>(a, tz, s) : tx == 128 ? born2d2_v<2>(a, tz, s) : hipErrorInvalidValue;
 }
 
 hipError_t launch_fwd2d(const StepArgs& a, int tz, int store, hipStream_t s) {
@@ -1274,18 +1358,6 @@ hipError_t launch_adj2d(const StepArgs& a, int tz, hipStream_t s) {
     case 64: return adj2d_tz<64>(a, s);
   }
   return hipErrorInvalidValue;
-}
-
-hipError_t launch_born2d2(const StepArgs& a, int tz, hipStream_t s) {
-  if (a.ntiles <= 0) return hipSuccess;
-  switch (tz) {
-    case 8: born2d2_kernel<8><<<a.ntiles, F2<8>::NT, 0, s>>>(a); break;
-    case 16: born2d2_kernel<16><<<a.ntiles, F2<16>::NT, 0, s>>>(a); break;
-    case 24: born2d2_kernel<24><<<a.ntiles, F2<24>::NT, 0, s>>>(a); break;
-    case 32: born2d2_kernel<32><<<a.ntiles, F2<32>::NT, 0, s>>>(a); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
 }
 
 hipError_t launch_born2d(const StepArgs& a, int tz, hipStream_t s) {

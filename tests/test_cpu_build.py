@@ -127,3 +127,14 @@ def test_3d_bricks_on_the_cpu_build(emu_lib):
     res = json.loads(r.stdout.strip().splitlines()[-1])
     print(res)
     assert all(res["bitwise"].values())
+
+
+def test_two_level_wide_tiles_on_the_cpu_build(emu_lib):
+    """Two levels per launch on 128-column tiles against one level per launch, under AddressSanitizer with
+    the host launch checks on: bitwise."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_two_level_wide.py")], emu_lib, timeout=900)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    print(res)
+    assert all(res["bitwise"]) and all(res["nonzero"])

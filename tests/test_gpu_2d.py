@@ -411,18 +411,23 @@ def test_kernel_timing_counts_every_step_launch_of_a_checkpointed_gradient():
 
 
 @pytest.mark.parametrize("tz", [8, 16, 24, 32])
-def test_two_level_tiles_at_their_column_edges_are_bitwise_the_one_level_path(tz):
-    """Windows one column short of, exactly and one column past one and two 128-column tiles (odd
-    widths end in half a column pair), with depths on both sides of a tile row edge, sources beside a tile
-    edge and receivers across it: gradient, F^T dd, traces and Born traces of the two-level kernels are
-    bitwise those of the one-level kernels (the same arithmetic per point)."""
+@pytest.mark.parametrize("widths", [[53, 54, 55], [117, 119, 13], [118] * 60 + [117] * 60, [245, 246] * 30],
+                         ids=["edge64", "edge128", "wide128", "wide256"])
+def test_two_level_tiles_at_their_column_edges_are_bitwise_the_one_level_path(tz, widths):
+    """Windows one column short of, exactly and one column past whole tiles (a few shots run on 64-column
+    tiles, many on 128-column ones; odd widths end in half a column pair), with depths on both sides of a
+    tile row edge, sources beside a tile edge and receivers across it: gradient, F^T dd, traces and Born
+    traces of the two-level kernels are bitwise those of the one-level kernels (the same arithmetic per
+    point)."""
     nbl = 5
-    for nz, widths in ((tz - 2 * nbl if tz > 2 * nbl + 4 else 25 - 2 * nbl, [117, 118, 119]), (39, [246, 247, 13])):
-        wl = W.small_2d(nz=nz + 2, nbl=nbl, windows=widths, T_per_shot=[60.0, 47.0, 53.0], nrec=29)
-        for s in wl.shots:   # base nodes in the last column of the first tile
+    many = len(widths) > 3
+    for nz in ((41 - 2 * nbl, 48 - 2 * nbl) if many else (max(tz, 17) - 2 * nbl, max(tz, 17) + 1 - 2 * nbl, 39)):
+        T = [30.0, 23.0, 26.0] if many else [60.0, 47.0, 53.0]
+        wl = W.small_2d(nz=nz, nbl=nbl, windows=widths, T_per_shot=[T[i % 3] for i in range(len(widths))], nrec=29)
+        for s in wl.shots:   # base nodes in the last column of a tile
             s.src[0] = min((127 - nbl + 0.4) * wl.h, (widths[s.window] - 3) * wl.h)
         dds = _residuals(wl)
-        dms = [W.random_field(wl.comp_shape(w), 23 + w, 2.0) * 0.01 for w in range(wl.nwindow)]
+        dms = [W.random_field(wl.comp_shape(w), 23 + w) * 0.01 for w in range(wl.nwindow)]
         outs = []
         for fuse in (A.FUSE_BOTH, A.FUSE_NONE):
             plan = make_plan(wl, storage=A.Storage(A.STORE_FULL))
