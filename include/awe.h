@@ -351,8 +351,8 @@ awe_status awe_plan_set_tiles(awe_plan* plan, int32_t tz, int32_t ty, int32_t bz
 /* 2D only: advance two time levels per launch, chosen per direction by the bits of mode:
  * AWE_FUSE_FORWARD for forward solves and Born modelling, AWE_FUSE_ADJOINT for reverse sweeps (0:
  * one level per launch everywhere).  Until this call or the autotuner sets it, a plan uses both, or
- * neither with CHECKPOINT storage or a 16-bit FULL store; its tile rows follow the size of the work.  The two-level kernels serve forward solves without
- * storage, with FULL FP32 storage or into PROBED sums, reverse sweeps from FULL FP32
+ * neither with CHECKPOINT storage; its tile rows follow the size of the work.  The two-level kernels
+ * serve forward solves without storage, with FULL storage or into PROBED sums, reverse sweeps from FULL
  * storage, into PROBED sums or without imaging, and the paired reversals of a CHECKPOINT
  * gradient (imaging from the recomputed forward levels); other modes always use one level per
  * launch.

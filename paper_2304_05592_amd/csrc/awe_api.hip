@@ -456,11 +456,10 @@ bool fused_ok(const awe_plan* P, int bit) {
   return P->ndim == 2 && (P->fuse2 & bit) && two_level_rows(tz);
 }
 
-// Does a direction in two-level mode also launch one-level kernels?  The levels of a 16-bit store
-// (quantised one level late) and the forward steps of a checkpointed gradient.
+// Does a direction in two-level mode also launch one-level kernels?  The forward steps of a
+// checkpointed gradient.
 bool one_level_too(const awe_plan* P, int bit) {
-  return (P->store.mode == AWE_STORE_FULL && P->store.prec != AWE_PREC_FP32) ||
-         (bit == AWE_FUSE_FORWARD && P->store.mode == AWE_STORE_CHECKPOINT);
+  return bit == AWE_FUSE_FORWARD && P->store.mode == AWE_STORE_CHECKPOINT;
 }
 
 // Tiles w columns wide and 24 rows high of a launch (the largest shot group's).
@@ -491,7 +490,7 @@ bool wide_tiles(const awe_plan* P, int bit) {
 // Launch shapes of the directions the caller has not set, from the storage and the work of a launch.
 //
 // 2D: two levels per launch, except for CHECKPOINT storage, whose launches stay one level each unless
-// asked otherwise, and for a 16-bit FULL store, whose kernels are one-level.  Two levels won at every
+// asked otherwise.  Two levels won at every
 // size timed: one shot of 281 x 181 2.3 -> 1.2 ms forward; one shot of 730 x 421 (1200 samples) 10.6 ->
 // 7.4 ms gradient; 24 shots of 592 x 336 (600 samples) 27.5 -> 18.
 // Tile rows follow the number of tiles: few are bound by the chain of one tile, so its rows are cut;
@@ -507,8 +506,7 @@ bool wide_tiles(const awe_plan* P, int bit) {
 // probes (400 samples) take 28.5, 29.9, 32.5, 34.6 ms.
 void default_shapes(awe_plan* P) {
   if (P->ndim != 2) return;
-  const bool one_level = P->store.mode == AWE_STORE_CHECKPOINT ||
-                         (P->store.mode == AWE_STORE_FULL && P->store.prec != AWE_PREC_FP32);
+  const bool one_level = P->store.mode == AWE_STORE_CHECKPOINT;
   if (P->auto_fuse) P->fuse2 = one_level ? AWE_FUSE_NONE : AWE_FUSE_BOTH;
   const bool probed = P->store.mode == AWE_STORE_PROBED;
   const long long n64 = tiles24(P, 64), n128 = tiles24(P, 128);
@@ -794,8 +792,7 @@ awe_status step_adj2(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s, bool s
 // Forward levels 1..nsteps: one single step first when the count is odd, then pairs.
 awe_status forward_loop(awe_plan* P, awe::StepArgs& a, int store, hipStream_t s) {
   awe_status st;
-  const bool fuse = fused_ok(P, AWE_FUSE_FORWARD) &&
-                    (store == awe::kStoreNone || store == awe::kStoreF32 || store == awe::kStoreProbe);
+  const bool fuse = fused_ok(P, AWE_FUSE_FORWARD);
   // a 2D FP32 sweep of one-level steps reads its previous levels back from the store
   if (!fuse && P->ndim == 2 && store == awe::kStoreF32) store = awe::kStoreF32R;
   ProfRun run(P, s, 0);
@@ -814,8 +811,7 @@ awe_status forward_loop(awe_plan* P, awe::StepArgs& a, int store, hipStream_t s)
 // Adjoint levels nsteps..1 (same pairing, from the top).
 awe_status adjoint_loop(awe_plan* P, awe::StepArgs& a, hipStream_t s) {
   awe_status st;
-  const bool fuse = fused_ok(P, AWE_FUSE_ADJOINT) &&
-                    (a.image_src == awe::kImgNone || a.image_src == awe::kImgFull32 || a.image_src == awe::kImgProbe);
+  const bool fuse = fused_ok(P, AWE_FUSE_ADJOINT);
   ProfRun run(P, s, 1);
   int n = P->nsteps;
   if (fuse && (P->nsteps & 1)) {
@@ -1427,13 +1423,10 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
   // probe adjoint levels only, so each direction keeps its own fastest shape
   struct Cand { int tz, ty, bz, fuse; };
   std::vector<Cand> cands;
-  const bool fusable = P->store.mode == AWE_STORE_NONE || P->store.mode == AWE_STORE_PROBED ||
-                       P->store.mode == AWE_STORE_CHECKPOINT ||
-                       (P->store.mode == AWE_STORE_FULL && P->store.prec == AWE_PREC_FP32);
   if (P->ndim == 2) {
     for (int tz : {8, 16, 24, 32, 64}) {
       cands.push_back({tz, 8, 0, 0});
-      if (fusable && tz != 64) cands.push_back({tz, 8, 0, 1});
+      if (tz != 64) cands.push_back({tz, 8, 0, 1});
     }
   } else {
     // z-blocks of the full depth, of fixed lengths, and of the depth split evenly into 2 to 8
@@ -1720,7 +1713,7 @@ awe_status awe_forward(awe_plan* P, const float* m, const float* q, float* d, in
     for (P->cur = 0; P->cur < G; ++P->cur)
       if ((st = forward_loop(P, a, kind, s)) != AWE_OK) return st;
     if (kind == awe::kStoreBF16 || kind == awe::kStoreFP16)
-      AWE_HIP(awe::launch_store_last(a, P->nshot, P->max_win_npts, s));
+      AWE_HIP(awe::launch_store_last(a, P->nshot, fused_ok(P, AWE_FUSE_FORWARD) ? 2 : 1, P->max_win_npts, s));
   }
   if (d) AWE_HIP(awe::launch_gather_last(a, P->nshot, P->total_recs, 0, s));
   if (store) P->kept_ws = ws;

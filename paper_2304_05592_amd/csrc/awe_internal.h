@@ -208,8 +208,8 @@ hipError_t launch_fill(unsigned char* ws, long long off, long long nbytes, hipSt
 hipError_t launch_screen(const float* x, long long n, double lo, unsigned long long* cnt, hipStream_t stream);
 hipError_t launch_screen(const double* x, long long n, double lo, unsigned long long* cnt, hipStream_t stream);
 hipError_t launch_fwd2d(const StepArgs& a, int tz, int store, hipStream_t stream);
-// Quantise the last forward level u^{nt-1} of every shot into the scaled FULL store.
-hipError_t launch_store_last(const StepArgs& a, int nshot, long long max_npts, hipStream_t stream);
+// Quantise the last `levels` forward levels u^{nt-1}, ... of every shot into the scaled FULL store.
+hipError_t launch_store_last(const StepArgs& a, int nshot, int levels, long long max_npts, hipStream_t stream);
 hipError_t launch_adj2d(const StepArgs& a, int tz, hipStream_t stream);
 // Two 2D steps per launch (levels step, step+1 forward; step, step-1 adjoint); tz 8, 16, 24 or 32,
 // on tiles of tx columns (64, one column per lane, or 128, two).

@@ -36,27 +36,31 @@ __device__ __forceinline__ float level_scale(const float* scl, int level) {
   return s;
 }
 
-// Max over the workgroup (all threads must call; uses one small LDS array), then one atomic
-// max on the float bits (exact and order independent for non-negative values) into the
-// workgroup's slot of this level.
+// One atomic max on the float bits of the N waves' maxima red (exact and order independent for
+// non-negative values) into the workgroup's slot of this level; one thread calls it.
 // PEEK: read the slot first and send no atomic that it already exceeds (3D).
-template <bool PEEK>
+template <int N, bool PEEK = false>
+__device__ __forceinline__ void max_to_slot(const float* red, float* scl, int level) {
+  float m = red[0];
+  for (int w = 1; w < N; ++w) m = fmaxf(m, red[w]);
+  // the atomics of a shot's level queue on one cache line, about 50 ns each: the 3600 workgroups of a
+  // 240^3 step took 183 us, 69 without the store; with the peek 75.  A 2D shot has too few
+  // workgroups for that, and the peek's latency showed there (1 to 3 % at 5 us a launch).  A stale
+  // read only sends an atomic that changes nothing.
+  unsigned* slot = reinterpret_cast<unsigned*>(scl) + level * kScaleSlots + (blockIdx.x & (kScaleSlots - 1));
+  if (!PEEK || __float_as_uint(m) > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(slot, __float_as_uint(m));
+}
+
+// max_to_slot of a value per thread of a workgroup of N waves (all threads must call; uses one small LDS
+// array).
+template <int N, bool PEEK>
 __device__ __forceinline__ void block_max_to_slot(float v, float* scl, int level) {
-  __shared__ float red[16];
+  __shared__ float red[N];
   v = wave_max(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    float m = red[0];
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = fmaxf(m, red[w]);
-    // the atomics of a shot's level queue on one cache line, about 50 ns each: the 3600 workgroups of a
-    // 240^3 step took 183 us, 69 without the store; with the peek 75.  A 2D shot has too few
-    // workgroups for that, and the peek's latency showed there (1 to 3 % at 5 us a launch).  A stale
-    // read only sends an atomic that changes nothing.
-    unsigned* slot = reinterpret_cast<unsigned*>(scl) + level * kScaleSlots + (blockIdx.x & (kScaleSlots - 1));
-    if (!PEEK || __float_as_uint(m) > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(slot, __float_as_uint(m));
-  }
+  if (threadIdx.x == 0) max_to_slot<N, PEEK>(red, scl, level);
 }
 
 }  // namespace awe

@@ -311,7 +311,7 @@ void fwd3d_kernel(StepArgs a, int bzlen) {
     plane(z, hA, qA, u2A, cfA, hB, qB, u2B, cfB);
     if (z + 1 < zend) plane(z + 1, hB, qB, u2B, cfB, hA, qA, u2A, cfA);
   }
-  if (S16) block_max_to_slot<true>(lmax, scl, k);
+  if (S16) block_max_to_slot<T3<TY>::NW, true>(lmax, scl, k);
 }
 
 // ------------------------------------------------------------------------------ adjoint
@@ -644,7 +644,7 @@ __global__ __launch_bounds__(kBT) void fwd3b_kernel(StepArgs a) {
       probe_add(probe_sums(pb, z * plane_pts + (cv >> 2), a.probe_r), a.probe_r, pcol, (double)incr, true, nullptr, 0.0,
                 false, a.probe_pitch);
   }
-  if (S16) block_max_to_slot<true>(lmax, scl, k);
+  if (S16) block_max_to_slot<kBT / 64, true>(lmax, scl, k);
 }
 
 template <int IMG, bool NT>

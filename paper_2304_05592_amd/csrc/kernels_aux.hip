@@ -131,10 +131,11 @@ __global__ void slot_kernel(StepArgs a, int slot, int state, int dir) {
   }
 }
 
-// u^{nt-1} -> FULL 16-bit store with its scale (the forward steps quantise u^1..u^{nt-2}).
+// u^{nt-1-blockIdx.z} -> FULL 16-bit store with its scale (the forward steps quantise the levels
+// below).
 __global__ void store_last_kernel(StepArgs a) {
   const ShotDev& S = a.t.shots[blockIdx.y];
-  const int k = S.nt - 1;
+  const int k = S.nt - 1 - (int)blockIdx.z;
   if (k < 1) return;
   const float* f = fbuf(a.ws, S, fwd_buf(k));
   const float inv = inv_scale(level_scale(reinterpret_cast<const float*>(a.ws + S.scale), k));
@@ -467,8 +468,8 @@ hipError_t launch_slot(const StepArgs& a, int nshot, int slot, int state, int di
   return hipGetLastError();
 }
 
-hipError_t launch_store_last(const StepArgs& a, int nshot, long long max_npts, hipStream_t s) {
-  store_last_kernel<<<dim3(grid_for(max_npts), nshot), kThreads, 0, s>>>(a);
+hipError_t launch_store_last(const StepArgs& a, int nshot, int levels, long long max_npts, hipStream_t s) {
+  store_last_kernel<<<dim3(grid_for(max_npts), nshot, levels), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 

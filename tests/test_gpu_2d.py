@@ -440,3 +440,26 @@ def test_two_level_tiles_at_their_column_edges_are_bitwise_the_one_level_path(tz
             outs.append([t.cpu() for t in (g, v, d, b)])
         for a, b in zip(*outs):
             assert torch.equal(a, b) and torch.isfinite(a).all() and a.abs().max() > 0
+
+
+@pytest.mark.parametrize("prec", [A.PREC_BF16, A.PREC_FP16], ids=["bf16", "fp16"])
+@pytest.mark.parametrize("widths,T", [([53, 54, 55], [60.0, 47.0, 53.0]), ([118] * 60 + [117] * 60, [30.0, 23.0]),
+                                      ([53], [2.0]), ([53, 54], [3.0, 1.0])],
+                         ids=["narrow", "wide", "one_step", "few_steps"])
+def test_two_level_16bit_store_is_bitwise_the_one_level_path(prec, widths, T):
+    """A 16-bit FULL store written two levels per launch (the levels before the last two by the steps, the
+    last two afterwards; from two samples on) holds the same codes and scales: gradient, F^T dd and traces
+    are bitwise those of one level per launch."""
+    wl = W.small_2d(nz=31, nbl=5, windows=widths, T_per_shot=[T[i % len(T)] for i in range(len(widths))], nrec=29)
+    dds = _residuals(wl)
+    outs = []
+    for fuse in (A.FUSE_BOTH, A.FUSE_NONE):
+        plan = make_plan(wl, storage=A.Storage(A.STORE_FULL, prec=prec))
+        plan.set_fusion(fuse)
+        m, q = gpu_inputs(wl, plan)
+        g, v, d = plan.gradient(m, q, plan.pack(dds, "d"), v=True, d=True)
+        _sync()
+        outs.append([t.cpu() for t in (g, v, d)])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b) and torch.isfinite(a).all()
+    assert max(T) < 10.0 or outs[0][0].abs().max() > 0
