@@ -52,8 +52,10 @@ BYTES = {
 FUSED_BYTES = {
     ("forward", "none"): 20,   # read u^{k-1}, u^{k-2}, coef; write u^k, u^{k+1}
     ("forward", "fp32"): 28,   # + stored copies of u^k and u^{k+1}
+    ("forward", "16bit"): 24,  # + 16-bit stored copies of u^{k-1} and u^{k-2}
     ("adjoint", "none"): 20,   # read w^{j+1}, w^{j+2}, coef; write w^j, w^{j-1}
     ("adjoint", "fp32"): 44,   # read w^{j+1}, w^{j+2}, coef, stored u^j, u^{j-1}, acc; write w^j, w^{j-1}, acc
+    ("adjoint", "16bit"): 40,  # the same with 16-bit u^j, u^{j-1}
     ("adjoint", "buffers"): 44,  # the same with u^j, u^{j-1} from the recomputed forward levels
     ("born", "none"): 40,      # read u^{k-1}, u^{k-2}, du^{k-1}, du^{k-2}, coef, dm; write u, du at k and k+1
 }
@@ -575,7 +577,11 @@ def bench_c3(args):
     sync()
     prof = plan.profile_read()
     plan.profile_disable()
-    # paired reversals (x, x-1) run as one two-level launch when the adjoint fusion is on
+    # advances run as pairs of levels, after a single one where their count is odd, when the forward fusion
+    # is on; paired reversals (x, x-1) as one two-level launch when the adjoint fusion is
+    fuse_fwd = bool(plan.get_tiles()["fusion"] & A.FUSE_FORWARD)
+    advances = [b - a for op, a, b in sched if op == 0]
+    mixed = {"forward": (sum(n // 2 for n in advances), sum(n % 2 for n in advances))} if fuse_fwd else {}
     two = bool(plan.get_tiles()["fusion"] & A.FUSE_ADJOINT)
     pairs = singles = 0
     i = 0
@@ -588,9 +594,11 @@ def bench_c3(args):
                 continue
             singles += 1
         i += 1
-    kernels = kernel_table(prof, launch_points, {"forward": "none", "adjoint": "buffers"},
-                           mixed={"adjoint": (pairs, singles)} if two else None)
-    names = {"forward": "fwd2d step (forward / recompute, 16 B/point)",
+    if two:
+        mixed["adjoint"] = (pairs, singles)
+    kernels = kernel_table(prof, launch_points, {"forward": "none", "adjoint": "buffers"}, mixed=mixed)
+    names = {"forward": ("fwd2d2 steps (forward / recompute, two levels per launch, 16 B/point-update)" if fuse_fwd
+                         else "fwd2d step (forward / recompute, 16 B/point)"),
              "adjoint": ("adj2d2 / adj2d steps (paired reversals two levels per launch, imaging from the "
                          "recomputed forward levels, 36 B/point-update)" if two else
                          "adj2d step (adjoint + imaging from recomputed buffers, 36 B/point)")}

@@ -298,10 +298,11 @@ awe_status awe_checkpoint_schedule(int32_t nsteps, int32_t nslots, int32_t* acti
 
 /* Tile-shape autotuner (setup call, synchronous).  The plan has a launch shape for its forward
  * solves (and Born modelling) and one for its adjoint steps (reverse sweeps and awe_adjoint); the
- * autotuner chooses each separately.  Candidates: 2D 8, 16, 24, 32 or 64 rows of 64 columns, and -
- * where the storage mode allows it - 8, 16, 24 or 32 rows with two time levels per launch (see
- * awe_plan_set_fusion); 3D bricks of 64 x 8 x 8 points (ty = 8, bz = 8, the default) and 64 x {4, 8, 16} columns with z-blocks of the full depth, of 128, 64 or
- * 32 planes, and of the depth split evenly in 2 to 8 (rounded up to an even plane count).  The forward probe times the last probe_steps forward levels of the sweep (storing
+ * autotuner chooses each separately.  Candidates: 2D 8, 16, 24 or 32 rows with two time levels per launch
+ * and 24 rows with one (see awe_plan_set_fusion); 3D bricks of 64 x 8 x 8 points (ty = 8, bz = 8, the
+ * default) and 64 x {4, 8, 16} columns with z-blocks of the full depth, of 128, 64 or 32 planes, and of the
+ * depth split evenly in 2 to 8 (rounded up to an even plane count).  The forward probe times the last
+ * probe_steps forward levels of the sweep (storing
  * the wavefield when the plan keeps one in FP32), the adjoint probe the last probe_steps adjoint
  * levels (with imaging when the plan keeps a wavefield; with PROBED storage both probes add to
  * the probe sums, taking their coefficients from the workspace), on the given inputs; the
@@ -350,12 +351,10 @@ awe_status awe_plan_set_tiles(awe_plan* plan, int32_t tz, int32_t ty, int32_t bz
 
 /* 2D only: advance two time levels per launch, chosen per direction by the bits of mode:
  * AWE_FUSE_FORWARD for forward solves and Born modelling, AWE_FUSE_ADJOINT for reverse sweeps (0:
- * one level per launch everywhere).  Until this call or the autotuner sets it, a plan uses both, or
- * neither with CHECKPOINT storage; its tile rows follow the size of the work.  The two-level kernels
- * serve forward solves without storage, with FULL storage or into PROBED sums, reverse sweeps from FULL
- * storage, into PROBED sums or without imaging, and the paired reversals of a CHECKPOINT
- * gradient (imaging from the recomputed forward levels); other modes always use one level per
- * launch.
+ * one level per launch everywhere).  Until this call or the autotuner sets it, a plan uses both, and
+ * its tile rows follow the size of the work.  The two-level kernels serve every storage: forward solves
+ * (a checkpoint advance of an odd number of levels begins with one level), Born modelling, reverse sweeps
+ * and the paired reversals of a CHECKPOINT gradient.
  * Results are bitwise identical either way (a two-level launch adds both levels' terms to an
  * FP64 sum in the order two launches would).  Two levels per launch need tiles of 8, 16, 24 or 32 rows (16 or 32 are set
  * otherwise).  Errors: INVALID_ARG (mode outside 0..3), HIP. */
@@ -368,7 +367,8 @@ awe_status awe_plan_set_fusion(awe_plan* plan, int32_t mode);
  * The steps of one sweep (the forward or the adjoint step loop of a call, per shot group) and
  * the forward steps of one checkpoint advance each form one interval, which counts every launch
  * it holds, so that no event is recorded between them; other step launches are timed one by
- * one.
+ * one.  With CHECKPOINT storage a plan whose fusion mode was never set counts time levels, the schedule's
+ * steps, in place of launches.
  * The records are stream work, so they are also captured into a HIP graph and then time
  * the graph's replays.  Classes: 0 forward step, 1 adjoint step (with imaging and, in 3D,
  * receiver injection), 2 Born step.  awe_profile_read waits for the recorded events,

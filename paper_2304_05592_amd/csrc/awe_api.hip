@@ -456,12 +456,6 @@ bool fused_ok(const awe_plan* P, int bit) {
   return P->ndim == 2 && (P->fuse2 & bit) && two_level_rows(tz);
 }
 
-// Does a direction in two-level mode also launch one-level kernels?  The forward steps of a
-// checkpointed gradient.
-bool one_level_too(const awe_plan* P, int bit) {
-  return bit == AWE_FUSE_FORWARD && P->store.mode == AWE_STORE_CHECKPOINT;
-}
-
 // Tiles w columns wide and 24 rows high of a launch (the largest shot group's).
 long long tiles24(const awe_plan* P, int w) {
   long long n = 0;
@@ -489,10 +483,10 @@ bool wide_tiles(const awe_plan* P, int bit) {
 
 // Launch shapes of the directions the caller has not set, from the storage and the work of a launch.
 //
-// 2D: two levels per launch, except for CHECKPOINT storage, whose launches stay one level each unless
-// asked otherwise.  Two levels won at every
-// size timed: one shot of 281 x 181 2.3 -> 1.2 ms forward; one shot of 730 x 421 (1200 samples) 10.6 ->
-// 7.4 ms gradient; 24 shots of 592 x 336 (600 samples) 27.5 -> 18.
+// 2D: two levels per launch, which won at every size timed: one shot of 281 x 181 2.3 -> 1.2 ms forward;
+// one shot of 730 x 421 (1200 samples) 10.6 -> 7.4 ms gradient; 24 shots of 592 x 336 (600 samples) 27.5 ->
+// 18; autograd pass with 16 checkpoints, 500 samples, 16 shots of 1104 x 592 63.3 -> 48.5, one of 730 x
+// 421 6.7 -> 4.8.
 // Tile rows follow the number of tiles: few are bound by the chain of one tile, so its rows are cut;
 // many by the halo, so they grow.  us per launch, forward with store / reverse, at 8, 16, 24, 32 rows:
 //   64 wide, n =   40:  4.0, 4.4, 4.9, 5.5     /  4.8, 5.6, 6.2, 7.2
@@ -506,8 +500,7 @@ bool wide_tiles(const awe_plan* P, int bit) {
 // probes (400 samples) take 28.5, 29.9, 32.5, 34.6 ms.
 void default_shapes(awe_plan* P) {
   if (P->ndim != 2) return;
-  const bool one_level = P->store.mode == AWE_STORE_CHECKPOINT;
-  if (P->auto_fuse) P->fuse2 = one_level ? AWE_FUSE_NONE : AWE_FUSE_BOTH;
+  if (P->auto_fuse) P->fuse2 = AWE_FUSE_BOTH;
   const bool probed = P->store.mode == AWE_STORE_PROBED;
   const long long n64 = tiles24(P, 64), n128 = tiles24(P, 128);
   if (P->auto_rows[0])
@@ -537,7 +530,7 @@ awe_status rebuild(awe_plan* P, int dirs) {
     two.tz = one.tz;
     const bool fused = fused_ok(P, bit);
     for (Tiling* T : {&one, &two}) {
-      if (T == &two ? fused : !fused || one_level_too(P, bit)) {
+      if ((T == &two) == fused) {
         if ((st = build_tiling(P, *T)) != AWE_OK) return st;
         if ((st = upload_tiling(P, *T)) != AWE_OK) return st;
       } else if (T->dev) {
@@ -673,14 +666,16 @@ awe_status prepare(awe_plan* P, const float* m, void* ws, bool zero_fwd, bool ze
   return AWE_OK;
 }
 
-// Kernel timing: an event pair around one launch (class cls) when enabled and not full.
+// Kernel timing: an event pair around one launch (class cls) of `levels` levels when enabled and not
+// full.  CHECKPOINT plans whose fusion mode was never set count levels: the schedule's steps.
 struct ProfScope {
   awe_plan* P;
   hipStream_t s;
   bool on;
-  ProfScope(awe_plan* P_, int cls, hipStream_t s_) : P(P_), s(s_) {
+  ProfScope(awe_plan* P_, int cls, hipStream_t s_, int levels = 1) : P(P_), s(s_) {
+    const int count = P->auto_fuse && P->store.mode == AWE_STORE_CHECKPOINT ? levels : 1;
     if (P->prof_in_run) {  // counted into the enclosing run's interval
-      ++P->prof_run_launches;
+      P->prof_run_launches += count;
       on = false;
       return;
     }
@@ -688,7 +683,7 @@ struct ProfScope {
     if (on) {
       (void)hipEventRecord(P->prof_ev[P->prof_next], s);
       P->prof_cls.push_back(cls);
-      P->prof_cnt.push_back(1);
+      P->prof_cnt.push_back(count);
     }
   }
   ~ProfScope() {
@@ -774,7 +769,8 @@ awe_status step_fwd2(awe_plan* P, awe::StepArgs& a, int n, int store, hipStream_
   a.single = single;
   if (a.ntiles <= 0) return AWE_OK;
   if (awe_status st = check_step(P, P->fw2, a, n, last, "two-level forward step")) return st;
-  ProfScope ps(P, 0, s);
+  ProfScope ps(P, 0, s, single ? 1 : 2);
+  if (store == awe::kStoreNone && a.st_slot >= 0) store = awe::kStoreSlot;
   AWE_HIP(awe::launch_fwd2d2(a, P->fw2.tx, P->fw2.tz, store, s));
   return AWE_OK;
 }
@@ -784,7 +780,7 @@ awe_status step_adj2(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s, bool s
   a.single = single;
   if (a.ntiles <= 0) return AWE_OK;
   if (awe_status st = check_step(P, P->rv2, a, single ? n : n - 1, n, "two-level adjoint step")) return st;
-  ProfScope ps(P, 1, s);
+  ProfScope ps(P, 1, s, single ? 1 : 2);
   AWE_HIP(awe::launch_adj2d2(a, P->rv2.tx, P->rv2.tz, s));
   return AWE_OK;
 }
@@ -869,19 +865,23 @@ awe_status run_actions(awe_plan* P, awe::StepArgs& fa, awe::StepArgs& aa, size_t
     const int op = P->sched[3 * i], x = P->sched[3 * i + 1], y = P->sched[3 * i + 2];
     switch (op) {
       case awe::kAdvance: {
-        // a store of the reached state that follows is fused into the last step (2D, FP32
-        // slots, and not into the slot the step may still read by reference)
+        // a store of the reached state that follows is fused into the last launch (2D, FP32
+        // slots, and not into the slot the launch may still read by reference)
         int fuse_slot = -1;
         if (by_ref && P->ndim == 2 && i + 1 < end && P->sched[3 * (i + 1)] == awe::kStore &&
             P->sched[3 * (i + 1) + 2] == y &&
             !(fa.rs_level != awe::kNoLevel && fa.rs_slot == P->sched[3 * (i + 1) + 1]))
           fuse_slot = P->sched[3 * (i + 1) + 1];
         ProfRun run(P, s, 0);
-        for (int n = x + 1; n <= y; ++n) {
-          fa.st_slot = n == y ? fuse_slot : -1;
-          awe_status st = step_fwd(P, fa, n, 0, s);
+        const bool fused = fused_ok(P, AWE_FUSE_FORWARD);
+        for (int n = x + 1; n <= y;) {   // a single level first where the count is odd
+          const bool two = fused && ((y - n) & 1);
+          fa.st_slot = n + two == y ? fuse_slot : -1;
+          awe_status st = fused ? step_fwd2(P, fa, n, awe::kStoreNone, s, !two)
+                                : step_fwd(P, fa, n, awe::kStoreNone, s);
           fa.st_slot = -1;
           if (st != AWE_OK) return st;
+          n += 1 + two;
         }
         if (fuse_slot >= 0) ++i;  // the store is done
         break;
@@ -901,11 +901,7 @@ awe_status run_actions(awe_plan* P, awe::StepArgs& fa, awe::StepArgs& aa, size_t
         break;
       }
       case awe::kRestore:
-        if (x < 0) {
-          for (int i = 0; i < P->g_nshot[P->cur]; ++i) {
-            const ShotDev& d = P->sd[P->order[P->g_shot0[P->cur] + i]];
-            if (awe_status st = fill(P, fa.ws, d.fld, 4 * d.npts * 4, s, "forward buffers (zero state)")) return st;
-          }
+        if (x < 0) {  // the zero state: the 2D steps and reversals read no level below 1
           set_rs(awe::kNoLevel, 0);
         } else if (by_ref) {
           set_rs(y, x);  // FP32 slot: levels y and y - 1 are read from the slot in place
@@ -1424,10 +1420,9 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
   struct Cand { int tz, ty, bz, fuse; };
   std::vector<Cand> cands;
   if (P->ndim == 2) {
-    for (int tz : {8, 16, 24, 32, 64}) {
-      cands.push_back({tz, 8, 0, 0});
-      if (tz != 64) cands.push_back({tz, 8, 0, 1});
-    }
+    // one level per launch lost at every size timed (see default_shapes): its best shape stays in
+    for (int tz : {8, 16, 24, 32}) cands.push_back({tz, 8, 0, 1});
+    cands.push_back({24, 8, 0, 0});
   } else {
     // z-blocks of the full depth, of fixed lengths, and of the depth split evenly into 2 to 8
     // (no short last block)
@@ -1478,8 +1473,6 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
     Tiling& T = dir == 0 ? P->fw : P->rv;
     const int bit = dir == 0 ? AWE_FUSE_FORWARD : AWE_FUSE_ADJOINT;
     for (const Cand& c : cands) {
-      // a checkpointed gradient recomputes one level per launch; its reversals run in pairs
-      if (c.fuse && dir == 0 && P->store.mode == AWE_STORE_CHECKPOINT) continue;
       T.tz = c.tz;
       T.ty = c.ty;
       T.bz = c.bz;
@@ -1508,20 +1501,22 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
         fa.probe_r = aa.probe_r = P->store.nslots;
         fa.probe_pitch = aa.probe_pitch = 0;
       }
-      if (hipError_t e = hipEventRecord(e0, s)) return fail_out(hip_fail(e, "autotune event"));
       // the last levels of the sweep, where every shot of an end-aligned batch is active (the
-      // first levels of uneven batches cover only the longest shots)
-      if (dir == 0) {
-        const bool f2 = fused_ok(P, AWE_FUSE_FORWARD);
-        const int k1 = P->ndim == 2 && fkind == awe::kStoreF32 ? awe::kStoreF32R : fkind;  // as forward_loop
-        for (int n = std::max(1, P->nsteps - probe + 1); n + (f2 ? 1 : 0) <= P->nsteps; n += f2 ? 2 : 1)
-          if ((st = f2 ? step_fwd2(P, fa, n, fkind, s) : step_fwd(P, fa, n, k1, s)) != AWE_OK)
-            return fail_out(st);
-      } else {
-        const bool a2 = fused_ok(P, AWE_FUSE_ADJOINT);
-        for (int n = P->nsteps; n > P->nsteps - probe && n >= 2; n -= a2 ? 2 : 1)
-          if ((st = a2 ? step_adj2(P, aa, n, s) : step_adj(P, aa, n, s)) != AWE_OK) return fail_out(st);
-      }
+      // first levels of uneven batches cover only the longest shots); the first launch runs once
+      // untimed, or the candidate tried first would be timed with its first launch's set-up (3D bricks, the
+      // first, then lost to slower marches now and then)
+      const bool two = fused_ok(P, dir == 0 ? AWE_FUSE_FORWARD : AWE_FUSE_ADJOINT);
+      const int k1 = P->ndim == 2 && fkind == awe::kStoreF32 ? awe::kStoreF32R : fkind;  // as forward_loop
+      const int n0 = dir == 0 ? std::max(1, P->nsteps - probe + 1) : P->nsteps;
+      auto in_probe = [&](int n) { return dir == 0 ? n + two <= P->nsteps : n > P->nsteps - probe && n >= 2; };
+      auto step = [&](int n) {
+        return dir == 0 ? (two ? step_fwd2(P, fa, n, fkind, s) : step_fwd(P, fa, n, k1, s))
+                        : (two ? step_adj2(P, aa, n, s) : step_adj(P, aa, n, s));
+      };
+      if (in_probe(n0) && (st = step(n0)) != AWE_OK) return fail_out(st);
+      if (hipError_t e = hipEventRecord(e0, s)) return fail_out(hip_fail(e, "autotune event"));
+      for (int n = n0; in_probe(n); n += dir == 0 ? 1 + two : -1 - two)
+        if ((st = step(n)) != AWE_OK) return fail_out(st);
       if (hipError_t e = hipEventRecord(e1, s)) return fail_out(hip_fail(e, "autotune event"));
       if (hipError_t e = hipEventSynchronize(e1)) return fail_out(hip_fail(e, "autotune event"));
       float ms = 0.f;

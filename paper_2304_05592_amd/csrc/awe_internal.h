@@ -42,8 +42,10 @@ enum ImageSrc : int { kImgNone = 0, kImgFull32 = 1, kImgBuffers = 2, kImgFullBF1
 // kStoreF32R (2D one-level steps of a sweep without two-level launches): FP32 copy as kStoreF32,
 // but the step reads its two previous levels back from the store instead of the rotating
 // buffers, which then receive only the last level.
+// kStoreSlot (2D two-level steps; launchers pick it by st_slot): no levels kept, but the state reached is
+// written into a checkpoint slot.
 enum StoreKind : int { kStoreNone = 0, kStoreF32 = 1, kStoreBF16 = 2, kStoreFP16 = 3, kStoreProbe = 4,
-                       kStoreF32R = 5 };
+                       kStoreF32R = 5, kStoreSlot = 6 };
 
 // Probed gradient: at most this many probes; a shot's sums are 2 r FP64 values per point at
 // ShotDev::store, B (forward second differences) first, then A (adjoint levels), each in the
@@ -141,7 +143,7 @@ struct StepArgs {
   int rs_slot;               //   (kNoLevel: none); see fwd_level
   int single;                // two-level kernels: produce level `step` alone
   int stream;                // 3D bricks: a step's fields exceed the last-level cache
-  int st_slot;               // 2D forward: also write (u^k, u^{k-1}) into this FP32 slot (-1: no)
+  int st_slot;               // 2D forward: also write the last level and the one before it into this FP32 slot (-1: no)
   int nbl;
   int store_prec;            // Prec of the kept wavefield (FULL store / checkpoint slots)
   int image_src;             // adjoint imaging source, see ImageSrc

@@ -138,3 +138,14 @@ def test_two_level_wide_tiles_on_the_cpu_build(emu_lib):
     res = json.loads(r.stdout.strip().splitlines()[-1])
     print(res)
     assert all(res["bitwise"]) and all(res["nonzero"])
+
+
+def test_two_level_checkpoint_advances_on_the_cpu_build(emu_lib):
+    """Checkpointed 2D gradients whose advances run two levels per launch, under AddressSanitizer with the
+    host launch checks on: bitwise the one-level results."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_ckpt_advances.py")], emu_lib, timeout=900)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    print(res)
+    assert res["nonzero"] and all(res["bitwise"].values())

@@ -463,3 +463,24 @@ def test_two_level_16bit_store_is_bitwise_the_one_level_path(prec, widths, T):
     for a, b in zip(*outs):
         assert torch.equal(a, b) and torch.isfinite(a).all()
     assert max(T) < 10.0 or outs[0][0].abs().max() > 0
+
+
+@pytest.mark.parametrize("many", [False, True], ids=["narrow", "wide"])
+@pytest.mark.parametrize("slots,prec", [(1, A.PREC_FP32), (2, A.PREC_FP32), (5, A.PREC_FP32), (3, A.PREC_BF16)])
+def test_two_level_checkpoint_advances_are_bitwise_the_one_level_path(slots, prec, many):
+    """The advances of a checkpointed gradient run two levels per launch (from a slot read by reference, into
+    a fused slot store, one level where a count is odd): on an uneven batch with per-shot nt the gradient,
+    F^T dd and traces are bitwise those of one level per launch."""
+    widths, T = ([118] * 60 + [117] * 60, [30.0, 23.0]) if many else ([90, 70, 113, 64], [300.0, 90.0, 200.0, 145.0])
+    wl = W.small_2d(nz=31, nbl=5, windows=widths, T_per_shot=[T[i % len(T)] for i in range(len(widths))], nrec=29)
+    dds = _residuals(wl)
+    outs = []
+    for fuse in (A.FUSE_NONE, A.FUSE_FORWARD, A.FUSE_BOTH):
+        plan = make_plan(wl, storage=A.Storage(A.STORE_CHECKPOINT, slots, prec))
+        plan.set_fusion(fuse)
+        m, q = gpu_inputs(wl, plan)
+        outs.append([t.cpu() for t in plan.gradient(m, q, plan.pack(dds, "d"), v=True, d=True)])
+        _sync()
+    for got in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(outs[0], got))
+    assert all(torch.isfinite(a).all() and a.abs().max() > 0 for a in outs[0])
