@@ -15,13 +15,19 @@ import torch.nn.functional as F
 from .binding import STORE_NONE, Plan
 
 
+def _f32(t: torch.Tensor) -> torch.Tensor:
+    """t as a contiguous float32 tensor outside the graph; t itself, detached, where it is one already."""
+    t = t.detach()
+    return t if t.dtype is torch.float32 and t.is_contiguous() else t.to(torch.float32).contiguous()
+
+
 class WaveOp(torch.autograd.Function):
     """d = F(m) q on a Plan; m and q are packed float32 CUDA tensors (see Plan)."""
 
     @staticmethod
     def forward(ctx, m: torch.Tensor, q: torch.Tensor, plan: Plan):
-        mf = m.detach().to(torch.float32).contiguous()
-        qf = q.detach().to(torch.float32).contiguous()
+        mf = _f32(m)
+        qf = _f32(q)
         keep = bool(ctx.needs_input_grad[0]) and plan.storage.mode != STORE_NONE
         ws = plan.workspace(mf.device)
         d = plan.forward(mf, qf, keep=keep, ws=ws)
@@ -34,7 +40,7 @@ class WaveOp(torch.autograd.Function):
     def backward(ctx, dy: torch.Tensor):
         mf, qf = ctx.saved_tensors
         plan = ctx.plan
-        dyf = dy.detach().to(torch.float32).contiguous()
+        dyf = _f32(dy)
         gm = gq = None
         if ctx.needs_input_grad[0]:
             if not ctx.kept:
@@ -60,10 +66,9 @@ class BornOp(torch.autograd.Function):
     def forward(ctx, dm: torch.Tensor, m: torch.Tensor, q: torch.Tensor, plan: Plan):
         if m.requires_grad or q.requires_grad:
             raise NotImplementedError("born_forward differentiates in dm only (m and q are the background)")
-        f32 = lambda t: t.detach().to(torch.float32).contiguous()
-        mf, qf = f32(m), f32(q)
+        mf, qf = _f32(m), _f32(q)
         ws = plan.workspace(mf.device)
-        dd = plan.born(mf, qf, f32(dm), ws=ws)
+        dd = plan.born(mf, qf, _f32(dm), ws=ws)
         ctx.plan, ctx.ws, ctx.dm_dtype = plan, ws, dm.dtype
         ctx.save_for_backward(mf, qf)
         return dd
@@ -73,7 +78,7 @@ class BornOp(torch.autograd.Function):
         mf, qf = ctx.saved_tensors
         if ctx.plan.storage.mode == STORE_NONE:
             raise RuntimeError("the pullback of born_forward needs a plan with FULL or CHECKPOINT storage")
-        g, _, _ = ctx.plan.gradient(mf, qf, dy.detach().to(torch.float32).contiguous(), ws=ctx.ws)
+        g, _, _ = ctx.plan.gradient(mf, qf, _f32(dy), ws=ctx.ws)
         ctx.ws = None
         return g.to(ctx.dm_dtype), None, None, None
 
@@ -107,7 +112,7 @@ class Slowness2(torch.autograd.Function):
     @staticmethod
     def forward(ctx, v: torch.Tensor):
         from .binding import slowness2
-        vf = v.detach().to(torch.float32).contiguous()
+        vf = _f32(v)
         ctx.save_for_backward(vf)
         ctx.v_dtype = v.dtype
         return slowness2(vf)
@@ -116,7 +121,7 @@ class Slowness2(torch.autograd.Function):
     def backward(ctx, gm: torch.Tensor):
         from .binding import velocity_gradient
         (vf,) = ctx.saved_tensors
-        return velocity_gradient(vf, gm.detach().to(torch.float32).contiguous()).to(ctx.v_dtype)
+        return velocity_gradient(vf, _f32(gm)).to(ctx.v_dtype)
 
 
 def slowness2_from_velocity(v: torch.Tensor) -> torch.Tensor:
@@ -134,8 +139,7 @@ class Patchy(torch.autograd.Function):
         from .binding import patchy
         if any(t.requires_grad for t in (vp, rho, phi)):
             raise NotImplementedError("patchy_rock_physics differentiates in the saturation only")
-        f32 = lambda t: t.detach().to(torch.float32).contiguous()
-        args = tuple(f32(t) for t in (sw, vp, rho, phi))
+        args = tuple(_f32(t) for t in (sw, vp, rho, phi))
         ctx.save_for_backward(*args)
         ctx.consts, ctx.sw_dtype = consts, sw.dtype
         return patchy(*args, consts=consts)
@@ -144,9 +148,8 @@ class Patchy(torch.autograd.Function):
     def backward(ctx, g_vp, g_rho):
         from .binding import patchy_vjp
         sw, vp, rho, phi = ctx.saved_tensors
-        f32 = lambda t: None if t is None else t.detach().to(torch.float32).contiguous()
-        g_vp = torch.zeros_like(vp) if g_vp is None else f32(g_vp)
-        g_sw = patchy_vjp(sw, vp, rho, phi, g_vp, f32(g_rho), consts=ctx.consts)
+        g_vp = torch.zeros_like(vp) if g_vp is None else _f32(g_vp)
+        g_sw = patchy_vjp(sw, vp, rho, phi, g_vp, None if g_rho is None else _f32(g_rho), consts=ctx.consts)
         return g_sw.to(ctx.sw_dtype), None, None, None, None
 
 

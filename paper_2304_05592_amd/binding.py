@@ -198,13 +198,18 @@ class Layout:
 
 
 def _stream_ptr(stream):
+    """The stream's handle (None: the current stream of the current device).  torch.cuda.current_stream()
+    builds a Stream object around that handle, 10 us a call, which a short call is bound by."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def describe(ndim, h, dt, nbl, vmax, windows, shots, damp_vref=None, damp_R=1e-3):
