@@ -93,7 +93,8 @@ struct awe_plan {
   bool auto_rows[2] = {true, true};  // tile rows (2D) / column blocks (3D): forward, adjoint
   bool auto_fuse = true;
   Tiling fw, rv;          // launch shapes of forward solves / adjoint steps
-  Tiling fw2, rv2;        // their tables for the two-level kernels, whose tiles are wider (rows: fw.tz, rv.tz)
+  Tiling fw2, rv2;        // their tables for the two-level kernels, whose tiles may be wider (rows: fw.tz, rv.tz)
+  Tiling bn2;             // two-level Born modelling, where fw2's tiles are 128 columns wide
   std::vector<awe_shot> shots;
   std::vector<double> rec_pos;    // copy of the problem's receiver rows
   std::vector<ShotDev> sd;
@@ -238,8 +239,8 @@ awe_status build_groups(awe_plan* P) {
 }
 
 // Tiles of every shot (in shot order) for the launch shape of T, the groups' tile ranges, and
-// the per-tile receiver gather lists and injection CSR.
-awe_status build_tiling(awe_plan* P, Tiling& T) {
+// the per-tile receiver gather lists and, for adjoint tilings (inject), injection CSR.
+awe_status build_tiling(awe_plan* P, Tiling& T, bool inject) {
   const int nd = P->ndim;
   const std::vector<int>& order = P->order;
   T.tiles.clear();
@@ -307,7 +308,7 @@ awe_status build_tiling(awe_plan* P, Tiling& T) {
       R.k = I.base[2];
       for (int c = 0; c < 8; ++c) R.w[c] = (float)I.w[c];
       rt.push_back({tile_of(s, R.i, R.j, R.k), R});
-      const int nc = nd == 2 ? 4 : 8;
+      const int nc = !inject ? 0 : nd == 2 ? 4 : 8;
       for (int c = 0; c < nc; ++c) {
         if (I.w[c] == 0.0) continue;
         int dx, dy, dz;
@@ -515,6 +516,17 @@ void default_shapes(awe_plan* P) {
                : n64 < 200 ? 8 : n64 < 800 ? 24 : 32;
 }
 
+// Tables of a tiling built and uploaded where calls use it, given back where none does.
+awe_status refresh(awe_plan* P, Tiling& T, bool used, bool inject) {
+  if (used) {
+    const awe_status st = build_tiling(P, T, inject);
+    return st != AWE_OK ? st : upload_tiling(P, T);
+  }
+  if (T.dev) (void)hipFree(T.dev);
+  T.dev = nullptr;
+  return AWE_OK;
+}
+
 // Shot groups and the tilings of the directions in `dirs` (bit 0 forward, bit 1 adjoint; the
 // groups change both, so a change of groups rebuilds both), built and uploaded: those of the kernels
 // the direction's calls can launch.
@@ -529,14 +541,15 @@ awe_status rebuild(awe_plan* P, int dirs) {
     two.tx = wide_tiles(P, bit) ? 128 : 64;
     two.tz = one.tz;
     const bool fused = fused_ok(P, bit);
-    for (Tiling* T : {&one, &two}) {
-      if ((T == &two) == fused) {
-        if ((st = build_tiling(P, *T)) != AWE_OK) return st;
-        if ((st = upload_tiling(P, *T)) != AWE_OK) return st;
-      } else if (T->dev) {
-        (void)hipFree(T->dev);
-        T->dev = nullptr;
-      }
+    for (Tiling* T : {&one, &two})
+      if ((st = refresh(P, *T, (T == &two) == fused, bit == AWE_FUSE_ADJOINT)) != AWE_OK) return st;
+    // Born launches hold two fields, and 128-column tiles of both cost more in occupancy than they save:
+    // 16 shots of 730 x 421 43.1 us per launch 128 wide at 24 rows, 39.5 64 wide at 32; 16 of 1104 x 592 108
+    // and 103 at 24 and 32 rows; 4 of 730 x 421 (n64 = 864) 15.8 and 15.9.
+    if (bit == AWE_FUSE_FORWARD) {
+      P->bn2.tx = 64;
+      P->bn2.tz = !P->auto_rows[0] ? one.tz : tiles24(P, 64) < 1750 ? 24 : 32;
+      if ((st = refresh(P, P->bn2, fused && two.tx != 64, false)) != AWE_OK) return st;
     }
   }
   return AWE_OK;
@@ -1381,7 +1394,7 @@ awe_status awe_plan_workspace_size(const awe_plan* plan, size_t* bytes) {
 void awe_plan_destroy(awe_plan* plan) {
   if (!plan) return;
   for (hipEvent_t e : plan->prof_ev) (void)hipEventDestroy(e);
-  for (const Tiling* T : {&plan->fw, &plan->rv, &plan->fw2, &plan->rv2})
+  for (const Tiling* T : {&plan->fw, &plan->rv, &plan->fw2, &plan->rv2, &plan->bn2})
     if (T->dev) (void)hipFree(T->dev);
   if (plan->chk_dev) (void)hipFree(plan->chk_dev);
   delete plan;
@@ -1883,7 +1896,7 @@ awe_status awe_born(awe_plan* P, const float* m, const float* q, const float* dm
     ProfRun run(P, s, 2);
     for (int n = 1; n <= P->nsteps;) {
       const bool two = fuse && (n > 1 || !(P->nsteps & 1));
-      const Tiling& T = fuse ? P->fw2 : P->fw;
+      const Tiling& T = !fuse ? P->fw : P->bn2.dev ? P->bn2 : P->fw2;
       set_group(P, T, a, two ? n + 1 : n);
       a.step = n;
       a.single = !two;
@@ -1891,7 +1904,7 @@ awe_status awe_born(awe_plan* P, const float* m, const float* q, const float* dm
         if ((st = check_step(P, T, a, n, two ? n + 1 : n, "Born step")) != AWE_OK) return st;
         ProfScope ps(P, 2, s);
         if (P->ndim == 3) AWE_HIP(awe::launch_born3d(a, T.ty, T.bz, s));
-        else if (fuse) AWE_HIP(awe::launch_born2d2(a, T.tx, T.tz, s));
+        else if (fuse) AWE_HIP(awe::launch_born2d2(a, T.tz, s));
         else AWE_HIP(awe::launch_born2d(a, T.tz, s));
       }
       n += two ? 2 : 1;

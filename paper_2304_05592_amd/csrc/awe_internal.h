@@ -218,8 +218,8 @@ hipError_t launch_adj2d(const StepArgs& a, int tz, hipStream_t stream);
 hipError_t launch_fwd2d2(const StepArgs& a, int tx, int tz, int store, hipStream_t stream);
 hipError_t launch_adj2d2(const StepArgs& a, int tx, int tz, hipStream_t stream);
 hipError_t launch_born2d(const StepArgs& a, int tz, hipStream_t stream);
-// Two Born steps per launch (levels step, step+1); tz 8, 16, 24 or 32.
-hipError_t launch_born2d2(const StepArgs& a, int tx, int tz, hipStream_t stream);
+// Two Born steps per launch (levels step, step+1) on 64-column tiles; tz 8, 16, 24 or 32.
+hipError_t launch_born2d2(const StepArgs& a, int tz, hipStream_t stream);
 // 3D steps on 64 x ty columns and z-blocks of bz planes; bricks3d shapes run the brick kernels, whose
 // adjoint step injects the residual itself (no launch_inj3d).
 bool bricks3d(int ty, int bz);
