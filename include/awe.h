@@ -351,8 +351,9 @@ awe_status awe_plan_set_tiles(awe_plan* plan, int32_t tz, int32_t ty, int32_t bz
 
 /* 2D only: advance two time levels per launch, chosen per direction by the bits of mode:
  * AWE_FUSE_FORWARD for forward solves and Born modelling, AWE_FUSE_ADJOINT for reverse sweeps (0:
- * one level per launch everywhere).  Until this call or the autotuner sets it, a plan uses both, and
- * its tile rows follow the size of the work.  The two-level kernels serve every storage: forward solves
+ * one level per launch everywhere).  Until this call or the autotuner sets it, a plan uses both, its
+ * tile rows follow the size of the work, and forward solves of small surveys (without storage or with FULL
+ * FP32 storage) advance three levels per launch.  The two-level kernels serve every storage: forward solves
  * (a checkpoint advance of an odd number of levels begins with one level), Born modelling, reverse sweeps
  * and the paired reversals of a CHECKPOINT gradient.
  * Results are bitwise identical either way (a two-level launch adds both levels' terms to an

@@ -798,10 +798,35 @@ awe_status step_adj2(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s, bool s
   return AWE_OK;
 }
 
+// Does a forward solve take kManyLevels levels per launch?  Default shapes only, while their tiles are 64
+// columns and at most 24 rows: launches of few tiles, bound by their fixed cost.  us per level at two and
+// three levels per launch, with FP32 store: one shot of 281 x 181 2.04 and 1.84; of 730 x 421 2.77 and 2.53;
+// two of those (n64 = 432) 3.53 and 3.26; from n64 = 500 on the rows are 32 and the halo work, a third more
+// than at two levels, fills the chip.
+bool many_levels(const awe_plan* P, int store) {
+  return P->auto_fuse && P->auto_rows[0] && fused_ok(P, AWE_FUSE_FORWARD) && P->fw2.tx == 64 && P->fw2.tz < 32 &&
+         (store == awe::kStoreNone || store == awe::kStoreF32);
+}
+
 // Forward levels 1..nsteps: one single step first when the count is odd, then pairs.
 awe_status forward_loop(awe_plan* P, awe::StepArgs& a, int store, hipStream_t s) {
   awe_status st;
   const bool fuse = fused_ok(P, AWE_FUSE_FORWARD);
+  if (many_levels(P, store)) {
+    ProfRun run(P, s, 0);
+    constexpr int T = awe::kManyLevels;
+    for (int m = (P->nsteps + T - 1) / T; m-- > 0;) {   // launches after this one
+      const int last = P->nsteps - T * m;
+      set_group(P, P->fw2, a, last);
+      a.step = last - T + 1;
+      a.flip = 2 * (m & 1);
+      if (a.ntiles <= 0) continue;
+      if ((st = check_step(P, P->fw2, a, std::max(1, a.step), last, "many-level forward step")) != AWE_OK) return st;
+      ProfScope ps(P, 0, s, last - std::max(1, a.step) + 1);
+      AWE_HIP(awe::launch_fwd2dm(a, P->fw2.tz, store, s));
+    }
+    return AWE_OK;
+  }
   // a 2D FP32 sweep of one-level steps reads its previous levels back from the store
   if (!fuse && P->ndim == 2 && store == awe::kStoreF32) store = awe::kStoreF32R;
   ProfRun run(P, s, 0);

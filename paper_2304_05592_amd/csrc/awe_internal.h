@@ -142,6 +142,7 @@ struct StepArgs {
   int rs_level;              // global state restored by reference from FP32 slot rs_slot
   int rs_slot;               //   (kNoLevel: none); see fwd_level
   int single;                // two-level kernels: produce level `step` alone
+  int flip;                  // many-level forward kernel: 2 where it writes the other two buffers, else 0
   int stream;                // 3D bricks: a step's fields exceed the last-level cache
   int st_slot;               // 2D forward: also write the last level and the one before it into this FP32 slot (-1: no)
   int nbl;
@@ -216,6 +217,10 @@ hipError_t launch_adj2d(const StepArgs& a, int tz, hipStream_t stream);
 // Two 2D steps per launch (levels step, step+1 forward; step, step-1 adjoint); tz 8, 16, 24 or 32,
 // on tiles of tx columns (64, one column per lane, or 128, two).
 hipError_t launch_fwd2d2(const StepArgs& a, int tx, int tz, int store, hipStream_t stream);
+// kManyLevels forward levels step, ... per launch on 64-column tiles (see StepArgs::flip); tz 8, 16 or 24;
+// stores kStoreNone and kStoreF32.
+constexpr int kManyLevels = 3;
+hipError_t launch_fwd2dm(const StepArgs& a, int tz, int store, hipStream_t stream);
 hipError_t launch_adj2d2(const StepArgs& a, int tx, int tz, hipStream_t stream);
 hipError_t launch_born2d(const StepArgs& a, int tz, hipStream_t stream);
 // Two Born steps per launch (levels step, step+1) on 64-column tiles; tz 8, 16, 24 or 32.

@@ -946,6 +946,152 @@ __global__ __launch_bounds__((F2<TZ, V>::NT)) void fwd2d2_kernel(StepArgs a) {
   }
 }
 
+// ------------------------------------------------------------------------------ T forward steps per launch
+// A launch of few tiles is bound by the launch itself (1.8 us) and by the chain of one tile, so small
+// forward solves take T levels per launch: level i of the launch is computed on the tile plus 4 (T - i)
+// cells, one LDS array per level, each point with the arithmetic of the one-level kernel in the same order
+// (so the results are bitwise the same).  Rows of a region split evenly over the eight waves; the columns
+// beside the tile go to all threads, a point each.  Three levels beat four: us per level at two, three, four
+// levels per launch, without a store, one shot of 281 x 181 2.11, 1.76, 1.75; of 480 x 280 2.39, 2.07, 2.20;
+// of 730 x 421 2.66, 2.37, 2.36; two of 730 x 421 3.37, 3.11, 3.22; the added halo takes the rest.
+template <int TZ, int T>
+struct FM {
+  static constexpr int NW = 8, NT = 64 * NW;
+  static constexpr int halo(int i) { return kHalo * (T - i); }
+  static constexpr int W(int i) { return kTX + 2 * halo(i); }
+  static constexpr int H(int i) { return TZ + 2 * halo(i); }
+  static constexpr int off(int i) { return i == 0 ? 0 : off(i - 1) + W(i - 1) * H(i - 1); }   // LDS floats below
+  static constexpr int rows(int i) { return H(i) / NW; }                                      // of a wave
+  static constexpr int cells(int i) { return 2 * halo(i) * H(i); }                            // beside the tile
+  static constexpr int per(int i) { return (cells(i) + NT - 1) / NT; }                        // of a thread
+  static_assert(TZ % NW == 0 && 2 * kHalo % NW == 0, "rows must split evenly over the waves");
+  // row and column of cell e of region i
+  static __device__ __forceinline__ void cell(int i, int e, int* r, int* c) {
+    const int n = 2 * halo(i);
+    *r = e / n;
+    const int k = e - *r * n;
+    *c = k < halo(i) ? k : kTX + k;
+  }
+};
+
+// Levels k .. k + T - 1 (k = step - off; levels below 1 are zero), the last of them T m levels below the
+// sweep's last.  Only the last two go to the rotating buffers: those of the sweep's last two levels, or the
+// other two when m is odd (flip = 2), so that no launch writes a buffer it reads.
+// SK = kStoreNone or kStoreF32.
+template <int TZ, int T, int SK>
+__global__ __launch_bounds__((FM<TZ, T>::NT)) void fwd2dm_kernel(StepArgs a) {
+  using G = FM<TZ, T>;
+  __shared__ float L[G::off(T)];
+  const int tid = xcd_tile(blockIdx.x, a.ntiles);
+  const TileDev Tl = a.t.tiles[a.tile_base + tid];
+  const ShotDev& S = a.t.shots[Tl.shot];
+  const int k = a.step - S.off;
+  if (k + T - 1 < 1) return;
+  const int nx = S.nx, nz = S.nz, px = S.px;
+  const int row4 = 4 * px;
+  const int b = S.nt - 1 + a.flip;
+  const Planes u1 = planes(fbuf(a.ws, S, fwd_buf(b + 2)), nz, k >= 2 ? nz : 0, row4);
+  const Planes u2 = planes(fbuf(a.ws, S, fwd_buf(b + 1)), nz, k >= 3 ? nz : 0, row4);
+  const Planes cf = planes(a.ws + S.coef, nz, nz, row4);
+  const brsrc ro = make_rsrc(fbuf(a.ws, S, fwd_buf(b)), nz * row4);
+  const brsrc rp = make_rsrc(fbuf(a.ws, S, fwd_buf(b - 1)), nz * row4);
+  const long long npts = S.npts;
+  float* st = reinterpret_cast<float*>(a.ws + S.store);
+  const int lane = threadIdx.x & 63, wv = wave_id();
+  const int x = Tl.x0 + lane;
+  const int cx = x < nx ? 4 * x : kOOB;
+
+  float v0[G::rows(0)], s0[G::per(0)];
+#pragma unroll
+  for (int n = 0; n < G::rows(0); ++n) v0[n] = ldp(u1, cx, Tl.z0 - G::halo(0) + wv + n * G::NW);
+  auto cell_off = [&](int i, int n) {
+    int r, c;
+    G::cell(i, min((int)threadIdx.x + n * G::NT, G::cells(i) - 1), &r, &c);
+    return col_off(Tl.x0 - G::halo(i) + c, Tl.z0 - G::halo(i) + r, nx, nz, px, 4);
+  };
+#pragma unroll
+  for (int n = 0; n < G::per(0); ++n) s0[n] = ldp_at(u1, cell_off(0, n));
+  // level k-2 of the first region, and coef of every region
+  float um2[G::rows(1)], sm2[G::per(1)], pc[T + 1][G::rows(1)], sc[T + 1][G::per(1)];
+#pragma unroll
+  for (int n = 0; n < G::rows(1); ++n) um2[n] = ldp(u2, cx, Tl.z0 - G::halo(1) + wv * G::rows(1) + n);
+#pragma unroll
+  for (int n = 0; n < G::per(1); ++n) sm2[n] = ldp_at(u2, cell_off(1, n));
+#pragma unroll
+  for (int i = 1; i <= T; ++i) {
+#pragma unroll
+    for (int n = 0; n < G::rows(i); ++n) pc[i][n] = ldp(cf, cx, Tl.z0 - G::halo(i) + wv * G::rows(i) + n);
+#pragma unroll
+    for (int n = 0; n < G::per(i); ++n) sc[i][n] = ldp_at(cf, cell_off(i, n));
+  }
+#pragma unroll
+  for (int n = 0; n < G::rows(0); ++n) L[(wv + n * G::NW) * G::W(0) + G::halo(0) + lane] = v0[n];
+#pragma unroll
+  for (int n = 0; n < G::per(0); ++n) {   // threads past the last cell write it again
+    int r, c;
+    G::cell(0, min((int)threadIdx.x + n * G::NT, G::cells(0) - 1), &r, &c);
+    L[r * G::W(0) + c] = s0[n];
+  }
+  __syncthreads();
+
+  const Source src(S);
+  const Damp<1> damp(x, nx, a.nbl);
+  auto level = [&](auto I) __attribute__((always_inline)) {
+    constexpr int i = decltype(I)::value, h = G::halo(i), N = G::rows(i), W = G::W(i), W1 = G::W(i - 1);
+    constexpr int W2 = i >= 2 ? G::W(i - 2) : 0, o2 = i >= 2 ? G::off(i - 2) : 0;
+    const int lv = k + i - 1;
+    const bool act = lv >= 1;
+    float* L0 = &L[G::off(i - 1)];
+    if (act && a.d != nullptr)
+      gather<G::NT, W1>(a, Tl, S, reinterpret_cast<const float (*)[W1]>(L0), Tl.z0 - G::halo(i - 1),
+                        Tl.x0 - G::halo(i - 1), lv - 1);
+    const float q = act ? a.q[S.q + lv - 1] : 0.f;
+    const brsrc rs = make_rsrc(st + (long long)(SK == kStoreF32 && act ? lv : 0) * npts,
+                               SK == kStoreF32 && act ? nz * row4 : 0);
+    fv<1> lap[N], u[N];
+    lap_rows<1, N, W1>(L0 + (wv * N + kHalo) * W1 + h + kHalo + lane, lap, u, a.c);
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int r = wv * N + n, z = Tl.z0 - h + r;
+      fv<1> m2, incr, v;
+      if constexpr (i == 1) m2[0] = um2[n];
+      else m2[0] = L[o2 + (r + 2 * kHalo) * W2 + h + 2 * kHalo + lane];
+      if (act) src.add<1>(&lap[n], x, z, q);
+      step_cols<1>(u[n], m2, fv<1>{pc[i][n]}, lap[n], damp, border_dist(z, nz, a.nbl), a.eta_dt, &incr, &v);
+      if (!act) v[0] = 0.f;
+      if constexpr (i < T) L[G::off(i) + r * W + h + lane] = v[0];
+      const int zo = (unsigned)(r - h) < (unsigned)TZ && z < nz ? z * row4 : kZOOB;
+      if (SK == kStoreF32) stb_nt(rs, v[0], cx, zo);
+      if (i == T) stb(ro, v[0], cx, zo);
+      if (i == T - 1) stb(rp, v[0], cx, zo);
+    }
+    if constexpr (i < T) {
+#pragma unroll
+      for (int n = 0; n < G::per(i); ++n) {
+        const int e = (int)threadIdx.x + n * G::NT;
+        if (e < G::cells(i)) {
+          int r, c;
+          G::cell(i, e, &r, &c);
+          const int xs = Tl.x0 - h + c, zs = Tl.z0 - h + r;
+          fv<1> l1[1], u1c[1], m2, incr, v;
+          lap_rows<1, 1, W1>(L0 + (r + kHalo) * W1 + c + kHalo, l1, u1c, a.c);
+          if constexpr (i == 1) m2[0] = sm2[n];
+          else m2[0] = L[o2 + (r + 2 * kHalo) * W2 + c + 2 * kHalo];
+          if (act) src.add<1>(&l1[0], xs, zs, q);
+          step_cols<1>(u1c[0], m2, fv<1>{sc[i][n]}, l1[0], Damp<1>(xs, nx, a.nbl), border_dist(zs, nz, a.nbl),
+                       a.eta_dt, &incr, &v);
+          L[G::off(i) + r * W + c] = act ? v[0] : 0.f;
+        }
+      }
+      __syncthreads();
+    }
+  };
+  level(std::integral_constant<int, 1>{});
+  level(std::integral_constant<int, 2>{});
+  level(std::integral_constant<int, 3>{});
+  static_assert(T == 3, "one call per level");
+}
+
 // Residual injected at the points [begin, begin + count) of a tile's list, into LDS at the points'
 // tile coordinates.
 template <int NT, int W>
@@ -1401,6 +1547,23 @@ hipError_t adj2d2_v(const StepArgs& a, int tz, hipStream_t s) {
 hipError_t launch_fwd2d2(const StepArgs& a, int tx, int tz, int store, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
   return tx == 64 ? fwd2d2_v<1>(a, tz, store, s) : tx == 128 ? fwd2d2_v<2>(a, tz, store, s) : hipErrorInvalidValue;
+}
+
+hipError_t launch_fwd2dm(const StepArgs& a, int tz, int store, hipStream_t s) {
+  if (a.ntiles <= 0) return hipSuccess;
+  auto go = [&](auto TZ) -> hipError_t {
+    constexpr int tz = decltype(TZ)::value;
+    if (store == kStoreNone) fwd2dm_kernel<tz, kManyLevels, kStoreNone><<<a.ntiles, FM<tz, kManyLevels>::NT, 0, s>>>(a);
+    else if (store == kStoreF32) fwd2dm_kernel<tz, kManyLevels, kStoreF32><<<a.ntiles, FM<tz, kManyLevels>::NT, 0, s>>>(a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  };
+  switch (tz) {
+    case 8: return go(std::integral_constant<int, 8>{});
+    case 16: return go(std::integral_constant<int, 16>{});
+    case 24: return go(std::integral_constant<int, 24>{});
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_adj2d2(const StepArgs& a, int tx, int tz, hipStream_t s) {

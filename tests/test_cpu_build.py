@@ -140,6 +140,16 @@ def test_two_level_wide_tiles_on_the_cpu_build(emu_lib):
     assert all(res["bitwise"]) and all(res["nonzero"])
 
 
+def test_many_level_forward_on_the_cpu_build(emu_lib):
+    """Small forward solves of default plans, several levels per launch, under AddressSanitizer with the host
+    launch checks on: bitwise one level per launch."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_many_levels.py")], emu_lib, timeout=900)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    print(res)
+    assert res["nonzero"] and all(res["bitwise"].values())
+
 def test_two_level_checkpoint_advances_on_the_cpu_build(emu_lib):
     """Checkpointed 2D gradients whose advances run two levels per launch, under AddressSanitizer with the
     host launch checks on: bitwise the one-level results."""

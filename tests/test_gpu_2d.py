@@ -484,3 +484,27 @@ def test_two_level_checkpoint_advances_are_bitwise_the_one_level_path(slots, pre
     for got in outs[1:]:
         assert all(torch.equal(a, b) for a, b in zip(outs[0], got))
     assert all(torch.isfinite(a).all() and a.abs().max() > 0 for a in outs[0])
+
+
+@pytest.mark.parametrize("widths,nz", [([53, 54, 55], 31), ([117, 64], 14), ([118] * 25, 31), ([54, 246] * 20, 38),
+                                       ([118] * 60, 45)],
+                         ids=["rows8", "one_row_of_tiles", "rows16", "rows24", "two_levels"])
+@pytest.mark.parametrize("T", [[1.0], [30.0], [31.0], [32.0], [30.0, 2.0, 23.0, 25.0]], ids=str)
+def test_small_forward_solves_are_bitwise_the_one_level_path(widths, nz, T):
+    """Default plans of small surveys advance several levels per launch, over every remainder of the step
+    count, shots that start inside a launch and each tile height: traces without a store, traces, gradient and
+    F^T dd from a FULL FP32 store are bitwise those of one level per launch."""
+    wl = W.small_2d(nz=nz, nbl=5, windows=widths, T_per_shot=[T[i % len(T)] for i in range(len(widths))], nrec=29)
+    dds = _residuals(wl)
+    outs = []
+    for fuse in (None, A.FUSE_NONE):
+        plan = make_plan(wl, storage=A.Storage(A.STORE_FULL))
+        if fuse is not None:
+            plan.set_fusion(fuse)
+        m, q = gpu_inputs(wl, plan)
+        o = plan.gradient(m, q, plan.pack(dds, "d"), v=True, d=True) + (plan.forward(m, q),)
+        _sync()
+        outs.append([t.cpu() for t in o])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b) and torch.isfinite(a).all()
+    assert max(T) < 10.0 or outs[0][3].abs().max() > 0
