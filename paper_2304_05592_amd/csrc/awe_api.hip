@@ -783,7 +783,7 @@ awe_status step_fwd2(awe_plan* P, awe::StepArgs& a, int n, int store, hipStream_
   if (a.ntiles <= 0) return AWE_OK;
   if (awe_status st = check_step(P, P->fw2, a, n, last, "two-level forward step")) return st;
   ProfScope ps(P, 0, s, single ? 1 : 2);
-  if (store == awe::kStoreNone && a.st_slot >= 0) store = awe::kStoreSlot;
+  if (store == awe::kStoreNone && (a.st_slot >= 0 || a.rs_level >= n - 2)) store = awe::kStoreSlot;
   AWE_HIP(awe::launch_fwd2d2(a, P->fw2.tx, P->fw2.tz, store, s));
   return AWE_OK;
 }

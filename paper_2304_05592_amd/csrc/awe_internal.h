@@ -42,8 +42,8 @@ enum ImageSrc : int { kImgNone = 0, kImgFull32 = 1, kImgBuffers = 2, kImgFullBF1
 // kStoreF32R (2D one-level steps of a sweep without two-level launches): FP32 copy as kStoreF32,
 // but the step reads its two previous levels back from the store instead of the rotating
 // buffers, which then receive only the last level.
-// kStoreSlot (2D two-level steps; launchers pick it by st_slot): no levels kept, but the state reached is
-// written into a checkpoint slot.
+// kStoreSlot (2D two-level steps): no levels kept, but the state may be read from a checkpoint slot by
+// reference and the state reached written into one (st_slot).
 enum StoreKind : int { kStoreNone = 0, kStoreF32 = 1, kStoreBF16 = 2, kStoreFP16 = 3, kStoreProbe = 4,
                        kStoreF32R = 5, kStoreSlot = 6 };
 

@@ -785,7 +785,7 @@ __device__ __forceinline__ void gather(const StepArgs& a, const TileDev& T, cons
 
 // Forward: levels k and k+1 (k = step - off); SK = kStoreNone, kStoreF32, kStoreBF16 / kStoreFP16 or
 // kStoreProbe (both levels' increments added to the probe sums in one FP64 read-modify-write, level k
-// first), or kStoreSlot (the state reached goes into a checkpoint slot).  A 16-bit store takes the levels k-2 and k-1, whose scales the launch before finished, from the
+// first), or kStoreSlot (a checkpoint advance: reads a slot by reference, the state reached may go into one).  A 16-bit store takes the levels k-2 and k-1, whose scales the launch before finished, from the
 // values the first step has in registers, and this launch's maxima go to the levels' slots: the gradient of
 // 3 shots of 261 x 185 (501 samples) 4.94 -> 3.27 ms against one level per launch.
 // a.single: level k alone.
@@ -808,11 +808,11 @@ __global__ __launch_bounds__((F2<TZ, V>::NT)) void fwd2d2_kernel(StepArgs a) {
   if (!act1 && !act2) return;
   const int nx = S.nx, nz = S.nz, px = S.px;
   const int row4 = 4 * px;
-  // levels below 1 are zero (see fwd2d_kernel); the advances of a checkpointed gradient may follow a restore
-  // by reference
-  constexpr bool SLOT = SK == kStoreSlot, REF = SLOT || SK == kStoreNone;
-  const Planes u1 = planes(REF ? fwd_level(a, S, k - 1) : fbuf(a.ws, S, fwd_buf(k - 1)), nz, k >= 2 ? nz : 0, row4);
-  const Planes u2 = planes(REF ? fwd_level(a, S, k - 2) : fbuf(a.ws, S, fwd_buf(k - 2)), nz, k >= 3 ? nz : 0, row4);
+  // levels below 1 are zero (see fwd2d_kernel); kStoreSlot may follow a restore by reference, whose look-up
+  // the other kinds are spared (it delays the tile's loads)
+  constexpr bool SLOT = SK == kStoreSlot;
+  const Planes u1 = planes(SLOT ? fwd_level(a, S, k - 1) : fbuf(a.ws, S, fwd_buf(k - 1)), nz, k >= 2 ? nz : 0, row4);
+  const Planes u2 = planes(SLOT ? fwd_level(a, S, k - 2) : fbuf(a.ws, S, fwd_buf(k - 2)), nz, k >= 3 ? nz : 0, row4);
   const Planes cf = planes(a.ws + S.coef, nz, nz, row4);
   const long long npts = S.npts;
   // new levels k and k+1 (a level outside 1..nt-1 belongs to an inactive step: no records)
@@ -824,8 +824,9 @@ __global__ __launch_bounds__((F2<TZ, V>::NT)) void fwd2d2_kernel(StepArgs a) {
   const brsrc rs2 = make_rsrc(st + (long long)(SK == kStoreF32 && act2 ? k + 1 : 0) * npts,
                               SK == kStoreF32 && act2 ? nz * row4 : 0);
   // checkpoint slot: the last level, and the one before it (level k-1 when this launch ends at k)
-  float* sl = st + (long long)(SLOT ? a.st_slot : 0) * 2 * npts;
-  const int slb = SLOT ? nz * row4 : 0;
+  const bool to_slot = SLOT && a.st_slot >= 0;
+  float* sl = st + (long long)(to_slot ? a.st_slot : 0) * 2 * npts;
+  const int slb = to_slot ? nz * row4 : 0;
   const brsrc rsl0 = make_rsrc(sl, a.single ? 0 : slb);
   const brsrc rslv = make_rsrc(a.single ? sl : sl + npts, slb), rslu = make_rsrc(sl + npts, a.single ? slb : 0);
   // 16-bit store: the levels k-1 and k-2
