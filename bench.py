@@ -508,7 +508,7 @@ def bench_c2(args):
                          "point-update, the launch itself moves 44 B per point)" if fa
                          else "adj2d step (adjoint + imaging from stored FP32, 36 B per point-update)")}
     roof = roofline_of(kernels, names)
-    dom_name = (f"adj2d2_kernel<{adjoint_tz(run.tiles)}, 1>" if fa else f"adj2d_kernel<{adjoint_tz(run.tiles)}, 1>") \
+    dom_name = (f"adj2d2_kernel<{adjoint_tz(run.tiles)}, 2, 1>" if fa else f"adj2d_kernel<{adjoint_tz(run.tiles)}, 1>") \
         if run.tiles else None
     roof["traffic"] = traffic_record("c2_grad", "kernels2d.hip", dom_name, run.launch_points)
     roof["traffic_counter"] = TRAFFIC_NOTE
