@@ -799,13 +799,13 @@ awe_status step_adj2(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s, bool s
 }
 
 // Does a forward solve take kManyLevels levels per launch?  Default shapes only, while their tiles are 64
-// columns and at most 24 rows: launches of few tiles, bound by their fixed cost.  us per level at two and
+// columns and at most 24 rows and, as PROBED plans have 8 rows at every size, few: launches of few tiles, bound by their fixed cost.  us per level at two and
 // three levels per launch, with FP32 store: one shot of 281 x 181 2.04 and 1.84; of 730 x 421 2.77 and 2.53;
 // two of those (n64 = 432) 3.53 and 3.26; from n64 = 500 on the rows are 32 and the halo work, a third more
 // than at two levels, fills the chip.
 bool many_levels(const awe_plan* P, int store) {
   return P->auto_fuse && P->auto_rows[0] && fused_ok(P, AWE_FUSE_FORWARD) && P->fw2.tx == 64 && P->fw2.tz < 32 &&
-         (store == awe::kStoreNone || store == awe::kStoreF32);
+         tiles24(P, 64) < 500 && (store == awe::kStoreNone || store == awe::kStoreF32);
 }
 
 // Forward levels 1..nsteps: one single step first when the count is odd, then pairs.
