@@ -357,7 +357,8 @@ awe_status awe_plan_set_tiles(awe_plan* plan, int32_t tz, int32_t ty, int32_t bz
  * (a checkpoint advance of an odd number of levels begins with one level), Born modelling, reverse sweeps
  * and the paired reversals of a CHECKPOINT gradient.
  * Results are bitwise identical either way (a two-level launch adds both levels' terms to an
- * FP64 sum in the order two launches would).  Two levels per launch need tiles of 8, 16, 24 or 32 rows (16 or 32 are set
+ * FP64 sum in the order two launches would), also where the mode changes between a kept forward and its
+ * awe_backward.  Two levels per launch need tiles of 8, 16, 24 or 32 rows (16 or 32 are set
  * otherwise).  Errors: INVALID_ARG (mode outside 0..3), HIP. */
 enum { AWE_FUSE_NONE = 0, AWE_FUSE_FORWARD = 1, AWE_FUSE_ADJOINT = 2, AWE_FUSE_BOTH = 3 };
 awe_status awe_plan_set_fusion(awe_plan* plan, int32_t mode);

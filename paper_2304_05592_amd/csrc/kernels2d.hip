@@ -191,6 +191,11 @@ __device__ __forceinline__ const float* fwd_src(const StepArgs& a, const ShotDev
   return fwd_level(a, S, k);
 }
 
+// Column offset of a checkpoint slot's stores in kernels of one column per lane.  Two-level steps on 128-column
+// tiles read a slot by column pairs, so where nx is odd the column after the last is written too: its lane read
+// only zeros, so the value is 0.  (The rotating buffers are cleared as a whole before a solve.)
+__device__ __forceinline__ int slot_col(int x, int nx) { return x < nx + (nx & 1) ? 4 * x : kOOB; }
+
 // Bytes of the rotating buffer a one-level forward step writes level k into: with kStoreF32R only
 // the last level goes there too (the receivers' last sample is taken from it), so the other
 // levels' buffer stores are dropped by the range check.
@@ -261,6 +266,7 @@ __global__ __launch_bounds__(T2<TZ>::NT) void fwd2d_kernel(StepArgs a) {
   float* sl = reinterpret_cast<float*>(a.ws + S.store) + (long long)(to_slot ? a.st_slot : 0) * 2 * npts;
   const brsrc rsl0 = make_rsrc(sl, to_slot ? nz * row4 : 0);
   const brsrc rsl1 = make_rsrc(sl + npts, to_slot ? nz * row4 : 0);
+  const int cs = slot_col(x, nx);
   const int cx2 = x < nx ? 2 * x : kOOB;
   constexpr bool S16 = SK == kStoreBF16 || SK == kStoreFP16;
   float* scl = S16 ? reinterpret_cast<float*>(a.ws + S.scale) : nullptr;
@@ -289,8 +295,8 @@ __global__ __launch_bounds__(T2<TZ>::NT) void fwd2d_kernel(StepArgs a) {
     const int zo = z * row4;
     stb(rout, un, cx, zo);
     if (to_slot) {
-      stb(rsl0, un, cx, zo);
-      stb(rsl1, u, cx, zo);
+      stb(rsl0, un, cs, zo);
+      stb(rsl1, u, cs, zo);
     }
     // a stored level the next launch reads back stays in the caches; otherwise it is written once
     // and read thousands of launches later
@@ -841,6 +847,7 @@ __global__ __launch_bounds__((F2<TZ, V>::NT)) void fwd2d2_kernel(StepArgs a) {
   const int x = T.x0 + V * lane;
   const int cx = x < nx ? 4 * x : kOOB;
   const int cx2 = x < nx ? 2 * x : kOOB;
+  const int cs = V == 1 ? slot_col(x, nx) : cx;
   const int zE = T.z0 - kHalo;           // row 0 of the first-step region
 
   // the level k-1 tile first, then level k-2 and coef of this thread's first-step points and coef
@@ -886,8 +893,8 @@ __global__ __launch_bounds__((F2<TZ, V>::NT)) void fwd2d2_kernel(StepArgs a) {
       stv<V>(ro1, v, cx, zo);
       if (SK == kStoreF32) stv<V, kNT>(rs1, v, cx, zo);
       if (SLOT) {
-        stv<V>(rslv, v, cx, zo);
-        stv<V>(rslu, u[i], cx, zo);
+        stv<V>(rslv, v, cs, zo);
+        stv<V>(rslu, u[i], cs, zo);
       }
       if (S16) {   // rows of other tiles count too: their points are the level's
         lmax = absmax<V>(lmax, v);
@@ -930,7 +937,7 @@ __global__ __launch_bounds__((F2<TZ, V>::NT)) void fwd2d2_kernel(StepArgs a) {
     const int zo = z * row4;
     stv<V>(ro2, un, cx, zo);
     if (SK == kStoreF32) stv<V, kNT>(rs2, un, cx, zo);
-    if (SLOT) stv<V>(rsl0, un, cx, zo);
+    if (SLOT) stv<V>(rsl0, un, cs, zo);
     if (S16) lmax = absmax<V>(lmax, un);
     if (PRB && z < nz) {
       // the same two FP64 additions, in the same order, as two one-level launches

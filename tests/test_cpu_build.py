@@ -159,3 +159,17 @@ def test_two_level_checkpoint_advances_on_the_cpu_build(emu_lib):
     res = json.loads(r.stdout.strip().splitlines()[-1])
     print(res)
     assert res["nonzero"] and all(res["bitwise"].values())
+
+
+@pytest.mark.parametrize("widths, copies", [([117, 241], 37), ([33, 64, 120], 1)])
+def test_fusion_mode_changed_between_a_kept_forward_and_its_gradient_on_the_cpu_build(emu_lib, widths, copies):
+    """awe_forward(keep) of a CHECKPOINT plan, awe_plan_set_fusion, awe_backward: every ordered pair of modes gives
+    bitwise the gradient and F^T dd of one level per launch, whatever the workspace held before (NaN bytes
+    here), on windows of odd widths in 128-column and in 64-column tiles."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_mode_switch.py")], emu_lib,
+                   {"EMU_FILL": "255", "CASE_WIDTHS": ",".join(map(str, widths)), "CASE_COPIES": str(copies)}, timeout=900)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    print(res)
+    assert res["finite"] and res["nonzero"] and all(res["bitwise"].values())
