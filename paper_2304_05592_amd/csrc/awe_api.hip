@@ -9,6 +9,7 @@
 #include <unistd.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -77,6 +78,8 @@ struct Tiling {
   std::vector<InjEntry> inj_ent;
   void* dev = nullptr;
   awe::Tables tab{};
+  std::array<int, 4> built{};       // shape the tables were built for: tx, tz, ty, bz
+  std::array<int, 4> shape() const { return {tx, tz, ty, bz}; }
 };
 
 struct awe_plan {
@@ -446,6 +449,7 @@ awe_status upload_tiling(awe_plan* P, Tiling& T) {
   T.tab.wins = reinterpret_cast<const WinDev*>(b + o_w);
   T.tab.win_shots = reinterpret_cast<const int*>(b + o_ws);
   T.tab.order = reinterpret_cast<const int*>(b + o_or);
+  T.built = T.shape();
   return AWE_OK;
 }
 
@@ -516,8 +520,10 @@ void default_shapes(awe_plan* P) {
                : n64 < 200 ? 8 : n64 < 800 ? 24 : 32;
 }
 
-// Tables of a tiling built and uploaded where calls use it, given back where none does.
-awe_status refresh(awe_plan* P, Tiling& T, bool used, bool inject) {
+// Tables of a tiling built and uploaded where calls use it, given back where none does.  mode_switch: the
+// shots and their groups are the tables' own, so tables of the right shape stay, as do those not used now.
+awe_status refresh(awe_plan* P, Tiling& T, bool used, bool inject, bool mode_switch) {
+  if (mode_switch && (!used || (T.dev && T.built == T.shape()))) return AWE_OK;
   if (used) {
     const awe_status st = build_tiling(P, T, inject);
     return st != AWE_OK ? st : upload_tiling(P, T);
@@ -529,8 +535,9 @@ awe_status refresh(awe_plan* P, Tiling& T, bool used, bool inject) {
 
 // Shot groups and the tilings of the directions in `dirs` (bit 0 forward, bit 1 adjoint; the
 // groups change both, so a change of groups rebuilds both), built and uploaded: those of the kernels
-// the direction's calls can launch.
-awe_status rebuild(awe_plan* P, int dirs) {
+// the direction's calls can launch.  mode_switch: only the fusion mode changed.  Then no table is given back, so
+// that a HIP graph captured in one mode stays valid in another, and switching back builds nothing.
+awe_status rebuild(awe_plan* P, int dirs, bool mode_switch = false) {
   awe_status st = build_groups(P);
   if (st != AWE_OK) return st;
   default_shapes(P);
@@ -542,14 +549,14 @@ awe_status rebuild(awe_plan* P, int dirs) {
     two.tz = one.tz;
     const bool fused = fused_ok(P, bit);
     for (Tiling* T : {&one, &two})
-      if ((st = refresh(P, *T, (T == &two) == fused, bit == AWE_FUSE_ADJOINT)) != AWE_OK) return st;
+      if ((st = refresh(P, *T, (T == &two) == fused, bit == AWE_FUSE_ADJOINT, mode_switch)) != AWE_OK) return st;
     // Born launches hold two fields, and 128-column tiles of both cost more in occupancy than they save:
     // 16 shots of 730 x 421 43.1 us per launch 128 wide at 24 rows, 39.5 64 wide at 32; 16 of 1104 x 592 108
     // and 103 at 24 and 32 rows; 4 of 730 x 421 (n64 = 864) 15.8 and 15.9.
     if (bit == AWE_FUSE_FORWARD) {
       P->bn2.tx = 64;
       P->bn2.tz = !P->auto_rows[0] ? one.tz : tiles24(P, 64) < 1750 ? 24 : 32;
-      if ((st = refresh(P, P->bn2, fused && two.tx != 64, false)) != AWE_OK) return st;
+      if ((st = refresh(P, P->bn2, fused && two.tx != 64, false, mode_switch)) != AWE_OK) return st;
     }
   }
   return AWE_OK;
@@ -1652,18 +1659,25 @@ awe_status awe_plan_set_groups(awe_plan* P, int32_t ngroups, int32_t* actual) {
 awe_status awe_plan_set_fusion(awe_plan* P, int32_t mode) {
   if (!P) return fail(AWE_ERR_INVALID_ARG, "plan is NULL");
   if (mode < 0 || mode > AWE_FUSE_BOTH) return fail(AWE_ERR_INVALID_ARG, "fusion mode must be 0..3");
-  const int changed = mode ^ P->fuse2;
+  const int before = P->fuse2;
+  const bool auto_before = P->auto_fuse;
   P->fuse2 = mode;
   P->auto_fuse = false;
-  // two-level kernels exist for 8, 16, 24 and 32 rows
   for (int bit : {AWE_FUSE_FORWARD, AWE_FUSE_ADJOINT}) {
     Tiling& T = bit == AWE_FUSE_FORWARD ? P->fw : P->rv;
-    awe_status st = AWE_OK;
-    if ((mode & bit) && !two_level_rows(T.tz)) st = awe_plan_set_tiles_dir(P, bit, T.tz < 24 ? 16 : 32, T.ty, T.bz);
-    else if (changed & bit) st = rebuild(P, bit);
-    if (st != AWE_OK) return st;
+    // two-level kernels exist for 8, 16, 24 and 32 rows
+    if ((mode & bit) && !two_level_rows(T.tz)) {
+      const awe_status st = awe_plan_set_tiles_dir(P, bit, T.tz < 24 ? 16 : 32, T.ty, T.bz);
+      if (st != AWE_OK) return st;
+    }
   }
-  return AWE_OK;
+  const awe_status st = rebuild(P, (mode ^ before) & AWE_FUSE_BOTH, true);
+  if (st != AWE_OK) {   // the tables of the mode before are still there
+    P->fuse2 = before;
+    P->auto_fuse = auto_before;
+    default_shapes(P);
+  }
+  return st;
 }
 
 awe_status awe_profile_enable(awe_plan* P, int64_t max_launches, int32_t stride) {

@@ -215,12 +215,15 @@ extern "C" long long emu_launch_count() { return emu::launches; }
 // ---------------------------------------------------------------- runtime calls
 namespace {
 std::map<void*, size_t> allocs;
+long long mallocs = 0, frees = 0;
 hipError_t last_error = hipSuccess;
 struct emu_event_t { int recorded = 0; };
 }  // namespace
 
 hipError_t hipMalloc(void** p, size_t n) {
   if (!p) return hipErrorInvalidValue;
+  if (std::getenv("EMU_FAIL_MALLOC")) return hipErrorMemoryAllocation;
+  ++mallocs;
   const size_t cap = (n + 255) / 256 * 256 + 256;
   void* q = std::aligned_alloc(256, cap);
   if (!q) return hipErrorMemoryAllocation;
@@ -250,9 +253,13 @@ hipError_t hipFree(void* p) {
     std::abort();
   }
   allocs.erase(it);
+  ++frees;
   std::free(p);
   return hipSuccess;
 }
+
+extern "C" long long emu_malloc_count() { return mallocs; }
+extern "C" long long emu_free_count() { return frees; }
 
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
   if (n) std::memcpy(d, s, n);

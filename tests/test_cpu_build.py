@@ -173,3 +173,15 @@ def test_fusion_mode_changed_between_a_kept_forward_and_its_gradient_on_the_cpu_
     res = json.loads(r.stdout.strip().splitlines()[-1])
     print(res)
     assert res["finite"] and res["nonzero"] and all(res["bitwise"].values())
+
+
+def test_fusion_mode_keeps_the_device_tables_on_the_cpu_build(emu_lib):
+    """awe_plan_set_fusion gives no device table back (a graph captured before holds their addresses), builds none
+    twice, and leaves the plan as it was when it fails."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_mode_tables.py")], emu_lib, timeout=600)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    print(res)
+    assert not any(res["freed"].values()) and not any(res["rebuilt"].values())
+    assert res["refused"] and res["unchanged"] and all(res["bitwise"])

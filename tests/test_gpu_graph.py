@@ -50,3 +50,38 @@ def test_graph_replays_match_eager(storage):
         torch.cuda.synchronize()
         assert torch.equal(g, g_ref), it
         assert torch.equal(loss_g, loss_ref), it
+
+
+@pytest.mark.parametrize("shots", [2, 60])
+def test_graph_replays_after_a_change_of_the_fusion_mode(shots):
+    """A graph holds the addresses of the plan's tables: a change of the fusion mode after the capture, with eager
+    calls in the other modes in between, leaves every replay bitwise right (narrow tiles, and enough shots for
+    128-column ones)."""
+    wl = W.small_2d(nshot=2) if shots == 2 else W.small_2d(nz=40, windows=[230] * shots, T_per_shot=[60.0] * shots, nrec=9)
+    plan = make_plan(wl, storage=A.Storage(A.STORE_FULL))
+    m, q = gpu_inputs(wl, plan)
+    dd = torch.randn(plan.layout.d_size, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    dm = 0.001 * m
+    ws = plan.workspace()
+    g = torch.empty(plan.layout.m_size, dtype=torch.float64, device="cuda")
+    d, jd = torch.empty_like(dd), torch.empty_like(dd)
+
+    def calls():
+        plan.forward(m, q, d=d, keep=True, ws=ws)
+        plan.backward(m, q, dd, g=g, ws=ws)
+        plan.born(m, q, dm, dd=jd, ws=ws)
+
+    calls()
+    torch.cuda.synchronize()
+    ref = [t.clone() for t in (g, d, jd)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls()
+    for mode in (A.FUSE_NONE, A.FUSE_FORWARD, A.FUSE_ADJOINT, A.FUSE_BOTH):
+        plan.set_fusion(mode)
+        for run in (calls, graph.replay):
+            for t in (g, d, jd):
+                t.zero_()
+            run()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip((g, d, jd), ref)), (mode, run)
