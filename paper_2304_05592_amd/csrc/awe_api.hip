@@ -486,6 +486,30 @@ bool wide_tiles(const awe_plan* P, int bit) {
   return n128 >= 220 && n64 * (bit == AWE_FUSE_FORWARD ? 1.08 : 1.05) >= 2.0 * n128;
 }
 
+// Tile rows for windows that tiles of `rows` rows (24 or 32) fit badly: 24, 16 or 32 where that takes at most 4/5 of
+// their padded rows.  us per level with one-level launches, 32 rows and the rows taken, graph replays, reverse sweep
+// without imaging / whole gradient with BF16 store: 450 windows of 41 x 45 25.6 / 59.1, 29.4 / 62.0, 25.6 / 58.4
+// (16 rows); 500 of 70 x 64 28.4 / 70.5, 29.3 / 67.5, 28.3 / 65.1 (24 rows).  A smaller saving
+// does not pay (300 windows of 49 x 250, reverse sweep: 24.9 at 24 rows, 26.4 at 32, a ninth fewer).  Where two heights fit
+// alike, forward launches are faster with the taller, reverse launches with the shorter.
+int fitting_rows(const awe_plan* P, int w, int rows, bool taller) {
+  if (rows < 24) return rows;
+  auto padded = [&](int tz) {
+    long long n = 0;
+    for (const ShotDev& d : P->sd) n += (long long)((d.nx + w - 1) / w) * ((d.nz + tz - 1) / tz) * tz;
+    return n;
+  };
+  const long long n = padded(rows);
+  long long least = n * 4 / 5;
+  int best = rows;
+  for (int tz : {16, 24, 32})
+    if (const long long t = padded(tz); t < least || (t == least && (taller || best == rows))) {
+      least = t;
+      best = tz;
+    }
+  return best;
+}
+
 // Launch shapes of the directions the caller has not set, from the storage and the work of a launch.
 //
 // 2D: two levels per launch, which won at every size timed: one shot of 281 x 181 2.3 -> 1.2 ms forward;
@@ -511,13 +535,13 @@ void default_shapes(awe_plan* P) {
   if (P->auto_rows[0])
     P->fw.tz = !(P->fuse2 & AWE_FUSE_FORWARD) ? 32
                : probed ? 8
-               : wide_tiles(P, AWE_FUSE_FORWARD) ? 24
-               : n64 < 100 ? 8 : n64 < 200 ? 16 : n64 < 500 ? 24 : 32;
+               : wide_tiles(P, AWE_FUSE_FORWARD) ? fitting_rows(P, 128, 24, true)
+               : n64 < 100 ? 8 : n64 < 200 ? 16 : n64 < 500 ? 24 : fitting_rows(P, 64, 32, true);
   if (P->auto_rows[1])
     P->rv.tz = !(P->fuse2 & AWE_FUSE_ADJOINT) ? 16
                : probed ? 8
-               : wide_tiles(P, AWE_FUSE_ADJOINT) ? (n128 < 600 ? 16 : 24)
-               : n64 < 200 ? 8 : n64 < 800 ? 24 : 32;
+               : wide_tiles(P, AWE_FUSE_ADJOINT) ? (n128 < 600 ? 16 : fitting_rows(P, 128, 24, false))
+               : n64 < 200 ? 8 : n64 < 800 ? 24 : fitting_rows(P, 64, 32, false);
 }
 
 // Tables of a tiling built and uploaded where calls use it, given back where none does.  mode_switch: the
@@ -552,10 +576,11 @@ awe_status rebuild(awe_plan* P, int dirs, bool mode_switch = false) {
       if ((st = refresh(P, *T, (T == &two) == fused, bit == AWE_FUSE_ADJOINT, mode_switch)) != AWE_OK) return st;
     // Born launches hold two fields, and 128-column tiles of both cost more in occupancy than they save:
     // 16 shots of 730 x 421 43.1 us per launch 128 wide at 24 rows, 39.5 64 wide at 32; 16 of 1104 x 592 108
-    // and 103 at 24 and 32 rows; 4 of 730 x 421 (n64 = 864) 15.8 and 15.9.
+    // and 103 at 24 and 32 rows; 4 of 730 x 421 (n64 = 864) 15.8 and 15.9.  800 windows of 12 x 250 130 us at 32
+    // rows, 117 at the 16 that fit.
     if (bit == AWE_FUSE_FORWARD) {
       P->bn2.tx = 64;
-      P->bn2.tz = !P->auto_rows[0] ? one.tz : tiles24(P, 64) < 1750 ? 24 : 32;
+      P->bn2.tz = !P->auto_rows[0] ? one.tz : fitting_rows(P, 64, tiles24(P, 64) < 1750 ? 24 : 32, true);
       if ((st = refresh(P, P->bn2, fused && two.tx != 64, false, mode_switch)) != AWE_OK) return st;
     }
   }

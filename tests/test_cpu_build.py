@@ -185,3 +185,15 @@ def test_fusion_mode_keeps_the_device_tables_on_the_cpu_build(emu_lib):
     print(res)
     assert not any(res["freed"].values()) and not any(res["rebuilt"].values())
     assert res["refused"] and res["unchanged"] and all(res["bitwise"])
+
+
+def test_default_rows_of_many_small_windows_on_the_cpu_build(emu_lib):
+    """Default tile rows fit short windows: other rows where those of the launch's size would be padded by a
+    quarter more, and those of its size elsewhere (times at the rule)."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_default_rows.py")], emu_lib, timeout=300)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    assert res == {"41 45 450": [24, 16, 3], "70 64 500": [24, 24, 3], "33 64 800": [24, 16, 3], "25 64 900": [32, 32, 3],
+                   "97 190 150": [32, 32, 3], "12 250 800": [16, 16, 3], "26 250 400": [32, 16, 3],
+                   "49 250 300": [24, 24, 3]}
