@@ -95,6 +95,8 @@ struct awe_plan {
   // shapes not set by the caller or the autotuner follow default_shapes
   bool auto_rows[2] = {true, true};  // tile rows (2D) / column blocks (3D): forward, adjoint
   bool auto_fuse = true;
+  bool many = true;       // forward solves of few tiles take kManyLevels levels per launch (many_levels): default
+                          // shapes, or the autotuner's choice
   Tiling fw, rv;          // launch shapes of forward solves / adjoint steps
   Tiling fw2, rv2;        // their tables for the two-level kernels, whose tiles may be wider (rows: fw.tz, rv.tz)
   Tiling bn2;             // two-level Born modelling, where fw2's tiles are 128 columns wide
@@ -830,14 +832,29 @@ awe_status step_adj2(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s, bool s
   return AWE_OK;
 }
 
-// Does a forward solve take kManyLevels levels per launch?  Default shapes only, while their tiles are 64
-// columns and at most 24 rows and, as PROBED plans have 8 rows at every size, few: launches of few tiles, bound by their fixed cost.  us per level at two and
+// Does a forward solve take kManyLevels levels per launch?  Where the default or the autotuner says so, while the
+// tiles are 64 columns and at most 24 rows and, as PROBED plans have 8 rows at every size, few: launches of few
+// tiles, bound by their fixed cost.  us per level at two and
 // three levels per launch, with FP32 store: one shot of 281 x 181 2.04 and 1.84; of 730 x 421 2.77 and 2.53;
 // two of those (n64 = 432) 3.53 and 3.26; from n64 = 500 on the rows are 32 and the halo work, a third more
 // than at two levels, fills the chip.
 bool many_levels(const awe_plan* P, int store) {
-  return P->auto_fuse && P->auto_rows[0] && fused_ok(P, AWE_FUSE_FORWARD) && P->fw2.tx == 64 && P->fw2.tz < 32 &&
+  return P->many && fused_ok(P, AWE_FUSE_FORWARD) && P->fw2.tx == 64 && P->fw2.tz < 32 &&
          tiles24(P, 64) < 500 && (store == awe::kStoreNone || store == awe::kStoreF32);
+}
+
+// The kManyLevels levels that end at `last` (those below level 1 do not count); flip alternates between launches,
+// 0 in the one that ends at nsteps.
+awe_status step_fwdm(awe_plan* P, awe::StepArgs& a, int last, int flip, int store, hipStream_t s) {
+  set_group(P, P->fw2, a, last);
+  a.step = last - awe::kManyLevels + 1;
+  a.flip = flip;
+  if (a.ntiles <= 0) return AWE_OK;
+  const int first = std::max(1, a.step);
+  if (awe_status st = check_step(P, P->fw2, a, first, last, "many-level forward step")) return st;
+  ProfScope ps(P, 0, s, last - first + 1);
+  AWE_HIP(awe::launch_fwd2dm(a, P->fw2.tz, store, s));
+  return AWE_OK;
 }
 
 // Forward levels 1..nsteps: one single step first when the count is odd, then pairs.
@@ -847,16 +864,8 @@ awe_status forward_loop(awe_plan* P, awe::StepArgs& a, int store, hipStream_t s)
   if (many_levels(P, store)) {
     ProfRun run(P, s, 0);
     constexpr int T = awe::kManyLevels;
-    for (int m = (P->nsteps + T - 1) / T; m-- > 0;) {   // launches after this one
-      const int last = P->nsteps - T * m;
-      set_group(P, P->fw2, a, last);
-      a.step = last - T + 1;
-      a.flip = 2 * (m & 1);
-      if (a.ntiles <= 0) continue;
-      if ((st = check_step(P, P->fw2, a, std::max(1, a.step), last, "many-level forward step")) != AWE_OK) return st;
-      ProfScope ps(P, 0, s, last - std::max(1, a.step) + 1);
-      AWE_HIP(awe::launch_fwd2dm(a, P->fw2.tz, store, s));
-    }
+    for (int m = (P->nsteps + T - 1) / T; m-- > 0;)   // launches after this one
+      if ((st = step_fwdm(P, a, P->nsteps - T * m, 2 * (m & 1), store, s)) != AWE_OK) return st;
     return AWE_OK;
   }
   // a 2D FP32 sweep of one-level steps reads its previous levels back from the store
@@ -1000,10 +1009,12 @@ awe_status run_actions(awe_plan* P, awe::StepArgs& fa, awe::StepArgs& aa, size_t
 }
 
 // ---- autotuner result cache: a JSON object of "key": {"fw": [tz, ty, bz], "rv": [...],
-// "fusion": f, "ms": t} entries, one per line, in the file named by AWE_TUNE_CACHE.
+// "fusion": f, "ms": t, "levels": n} entries, one per line, in the file named by AWE_TUNE_CACHE ("levels", the
+// levels per launch of forward solves, may be left out: three only where it says so).
 struct TuneEntry {
   int fw[3], rv[3], fusion;
   double ms;
+  int levels;
 };
 
 // Device, problem shape, storage, grouping and probe length: what the timing of the candidate
@@ -1049,8 +1060,9 @@ std::map<std::string, TuneEntry> read_tune_cache(const char* path) {
   char line[2048], key[1024];
   while (std::fgets(line, sizeof line, f)) {
     TuneEntry e{};
-    if (std::sscanf(line, " \"%1023[^\"]\": {\"fw\": [%d, %d, %d], \"rv\": [%d, %d, %d], \"fusion\": %d, \"ms\": %lf}",
-                    key, &e.fw[0], &e.fw[1], &e.fw[2], &e.rv[0], &e.rv[1], &e.rv[2], &e.fusion, &e.ms) == 9)
+    if (std::sscanf(line, " \"%1023[^\"]\": {\"fw\": [%d, %d, %d], \"rv\": [%d, %d, %d], \"fusion\": %d, \"ms\": %lf, \"levels\": %d}",
+                    key, &e.fw[0], &e.fw[1], &e.fw[2], &e.rv[0], &e.rv[1], &e.rv[2], &e.fusion, &e.ms,
+                    &e.levels) >= 9)
       out[key] = e;
   }
   std::fclose(f);
@@ -1066,8 +1078,8 @@ void write_tune_cache(const char* path, const std::map<std::string, TuneEntry>& 
   std::fprintf(f, "{\n");
   size_t i = 0;
   for (const auto& [k, e] : entries)
-    std::fprintf(f, "  \"%s\": {\"fw\": [%d, %d, %d], \"rv\": [%d, %d, %d], \"fusion\": %d, \"ms\": %.6f}%s\n",
-                 k.c_str(), e.fw[0], e.fw[1], e.fw[2], e.rv[0], e.rv[1], e.rv[2], e.fusion, e.ms,
+    std::fprintf(f, "  \"%s\": {\"fw\": [%d, %d, %d], \"rv\": [%d, %d, %d], \"fusion\": %d, \"ms\": %.6f, \"levels\": %d}%s\n",
+                 k.c_str(), e.fw[0], e.fw[1], e.fw[2], e.rv[0], e.rv[1], e.rv[2], e.fusion, e.ms, e.levels,
                  ++i < entries.size() ? "," : "");
   std::fprintf(f, "}\n");
   const bool ok = std::fclose(f) == 0;
@@ -1091,6 +1103,7 @@ bool apply_tune_entry(awe_plan* P, const TuneEntry& e, awe_status* st) {
   P->rv.bz = e.rv[2];
   P->fuse2 = e.fusion;
   P->auto_fuse = P->auto_rows[0] = P->auto_rows[1] = false;
+  P->many = e.levels == awe::kManyLevels;
   P->kept_ws = nullptr;
   *st = rebuild(P, 3);
   return true;
@@ -1487,12 +1500,16 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
   P->auto_fuse = P->auto_rows[0] = P->auto_rows[1] = false;
   // one candidate list per direction; the forward probe times forward levels only, the adjoint
   // probe adjoint levels only, so each direction keeps its own fastest shape
-  struct Cand { int tz, ty, bz, fuse; };
+  struct Cand { int tz, ty, bz, fuse, many; };
   std::vector<Cand> cands;
   if (P->ndim == 2) {
     // one level per launch lost at every size timed (see default_shapes): its best shape stays in
-    for (int tz : {8, 16, 24, 32}) cands.push_back({tz, 8, 0, 1});
-    cands.push_back({24, 8, 0, 0});
+    for (int tz : {8, 16, 24, 32}) cands.push_back({tz, 8, 0, 1, 0});
+    cands.push_back({24, 8, 0, 0, 0});
+    // forward solves only, where many_levels holds; a checkpointed gradient's forward launches are advances, which
+    // do not take them
+    if (P->store.mode != AWE_STORE_CHECKPOINT)
+      for (int tz : {8, 16, 24}) cands.push_back({tz, 8, 0, 1, 1});
   } else {
     // z-blocks of the full depth, of fixed lengths, and of the depth split evenly into 2 to 8
     // (no short last block)
@@ -1503,9 +1520,9 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
       const int b = ((nz + k - 1) / k + 1) & ~1;
       if (b >= 16 && std::find(bzs.begin(), bzs.end(), b) == bzs.end()) bzs.push_back(b);
     }
-    cands.push_back({32, 8, 8, 0});   // bricks
+    cands.push_back({32, 8, 8, 0, 0});   // bricks
     for (int ty : {4, 8, 16})
-      for (int bz : bzs) cands.push_back({32, ty, bz, 0});
+      for (int bz : bzs) cands.push_back({32, ty, bz, 0, 0});
   }
   hipEvent_t e0, e1;
   AWE_HIP(hipEventCreate(&e0));
@@ -1532,6 +1549,7 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
                          : P->sd[0].acc >= 0 ? awe::kImgBuffers : awe::kImgNone;
   double best[2] = {1e300, 1e300};
   Cand win[2] = {cands[0], cands[0]};
+  bool many_timed = false;
   P->cur = 0;  // the probes time the first shot group
   auto fail_out = [&](awe_status e) {
     keep_ev.swap(P->prof_ev);
@@ -1547,7 +1565,11 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
       T.ty = c.ty;
       T.bz = c.bz;
       P->fuse2 = (P->fuse2 & ~bit) | (c.fuse ? bit : 0);
+      if (c.many && dir == 1) continue;
       if ((st = rebuild(P, dir == 0 ? 1 : 2)) != AWE_OK) return fail_out(st);
+      P->many = c.many;
+      if (c.many && !many_levels(P, fkind)) continue;
+      many_timed |= c.many != 0;
       if ((st = prepare(P, m, ws, true, true, s)) != AWE_OK) return fail_out(st);
       for (int i = 0; i < P->nshot; ++i) {
         if (P->sd[i].acc >= 0)
@@ -1576,23 +1598,31 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
       // untimed, or the candidate tried first would be timed with its first launch's set-up (3D bricks, the
       // first, then lost to slower marches now and then)
       const bool two = fused_ok(P, dir == 0 ? AWE_FUSE_FORWARD : AWE_FUSE_ADJOINT);
+      const int levels = c.many ? awe::kManyLevels : 1 + two;
       const int k1 = P->ndim == 2 && fkind == awe::kStoreF32 ? awe::kStoreF32R : fkind;  // as forward_loop
-      const int n0 = dir == 0 ? std::max(1, P->nsteps - probe + 1) : P->nsteps;
-      auto in_probe = [&](int n) { return dir == 0 ? n + two <= P->nsteps : n > P->nsteps - probe && n >= 2; };
+      const int n0 = dir == 0 ? std::max(1, P->nsteps - std::max(probe, levels) + 1) : P->nsteps;
+      auto in_probe = [&](int n) {
+        return dir == 0 ? n + levels - 1 <= P->nsteps : n > P->nsteps - probe && n >= 2;
+      };
       auto step = [&](int n) {
+        if (c.many) return step_fwdm(P, fa, n + levels - 1, 2 * ((n - n0) / levels & 1), fkind, s);
         return dir == 0 ? (two ? step_fwd2(P, fa, n, fkind, s) : step_fwd(P, fa, n, k1, s))
                         : (two ? step_adj2(P, aa, n, s) : step_adj(P, aa, n, s));
       };
       if (in_probe(n0) && (st = step(n0)) != AWE_OK) return fail_out(st);
       if (hipError_t e = hipEventRecord(e0, s)) return fail_out(hip_fail(e, "autotune event"));
-      for (int n = n0; in_probe(n); n += dir == 0 ? 1 + two : -1 - two)
+      int done = 0;
+      for (int n = n0; in_probe(n); n += dir == 0 ? levels : -levels, done += levels)
         if ((st = step(n)) != AWE_OK) return fail_out(st);
       if (hipError_t e = hipEventRecord(e1, s)) return fail_out(hip_fail(e, "autotune event"));
       if (hipError_t e = hipEventSynchronize(e1)) return fail_out(hip_fail(e, "autotune event"));
       float ms = 0.f;
       if (hipError_t e = hipEventElapsedTime(&ms, e0, e1)) return fail_out(hip_fail(e, "autotune event"));
-      if (ms < best[dir]) {
-        best[dir] = ms;
+      // launches of two or three levels may cover a level more or less than probe; a candidate that the sweep is
+      // too short for loses to one that ran
+      const double t = done > 0 ? (double)ms * probe / done : 1e200;
+      if (t < best[dir]) {
+        best[dir] = t;
         win[dir] = c;
       }
     }
@@ -1607,6 +1637,9 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
   P->rv.ty = win[1].ty;
   P->rv.bz = win[1].bz;
   P->fuse2 = (win[0].fuse ? AWE_FUSE_FORWARD : 0) | (win[1].fuse ? AWE_FUSE_ADJOINT : 0);
+  P->many = win[0].many || !many_timed;   // not timed with the storage kept: solves without it follow the rule
+  for (double& b : best)
+    if (b >= 1e200) b = 0.0;   // nothing to time
   if ((st = rebuild(P, 3)) != AWE_OK) return st;
   if (chosen) {
     chosen[0] = P->fw.tz;
@@ -1618,7 +1651,7 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
   if (cache && *cache) {
     auto entries = read_tune_cache(cache);
     entries[key] = TuneEntry{{P->fw.tz, P->fw.ty, P->fw.bz}, {P->rv.tz, P->rv.ty, P->rv.bz}, P->fuse2,
-                             best[0] + best[1]};
+                             best[0] + best[1], P->many ? awe::kManyLevels : 0};
     write_tune_cache(cache, entries);
   }
   return AWE_OK;
@@ -1659,6 +1692,7 @@ awe_status awe_plan_set_tiles_dir(awe_plan* P, int32_t dirs, int32_t tz, int32_t
   for (Tiling* T : {&P->fw, &P->rv}) {
     if (!(dirs & (T == &P->fw ? 1 : 2))) continue;
     P->auto_rows[T == &P->fw ? 0 : 1] = false;
+    if (T == &P->fw) P->many = false;
     T->tz = tz;
     T->ty = ty;
     T->bz = bz;
@@ -1685,9 +1719,9 @@ awe_status awe_plan_set_fusion(awe_plan* P, int32_t mode) {
   if (!P) return fail(AWE_ERR_INVALID_ARG, "plan is NULL");
   if (mode < 0 || mode > AWE_FUSE_BOTH) return fail(AWE_ERR_INVALID_ARG, "fusion mode must be 0..3");
   const int before = P->fuse2;
-  const bool auto_before = P->auto_fuse;
+  const bool auto_before = P->auto_fuse, many_before = P->many;
   P->fuse2 = mode;
-  P->auto_fuse = false;
+  P->auto_fuse = P->many = false;
   for (int bit : {AWE_FUSE_FORWARD, AWE_FUSE_ADJOINT}) {
     Tiling& T = bit == AWE_FUSE_FORWARD ? P->fw : P->rv;
     // two-level kernels exist for 8, 16, 24 and 32 rows
@@ -1700,6 +1734,7 @@ awe_status awe_plan_set_fusion(awe_plan* P, int32_t mode) {
   if (st != AWE_OK) {   // the tables of the mode before are still there
     P->fuse2 = before;
     P->auto_fuse = auto_before;
+    P->many = many_before;
     default_shapes(P);
   }
   return st;

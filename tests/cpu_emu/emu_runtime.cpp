@@ -217,7 +217,7 @@ namespace {
 std::map<void*, size_t> allocs;
 long long mallocs = 0, frees = 0;
 hipError_t last_error = hipSuccess;
-struct emu_event_t { int recorded = 0; };
+struct emu_event_t { int recorded = 0; long long launches = 0; };
 }  // namespace
 
 hipError_t hipMalloc(void** p, size_t n) {
@@ -306,13 +306,16 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
   if (!e) return hipErrorInvalidValue;
-  reinterpret_cast<emu_event_t*>(e)->recorded = 1;
+  auto* ev = reinterpret_cast<emu_event_t*>(e);
+  ev->recorded = 1;
+  ev->launches = emu::launches;
   return hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) { return e ? hipSuccess : hipErrorInvalidValue; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
+  // emulated time: a millisecond per launch
   if (!ms || !a || !b) return hipErrorInvalidValue;
-  *ms = 0.f;
+  *ms = (float)(reinterpret_cast<emu_event_t*>(b)->launches - reinterpret_cast<emu_event_t*>(a)->launches);
   return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }

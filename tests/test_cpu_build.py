@@ -197,3 +197,17 @@ def test_default_rows_of_many_small_windows_on_the_cpu_build(emu_lib):
     assert res == {"41 45 450": [24, 16, 3], "70 64 500": [24, 24, 3], "33 64 800": [24, 16, 3], "25 64 900": [32, 32, 3],
                    "97 190 150": [32, 32, 3], "12 250 800": [16, 16, 3], "26 250 400": [32, 16, 3],
                    "49 250 300": [24, 24, 3]}
+
+
+def test_tuned_forward_solves_keep_their_levels_per_launch_on_the_cpu_build(emu_lib):
+    """The autotuner knows three levels per launch: a tuned plan's forward solve takes as few launches as a default
+    plan's, and the tuner's cache keeps that."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_tuned_levels.py")], emu_lib, timeout=600)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    print(res)
+    assert all(res["bitwise"])
+    assert all(n <= v[0] for v in res["launches"].values() for n in v)
+    n1, n2, n3 = res["cache"]
+    assert n1 == n2 == res["launches"]["none"][0] < n3
