@@ -314,7 +314,7 @@ awe_status awe_checkpoint_schedule(int32_t nsteps, int32_t nslots, int32_t* acti
  * fusion mode (awe_plan_get_tiles gives both shapes); best_ms (may be NULL) the sum of the two
  * winning probe times (for probe_steps levels).
  * Result cache: when the environment variable AWE_TUNE_CACHE names a file, the call first looks
- * up a key made of the device (architecture name, compute units), the problem's shape (ndim,
+ * up a key made of the library's and its tuner's version, the device (architecture name, compute units), the problem's shape (ndim,
  * shot count and a hash of every shot's grid, nt, receiver count and window), the storage, the
  * shot grouping and probe_steps.  A valid entry found there is put in effect without running
  * any probe (best_ms then returns the stored time); otherwise the probes run and the result is

@@ -1017,7 +1017,11 @@ struct TuneEntry {
   int levels;
 };
 
-// Device, problem shape, storage, grouping and probe length: what the timing of the candidate
+// Generation of the step kernels and of the tuner's candidates, raised with every change of either: shapes timed on
+// other kernels (one level per launch, 3D marches) do not fit.
+constexpr int kTunerRevision = 2;
+
+// Tuner, device, problem shape, storage, grouping and probe length: what the timing of the candidate
 // shapes depends on.  The shots' grids, time axes, receiver counts and windows enter through a
 // 64-bit FNV-1a hash.
 std::string tune_key(const awe_plan* P, int probe) {
@@ -1047,8 +1051,8 @@ std::string tune_key(const awe_plan* P, int probe) {
     mix(sh.m_offset);
   }
   char buf[512];
-  std::snprintf(buf, sizeof buf, "v%d/%s/%dcu/%dd/n%d/st%d.%d.%d/g%zu/p%d/%016llx", AWE_VERSION, arch.c_str(),
-                cus, P->ndim, P->nshot, P->store.mode, P->store.nslots, P->store.prec, P->g_nshot.size(),
+  std::snprintf(buf, sizeof buf, "v%d.%d/%s/%dcu/%dd/n%d/st%d.%d.%d/g%zu/p%d/%016llx", AWE_VERSION, kTunerRevision,
+                arch.c_str(), cus, P->ndim, P->nshot, P->store.mode, P->store.nslots, P->store.prec, P->g_nshot.size(),
                 probe, h);
   return buf;
 }

@@ -211,3 +211,12 @@ def test_tuned_forward_solves_keep_their_levels_per_launch_on_the_cpu_build(emu_
     assert all(n <= v[0] for v in res["launches"].values() for n in v)
     n1, n2, n3 = res["cache"]
     assert n1 == n2 == res["launches"]["none"][0] < n3
+
+
+def test_tune_cache_entries_of_other_kernels_are_not_applied_on_the_cpu_build(emu_lib):
+    """The cache key names the tuner's version: an entry without it is timed again, not applied."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_tune_key.py")], emu_lib, timeout=300)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    assert not res["applied"] and res["same"] and res["entries"], res
