@@ -220,7 +220,8 @@ def points_of(wl, shots):
 
 
 def kernel_table(prof, launch_points, kinds, fused=0, mixed=None):
-    """Per kernel class: launches, average event time and achieved algorithmic GB/s.  A class
+    """Per kernel class: launches, average event time and achieved algorithmic GB/s.  A plan with
+    default shapes (no tiles chosen: fused and mixed empty) counts time levels as launches.  A class
     that runs two levels per launch (fused: bit 0 forward, bit 1 adjoint) performs two
     point-updates per grid point and launch; its own (fused) bytes are reported beside."""
     out = {}
@@ -578,10 +579,11 @@ def bench_c3(args):
     prof = plan.profile_read()
     plan.profile_disable()
     # advances run as pairs of levels, after a single one where their count is odd, when the forward fusion
-    # is on; paired reversals (x, x-1) as one two-level launch when the adjoint fusion is
+    # is on; paired reversals (x, x-1) as one two-level launch when the adjoint fusion is.  A plan with default
+    # shapes (no tiles chosen) counts levels instead of launches
     fuse_fwd = bool(plan.get_tiles()["fusion"] & A.FUSE_FORWARD)
     advances = [b - a for op, a, b in sched if op == 0]
-    mixed = {"forward": (sum(n // 2 for n in advances), sum(n % 2 for n in advances))} if fuse_fwd else {}
+    mixed = {"forward": (sum(n // 2 for n in advances), sum(n % 2 for n in advances))} if fuse_fwd and tiles else {}
     two = bool(plan.get_tiles()["fusion"] & A.FUSE_ADJOINT)
     pairs = singles = 0
     i = 0
@@ -594,7 +596,7 @@ def bench_c3(args):
                 continue
             singles += 1
         i += 1
-    if two:
+    if two and tiles:
         mixed["adjoint"] = (pairs, singles)
     kernels = kernel_table(prof, launch_points, {"forward": "none", "adjoint": "buffers"}, mixed=mixed)
     names = {"forward": ("fwd2d2 steps (forward / recompute, two levels per launch, 16 B/point-update)" if fuse_fwd

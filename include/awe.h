@@ -375,12 +375,12 @@ awe_status awe_plan_set_fusion(awe_plan* plan, int32_t mode);
  * The steps of one sweep (the forward or the adjoint step loop of a call, per shot group) and
  * the forward steps of one checkpoint advance each form one interval, which counts every launch
  * it holds, so that no event is recorded between them; other step launches are timed one by
- * one.  With CHECKPOINT storage a plan whose fusion mode was never set counts time levels, the schedule's
- * steps, in place of launches.
+ * one.  A plan whose fusion mode is the default (set neither by awe_plan_set_fusion nor by the autotuner) counts
+ * time levels in place of launches, so that its counts do not depend on how many levels a launch takes.
  * The records are stream work, so they are also captured into a HIP graph and then time
  * the graph's replays.  Classes: 0 forward step, 1 adjoint step (with imaging and, in 3D,
  * receiver injection), 2 Born step.  awe_profile_read waits for the recorded events,
- * returns per class the number of timed launches and the summed time of their intervals in ms,
+ * returns per class the number of timed launches (or levels, see above) and the summed time of their intervals in ms,
  * and restarts the count.  Enabling creates HIP events (host resources, no device memory). */
 awe_status awe_profile_enable(awe_plan* plan, int64_t max_launches, int32_t stride);
 awe_status awe_profile_read(awe_plan* plan, int64_t counts[3], double ms[3]);

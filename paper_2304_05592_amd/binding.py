@@ -387,7 +387,8 @@ class Plan:
         check(lib().awe_profile_enable(self._h, int(max_launches), int(stride)))
 
     def profile_read(self):
-        """{class: (launches, total ms)} for classes 'forward', 'adjoint', 'born'."""
+        """{class: (launches, total ms)} for classes 'forward', 'adjoint', 'born'; time levels in place of
+        launches while the plan's fusion mode is the default (see awe_profile_read)."""
         counts = (ctypes.c_int64 * 3)()
         ms = (ctypes.c_double * 3)()
         check(lib().awe_profile_read(self._h, counts, ms))

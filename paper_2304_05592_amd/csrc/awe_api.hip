@@ -131,7 +131,7 @@ struct awe_plan {
   // kernel timing
   std::vector<hipEvent_t> prof_ev;
   std::vector<int> prof_cls;
-  std::vector<long long> prof_cnt;  // launches inside each timed interval
+  std::vector<long long> prof_cnt;  // launches (or levels, see ProfScope) inside each timed interval
   bool prof_in_run = false;         // inside a timed run of steps (see ProfRun)
   long long prof_run_launches = 0;
   size_t prof_next = 0;
@@ -714,13 +714,13 @@ awe_status prepare(awe_plan* P, const float* m, void* ws, bool zero_fwd, bool ze
 }
 
 // Kernel timing: an event pair around one launch (class cls) of `levels` levels when enabled and not
-// full.  CHECKPOINT plans whose fusion mode was never set count levels: the schedule's steps.
+// full.  Plans whose fusion mode is the default count levels, the others launches.
 struct ProfScope {
   awe_plan* P;
   hipStream_t s;
   bool on;
   ProfScope(awe_plan* P_, int cls, hipStream_t s_, int levels = 1) : P(P_), s(s_) {
-    const int count = P->auto_fuse && P->store.mode == AWE_STORE_CHECKPOINT ? levels : 1;
+    const int count = P->auto_fuse ? levels : 1;
     if (P->prof_in_run) {  // counted into the enclosing run's interval
       P->prof_run_launches += count;
       on = false;
@@ -2005,7 +2005,7 @@ awe_status awe_born(awe_plan* P, const float* m, const float* q, const float* dm
       a.single = !two;
       if (a.ntiles > 0) {
         if ((st = check_step(P, T, a, n, two ? n + 1 : n, "Born step")) != AWE_OK) return st;
-        ProfScope ps(P, 2, s);
+        ProfScope ps(P, 2, s, two ? 2 : 1);
         if (P->ndim == 3) AWE_HIP(awe::launch_born3d(a, T.ty, T.bz, s));
         else if (fuse) AWE_HIP(awe::launch_born2d2(a, T.tz, s));
         else AWE_HIP(awe::launch_born2d(a, T.tz, s));

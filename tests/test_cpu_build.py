@@ -220,3 +220,20 @@ def test_tune_cache_entries_of_other_kernels_are_not_applied_on_the_cpu_build(em
     assert r.returncode == 0, r.stderr[-4000:]
     res = json.loads(r.stdout.strip().splitlines()[-1])
     assert not res["applied"] and res["same"] and res["entries"], res
+
+
+def test_kernel_timing_counts_on_the_cpu_build(emu_lib):
+    """awe_profile_read: time levels for plans whose fusion mode is the default, whatever their storage and the
+    call; launches for plans whose mode was set."""
+    import driver
+    r = driver.run([os.path.join(EMU, "case_profile_counts.py")], emu_lib, timeout=600)
+    assert r.returncode == 0, r.stderr[-4000:]
+    res = json.loads(r.stdout.strip().splitlines()[-1])
+    print(res)
+    n, half = res["levels"], -(-res["levels"] // 2)
+    for name, fwd in (("full", n), ("bf16", n), ("checkpoint", res["advances"])):
+        for mode in ("default", "tiles", "0"):
+            assert res["counts"][f"{name} {mode}"] == [fwd, n, n], (name, mode)
+    assert res["counts"]["full 3"] == [half, half, half] and res["counts"]["bf16 3"] == [half, half, half]
+    assert res["counts"]["checkpoint 3"][2] == half and res["counts"]["checkpoint 3"][0] < res["advances"]
+    assert res["counts"]["full tuned"][0] == -(-n // 3)   # three levels per launch
