@@ -298,10 +298,8 @@ awe_status awe_checkpoint_schedule(int32_t nsteps, int32_t nslots, int32_t* acti
 
 /* Tile-shape autotuner (setup call, synchronous).  The plan has a launch shape for its forward
  * solves (and Born modelling) and one for its adjoint steps (reverse sweeps and awe_adjoint); the
- * autotuner chooses each separately.  Candidates: 2D 8, 16, 24 or 32 rows with two time levels per launch,
- * 24 rows with one and, for forward solves where a default plan takes them, 8, 16 or 24 rows with three (see
- * awe_plan_set_fusion; where the kept storage has no such launches, solves without it take them as a default plan
- * does); 3D bricks of 64 x 8 x 8 points (ty = 8, bz = 8, the
+ * autotuner chooses each separately.  Candidates: 2D 8, 16, 24 or 32 rows with two time levels per launch
+ * (three in forward solves where a default plan takes them) and 24 rows with one (see awe_plan_set_fusion); 3D bricks of 64 x 8 x 8 points (ty = 8, bz = 8, the
  * default) and 64 x {4, 8, 16} columns with z-blocks of the full depth, of 128, 64 or 32 planes, and of the
  * depth split evenly in 2 to 8 (rounded up to an even plane count).  The forward probe times the last
  * probe_steps forward levels of the sweep (storing
@@ -319,8 +317,7 @@ awe_status awe_checkpoint_schedule(int32_t nsteps, int32_t nslots, int32_t* acti
  * shot grouping and probe_steps.  A valid entry found there is put in effect without running
  * any probe (best_ms then returns the stored time); otherwise the probes run and the result is
  * added to the file.  The file is a JSON object with one entry per line,
- *   "key": {"fw": [tz, ty, bz], "rv": [tz, ty, bz], "fusion": f, "ms": t, "levels": n}
- * ("levels": 3 where forward solves take three levels per launch; it may be left out)
+ *   "key": {"fw": [tz, ty, bz], "rv": [tz, ty, bz], "fusion": f, "ms": t}
  * rewritten whole through a temporary file and a rename; lines of any other form are ignored
  * (and dropped at the next rewrite), and a file that cannot be written leaves the call's
  * result unaffected. */
@@ -356,7 +353,7 @@ awe_status awe_plan_set_tiles(awe_plan* plan, int32_t tz, int32_t ty, int32_t bz
  * AWE_FUSE_FORWARD for forward solves and Born modelling, AWE_FUSE_ADJOINT for reverse sweeps (0:
  * one level per launch everywhere).  Until this call or the autotuner sets it, a plan uses both, its
  * tile rows follow the size of the work, and forward solves of small surveys (without storage or with FULL
- * FP32 storage) advance three levels per launch; the autotuner may keep that, this call and
+ * FP32 storage) advance three levels per launch; the autotuner keeps that, this call and
  * awe_plan_set_tiles (forward) end it.  The two-level kernels serve every storage: forward solves
  * (a checkpoint advance of an odd number of levels begins with one level), Born modelling, reverse sweeps
  * and the paired reversals of a CHECKPOINT gradient.

@@ -95,8 +95,8 @@ struct awe_plan {
   // shapes not set by the caller or the autotuner follow default_shapes
   bool auto_rows[2] = {true, true};  // tile rows (2D) / column blocks (3D): forward, adjoint
   bool auto_fuse = true;
-  bool many = true;       // forward solves of few tiles take kManyLevels levels per launch (many_levels): default
-                          // shapes, or the autotuner's choice
+  bool many = true;       // forward solves of few tiles take kManyLevels levels per launch (many_levels), until the
+                          // caller sets their rows or the mode
   Tiling fw, rv;          // launch shapes of forward solves / adjoint steps
   Tiling fw2, rv2;        // their tables for the two-level kernels, whose tiles may be wider (rows: fw.tz, rv.tz)
   Tiling bn2;             // two-level Born modelling, where fw2's tiles are 128 columns wide
@@ -514,7 +514,8 @@ int fitting_rows(const awe_plan* P, int w, int rows, bool taller) {
 
 // Launch shapes of the directions the caller has not set, from the storage and the work of a launch.
 //
-// 2D: two levels per launch, which won at every size timed: one shot of 281 x 181 2.3 -> 1.2 ms forward;
+// 2D: two levels per launch, which won at every size timed (a reverse sweep without imaging over hundreds of short
+// windows excepted, where either is up to 5 % ahead): one shot of 281 x 181 2.3 -> 1.2 ms forward;
 // one shot of 730 x 421 (1200 samples) 10.6 -> 7.4 ms gradient; 24 shots of 592 x 336 (600 samples) 27.5 ->
 // 18; autograd pass with 16 checkpoints, 500 samples, 16 shots of 1104 x 592 63.3 -> 48.5, one of 730 x
 // 421 6.7 -> 4.8.
@@ -546,10 +547,15 @@ void default_shapes(awe_plan* P) {
                : n64 < 200 ? 8 : n64 < 800 ? 24 : fitting_rows(P, 64, 32, false);
 }
 
-// Tables of a tiling built and uploaded where calls use it, given back where none does.  mode_switch: the
-// shots and their groups are the tables' own, so tables of the right shape stay, as do those not used now.
-awe_status refresh(awe_plan* P, Tiling& T, bool used, bool inject, bool mode_switch) {
-  if (mode_switch && (!used || (T.dev && T.built == T.shape()))) return AWE_OK;
+// Which device tables a rebuild keeps.  kSameShape: the shot groups are those of the tables, so tables of the right
+// shape stay.  kModeSwitch: only the fusion mode changed; no table is given back either, so that a HIP graph
+// captured in one mode stays valid in another, and switching back builds nothing.
+enum class Keep { kNone, kSameShape, kModeSwitch };
+
+// Tables of a tiling built and uploaded where calls use it, given back where none does.
+awe_status refresh(awe_plan* P, Tiling& T, bool used, bool inject, Keep keep) {
+  if (keep != Keep::kNone && used && T.dev && T.built == T.shape()) return AWE_OK;
+  if (keep == Keep::kModeSwitch && !used) return AWE_OK;
   if (used) {
     const awe_status st = build_tiling(P, T, inject);
     return st != AWE_OK ? st : upload_tiling(P, T);
@@ -561,9 +567,8 @@ awe_status refresh(awe_plan* P, Tiling& T, bool used, bool inject, bool mode_swi
 
 // Shot groups and the tilings of the directions in `dirs` (bit 0 forward, bit 1 adjoint; the
 // groups change both, so a change of groups rebuilds both), built and uploaded: those of the kernels
-// the direction's calls can launch.  mode_switch: only the fusion mode changed.  Then no table is given back, so
-// that a HIP graph captured in one mode stays valid in another, and switching back builds nothing.
-awe_status rebuild(awe_plan* P, int dirs, bool mode_switch = false) {
+// the direction's calls can launch.
+awe_status rebuild(awe_plan* P, int dirs, Keep keep = Keep::kNone) {
   awe_status st = build_groups(P);
   if (st != AWE_OK) return st;
   default_shapes(P);
@@ -575,7 +580,7 @@ awe_status rebuild(awe_plan* P, int dirs, bool mode_switch = false) {
     two.tz = one.tz;
     const bool fused = fused_ok(P, bit);
     for (Tiling* T : {&one, &two})
-      if ((st = refresh(P, *T, (T == &two) == fused, bit == AWE_FUSE_ADJOINT, mode_switch)) != AWE_OK) return st;
+      if ((st = refresh(P, *T, (T == &two) == fused, bit == AWE_FUSE_ADJOINT, keep)) != AWE_OK) return st;
     // Born launches hold two fields, and 128-column tiles of both cost more in occupancy than they save:
     // 16 shots of 730 x 421 43.1 us per launch 128 wide at 24 rows, 39.5 64 wide at 32; 16 of 1104 x 592 108
     // and 103 at 24 and 32 rows; 4 of 730 x 421 (n64 = 864) 15.8 and 15.9.  800 windows of 12 x 250 130 us at 32
@@ -583,7 +588,7 @@ awe_status rebuild(awe_plan* P, int dirs, bool mode_switch = false) {
     if (bit == AWE_FUSE_FORWARD) {
       P->bn2.tx = 64;
       P->bn2.tz = !P->auto_rows[0] ? one.tz : fitting_rows(P, 64, tiles24(P, 64) < 1750 ? 24 : 32, true);
-      if ((st = refresh(P, P->bn2, fused && two.tx != 64, false, mode_switch)) != AWE_OK) return st;
+      if ((st = refresh(P, P->bn2, fused && two.tx != 64, false, keep)) != AWE_OK) return st;
     }
   }
   return AWE_OK;
@@ -832,12 +837,11 @@ awe_status step_adj2(awe_plan* P, awe::StepArgs& a, int n, hipStream_t s, bool s
   return AWE_OK;
 }
 
-// Does a forward solve take kManyLevels levels per launch?  Where the default or the autotuner says so, while the
-// tiles are 64 columns and at most 24 rows and, as PROBED plans have 8 rows at every size, few: launches of few
-// tiles, bound by their fixed cost.  us per level at two and
-// three levels per launch, with FP32 store: one shot of 281 x 181 2.04 and 1.84; of 730 x 421 2.77 and 2.53;
-// two of those (n64 = 432) 3.53 and 3.26; from n64 = 500 on the rows are 32 and the halo work, a third more
-// than at two levels, fills the chip.
+// Does a forward solve take kManyLevels levels per launch?  Default and tuned shapes only, while their tiles are 64
+// columns and at most 24 rows and, as PROBED plans have 8 rows at every size, few: launches of few tiles, bound by
+// their fixed cost.  us per level at two and three levels per launch, with FP32 store: one shot of 281 x 181 2.04
+// and 1.84; of 730 x 421 2.77 and 2.53; two of those (n64 = 432) 3.53 and 3.26; from n64 = 500 on the rows are 32
+// and the halo work, a third more than at two levels, fills the chip.
 bool many_levels(const awe_plan* P, int store) {
   return P->many && fused_ok(P, AWE_FUSE_FORWARD) && P->fw2.tx == 64 && P->fw2.tz < 32 &&
          tiles24(P, 64) < 500 && (store == awe::kStoreNone || store == awe::kStoreF32);
@@ -1009,12 +1013,10 @@ awe_status run_actions(awe_plan* P, awe::StepArgs& fa, awe::StepArgs& aa, size_t
 }
 
 // ---- autotuner result cache: a JSON object of "key": {"fw": [tz, ty, bz], "rv": [...],
-// "fusion": f, "ms": t, "levels": n} entries, one per line, in the file named by AWE_TUNE_CACHE ("levels", the
-// levels per launch of forward solves, may be left out: three only where it says so).
+// "fusion": f, "ms": t} entries, one per line, in the file named by AWE_TUNE_CACHE.
 struct TuneEntry {
   int fw[3], rv[3], fusion;
   double ms;
-  int levels;
 };
 
 // Generation of the step kernels and of the tuner's candidates, raised with every change of either: shapes timed on
@@ -1064,9 +1066,8 @@ std::map<std::string, TuneEntry> read_tune_cache(const char* path) {
   char line[2048], key[1024];
   while (std::fgets(line, sizeof line, f)) {
     TuneEntry e{};
-    if (std::sscanf(line, " \"%1023[^\"]\": {\"fw\": [%d, %d, %d], \"rv\": [%d, %d, %d], \"fusion\": %d, \"ms\": %lf, \"levels\": %d}",
-                    key, &e.fw[0], &e.fw[1], &e.fw[2], &e.rv[0], &e.rv[1], &e.rv[2], &e.fusion, &e.ms,
-                    &e.levels) >= 9)
+    if (std::sscanf(line, " \"%1023[^\"]\": {\"fw\": [%d, %d, %d], \"rv\": [%d, %d, %d], \"fusion\": %d, \"ms\": %lf}",
+                    key, &e.fw[0], &e.fw[1], &e.fw[2], &e.rv[0], &e.rv[1], &e.rv[2], &e.fusion, &e.ms) == 9)
       out[key] = e;
   }
   std::fclose(f);
@@ -1082,8 +1083,8 @@ void write_tune_cache(const char* path, const std::map<std::string, TuneEntry>& 
   std::fprintf(f, "{\n");
   size_t i = 0;
   for (const auto& [k, e] : entries)
-    std::fprintf(f, "  \"%s\": {\"fw\": [%d, %d, %d], \"rv\": [%d, %d, %d], \"fusion\": %d, \"ms\": %.6f, \"levels\": %d}%s\n",
-                 k.c_str(), e.fw[0], e.fw[1], e.fw[2], e.rv[0], e.rv[1], e.rv[2], e.fusion, e.ms, e.levels,
+    std::fprintf(f, "  \"%s\": {\"fw\": [%d, %d, %d], \"rv\": [%d, %d, %d], \"fusion\": %d, \"ms\": %.6f}%s\n",
+                 k.c_str(), e.fw[0], e.fw[1], e.fw[2], e.rv[0], e.rv[1], e.rv[2], e.fusion, e.ms,
                  ++i < entries.size() ? "," : "");
   std::fprintf(f, "}\n");
   const bool ok = std::fclose(f) == 0;
@@ -1107,7 +1108,7 @@ bool apply_tune_entry(awe_plan* P, const TuneEntry& e, awe_status* st) {
   P->rv.bz = e.rv[2];
   P->fuse2 = e.fusion;
   P->auto_fuse = P->auto_rows[0] = P->auto_rows[1] = false;
-  P->many = e.levels == awe::kManyLevels;
+  P->many = true;
   P->kept_ws = nullptr;
   *st = rebuild(P, 3);
   return true;
@@ -1421,7 +1422,10 @@ awe_status awe_plan_create(const awe_problem* prob, const awe_storage* store, aw
     return st;
   }
   // default launch shapes (the autotuner or awe_plan_set_tiles choose others): 2D by
-  // default_shapes; 3D bricks, the fastest at every size timed (see adj3b_kernel)
+  // default_shapes; 3D bricks, within 1 % of the fastest at every size timed (figures at the brick kernels).
+  // Born steps march over 8 planes with that shape.  us per level at 8 x 8, at the best longer z-block of 8 or 16
+  // rows, and at 8 x 128: 144^3 27, 32, 177; 200^3 80, 87, 210; 240^3 122, 123, 219; 336^3 322, 320, 320; 400^3 573,
+  // 547, 633; 500^3 1197, 1086, 1204
   P->fw.ty = P->rv.ty = 8;
   P->fw.bz = P->rv.bz = 8;
   if ((st = rebuild(P, 3)) != AWE_OK) {
@@ -1502,18 +1506,15 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
     }
   }
   P->auto_fuse = P->auto_rows[0] = P->auto_rows[1] = false;
+  P->many = true;
   // one candidate list per direction; the forward probe times forward levels only, the adjoint
   // probe adjoint levels only, so each direction keeps its own fastest shape
-  struct Cand { int tz, ty, bz, fuse, many; };
+  struct Cand { int tz, ty, bz, fuse; };
   std::vector<Cand> cands;
   if (P->ndim == 2) {
-    // one level per launch lost at every size timed (see default_shapes): its best shape stays in
-    for (int tz : {8, 16, 24, 32}) cands.push_back({tz, 8, 0, 1, 0});
-    cands.push_back({24, 8, 0, 0, 0});
-    // forward solves only, where many_levels holds; a checkpointed gradient's forward launches are advances, which
-    // do not take them
-    if (P->store.mode != AWE_STORE_CHECKPOINT)
-      for (int tz : {8, 16, 24}) cands.push_back({tz, 8, 0, 1, 1});
+    // one level per launch lost at nearly every size timed (see default_shapes): its best shape stays in
+    for (int tz : {8, 16, 24, 32}) cands.push_back({tz, 8, 0, 1});
+    cands.push_back({24, 8, 0, 0});
   } else {
     // z-blocks of the full depth, of fixed lengths, and of the depth split evenly into 2 to 8
     // (no short last block)
@@ -1524,9 +1525,9 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
       const int b = ((nz + k - 1) / k + 1) & ~1;
       if (b >= 16 && std::find(bzs.begin(), bzs.end(), b) == bzs.end()) bzs.push_back(b);
     }
-    cands.push_back({32, 8, 8, 0, 0});   // bricks
+    cands.push_back({32, 8, 8, 0});   // bricks
     for (int ty : {4, 8, 16})
-      for (int bz : bzs) cands.push_back({32, ty, bz, 0, 0});
+      for (int bz : bzs) cands.push_back({32, ty, bz, 0});
   }
   hipEvent_t e0, e1;
   AWE_HIP(hipEventCreate(&e0));
@@ -1553,7 +1554,6 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
                          : P->sd[0].acc >= 0 ? awe::kImgBuffers : awe::kImgNone;
   double best[2] = {1e300, 1e300};
   Cand win[2] = {cands[0], cands[0]};
-  bool many_timed = false;
   P->cur = 0;  // the probes time the first shot group
   auto fail_out = [&](awe_status e) {
     keep_ev.swap(P->prof_ev);
@@ -1569,11 +1569,7 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
       T.ty = c.ty;
       T.bz = c.bz;
       P->fuse2 = (P->fuse2 & ~bit) | (c.fuse ? bit : 0);
-      if (c.many && dir == 1) continue;
-      if ((st = rebuild(P, dir == 0 ? 1 : 2)) != AWE_OK) return fail_out(st);
-      P->many = c.many;
-      if (c.many && !many_levels(P, fkind)) continue;
-      many_timed |= c.many != 0;
+      if ((st = rebuild(P, dir == 0 ? 1 : 2, Keep::kSameShape)) != AWE_OK) return fail_out(st);
       if ((st = prepare(P, m, ws, true, true, s)) != AWE_OK) return fail_out(st);
       for (int i = 0; i < P->nshot; ++i) {
         if (P->sd[i].acc >= 0)
@@ -1602,14 +1598,17 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
       // untimed, or the candidate tried first would be timed with its first launch's set-up (3D bricks, the
       // first, then lost to slower marches now and then)
       const bool two = fused_ok(P, dir == 0 ? AWE_FUSE_FORWARD : AWE_FUSE_ADJOINT);
-      const int levels = c.many ? awe::kManyLevels : 1 + two;
+      // forward solves of few tiles run three levels (won at every such size timed, see many_levels); the forward
+      // launches of a checkpointed gradient are advances, which do not
+      const bool many = dir == 0 && P->store.mode != AWE_STORE_CHECKPOINT && many_levels(P, fkind);
+      const int levels = many ? awe::kManyLevels : 1 + two;
       const int k1 = P->ndim == 2 && fkind == awe::kStoreF32 ? awe::kStoreF32R : fkind;  // as forward_loop
       const int n0 = dir == 0 ? std::max(1, P->nsteps - std::max(probe, levels) + 1) : P->nsteps;
       auto in_probe = [&](int n) {
         return dir == 0 ? n + levels - 1 <= P->nsteps : n > P->nsteps - probe && n >= 2;
       };
       auto step = [&](int n) {
-        if (c.many) return step_fwdm(P, fa, n + levels - 1, 2 * ((n - n0) / levels & 1), fkind, s);
+        if (many) return step_fwdm(P, fa, n + levels - 1, 2 * ((n - n0) / levels & 1), fkind, s);
         return dir == 0 ? (two ? step_fwd2(P, fa, n, fkind, s) : step_fwd(P, fa, n, k1, s))
                         : (two ? step_adj2(P, aa, n, s) : step_adj(P, aa, n, s));
       };
@@ -1641,10 +1640,9 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
   P->rv.ty = win[1].ty;
   P->rv.bz = win[1].bz;
   P->fuse2 = (win[0].fuse ? AWE_FUSE_FORWARD : 0) | (win[1].fuse ? AWE_FUSE_ADJOINT : 0);
-  P->many = win[0].many || !many_timed;   // not timed with the storage kept: solves without it follow the rule
   for (double& b : best)
     if (b >= 1e200) b = 0.0;   // nothing to time
-  if ((st = rebuild(P, 3)) != AWE_OK) return st;
+  if ((st = rebuild(P, 3, Keep::kSameShape)) != AWE_OK) return st;
   if (chosen) {
     chosen[0] = P->fw.tz;
     chosen[1] = P->fw.ty;
@@ -1655,7 +1653,7 @@ awe_status awe_plan_autotune(awe_plan* P, const float* m, const float* q, const 
   if (cache && *cache) {
     auto entries = read_tune_cache(cache);
     entries[key] = TuneEntry{{P->fw.tz, P->fw.ty, P->fw.bz}, {P->rv.tz, P->rv.ty, P->rv.bz}, P->fuse2,
-                             best[0] + best[1], P->many ? awe::kManyLevels : 0};
+                             best[0] + best[1]};
     write_tune_cache(cache, entries);
   }
   return AWE_OK;
@@ -1734,7 +1732,7 @@ awe_status awe_plan_set_fusion(awe_plan* P, int32_t mode) {
       if (st != AWE_OK) return st;
     }
   }
-  const awe_status st = rebuild(P, (mode ^ before) & AWE_FUSE_BOTH, true);
+  const awe_status st = rebuild(P, (mode ^ before) & AWE_FUSE_BOTH, Keep::kModeSwitch);
   if (st != AWE_OK) {   // the tables of the mode before are still there
     P->fuse2 = before;
     P->auto_fuse = auto_before;

@@ -44,13 +44,9 @@ def main():
     with tempfile.TemporaryDirectory() as tmp:
         path = os.environ["AWE_TUNE_CACHE"] = os.path.join(tmp, "tune.json")
         n1, _ = forward(B.Storage(), 12)
-        key, e = next(iter(json.load(open(path)).items()))
         n2, d = forward(B.Storage(), 12)          # from the file
-        del e["levels"]
-        with open(path, "w") as f:
-            f.write('{\n  "%s": %s\n}\n' % (key, json.dumps(e)))
-        n3, _ = forward(B.Storage(), 12)          # an entry without the number: two levels
-        res["cache"] = [n1, n2, n3]
+        res["cache"] = [n1, n2, len(json.load(open(path)))]
+        res["bitwise"].append(bool(np.array_equal(d, ref)))
         del os.environ["AWE_TUNE_CACHE"]
     print(json.dumps(res), flush=True)
 
