@@ -1067,8 +1067,9 @@ def bench_c5(args):
     if run.tiles and roof.get("kernel") == names["adjoint"]:
         adj = run.tiles["adjoint"]
         img = {A.PREC_FP32: 1, A.PREC_BF16: 3, A.PREC_FP16: 4}[prec]
-        roof["traffic"] = traffic_record("c5_3d", "kernels3d.hip", f"adj3d_kernel<{adj['ty']}, {img}>",
-                                         run.launch_points, {"ty": adj["ty"], "bz": adj["bz"]})
+        kernel = f"adj3b_kernel<{img}, true>" if (adj["ty"], adj["bz"]) == (8, 8) else f"adj3d_kernel<{adj['ty']}, {img}>"
+        roof["traffic"] = traffic_record("c5_3d", "kernels3d.hip", kernel, run.launch_points,
+                                         {"ty": adj["ty"], "bz": adj["bz"]})
         roof["traffic_counter"] = TRAFFIC_NOTE
     out = base_line(args, wl, run.points / sec / 1e9, sec, {
         "config": {"workload": f"{wl.name}: {wl.description}", "grid": list(wl.comp_shape(0)),

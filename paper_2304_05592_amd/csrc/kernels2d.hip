@@ -497,16 +497,15 @@ __global__ __launch_bounds__(T2<TZ>::NT) void born2d_kernel(StepArgs a) {
 }
 
 // ------------------------------------------------------------------------------ two steps per launch
-// A tile of TZ rows x 128 columns.  Level n-1 is staged with an 8-cell halo (LDS L1); the first
+// A tile of TZ rows x 64 V columns (V = 1, 2).  Level n-1 is staged with an 8-cell halo (LDS L1); the first
 // step computes level n on the tile plus a 4-cell halo (LDS LE: everything the second step's
 // stencil needs), the second step computes level n+1 (forward) or n-1 (adjoint) on the tile.  Both
 // steps do exactly the arithmetic of the one-step kernels, in the same order, so results are
 // bitwise identical; HBM traffic per two steps falls from 2 x (3 reads + 1 write) to 3 reads +
 // 2 writes.
 //
-// These kernels issue vector instructions most of their time (a launch without a store, its fields
-// in the last-level cache, ran at the vector units' rate with 93 lane-operations per point and
-// level), so the work per point is cut: a lane owns V adjacent columns (V = 2: 8-byte global and LDS
+// Vector issue is most of a forward launch's time (at one wave instruction per cycle and compute unit 61 % of
+// one with FP32 store, 70 % without) and 45 % of a reverse launch's, so the work per point is cut: a lane owns V adjacent columns (V = 2: 8-byte global and LDS
 // accesses, one set of address and row work for two points) and RA or RB consecutive rows, whose
 // z-neighbours it reads from LDS once (N + 8 reads for N rows instead of 9 N); along x a difference
 // u(b) - u(a) that serves the stencils of two of its points is formed once.  A row of the tile is one
@@ -516,7 +515,10 @@ __global__ __launch_bounds__(T2<TZ>::NT) void born2d_kernel(StepArgs a) {
 // chain of a small launch; wide_tiles holds the rule.
 // Measured, 16 shots of 730 x 421, us per launch of two levels, against one column and row at a time:
 // forward without store 23.4 -> 21.3 (V = 2), with FP32 store 24.7 -> 23.3, reverse with imaging 41.4 ->
-// 38.0; one shot of 281 x 181, against one level per launch twice: forward 7.4 -> 4.0.
+// 38.0; one shot of 281 x 181, against one level per launch twice: forward 7.4 -> 4.0.  Lane-operations per
+// point and level with the halos' (SQ_INSTS_VALU, 16 shots of 730 x 421): forward with FP32 store 79 -> 60,
+// reverse with imaging 93 -> 68.
+
 // V adjacent columns of a lane.
 template <int V>
 struct VecOf {
@@ -791,8 +793,9 @@ __device__ __forceinline__ void gather(const StepArgs& a, const TileDev& T, cons
 
 // Forward: levels k and k+1 (k = step - off); SK = kStoreNone, kStoreF32, kStoreBF16 / kStoreFP16 or
 // kStoreProbe (both levels' increments added to the probe sums in one FP64 read-modify-write, level k
-// first), or kStoreSlot (a checkpoint advance: reads a slot by reference, the state reached may go into one).  A 16-bit store takes the levels k-2 and k-1, whose scales the launch before finished, from the
-// values the first step has in registers, and this launch's maxima go to the levels' slots: the gradient of
+// first), or kStoreSlot (a checkpoint advance: reads a slot by reference, the state reached may go into one).
+// A 16-bit store takes the levels k-2 and k-1, whose scales the launch before finished, from the values the
+// first step has in registers, and this launch's maxima go to the levels' slots: the gradient of
 // 3 shots of 261 x 185 (501 samples) 4.94 -> 3.27 ms against one level per launch.
 // a.single: level k alone.
 template <int TZ, int V, int SK>
@@ -1118,8 +1121,8 @@ __device__ __forceinline__ void inject(const StepArgs& a, const InjPoint* pts, i
 
 // Adjoint: levels j and j-1 (j = step - off), receiver residual injected in both steps,
 // imaging of both steps accumulated (in step order) into one FP64 read-modify-write.
-// IMG = kImgNone, kImgFull32, kImgFullBF16, kImgFullFP16, kImgBuffers or kImgProbe (both levels added to the probe sums A_j in
-// one FP64 read-modify-write, level j first).  a.single: level j alone.
+// IMG = kImgNone, kImgFull32, kImgFullBF16, kImgFullFP16, kImgBuffers or kImgProbe (both levels added to the
+// probe sums A_j in one FP64 read-modify-write, level j first).  a.single: level j alone.
 //
 // The injected residual takes no LDS of its own: the first step's lies where the point's new level
 // goes (LE), which its own thread reads before it writes; the second step's in L1, of which the

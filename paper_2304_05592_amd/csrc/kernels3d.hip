@@ -2,7 +2,8 @@
 // receiver injection.
 //
 // Two forms: bricks of 64 x 8 x 8 points (shape ty = 8, bz = 8, the default of forward and adjoint
-// steps; described at their kernels) and the z-march of every other shape and of Born steps:
+// steps, probe sums included; described at their kernels) and the z-march of every other shape and of
+// Born steps, which march over blocks of 8 planes where the shape is the bricks':
 //
 // A workgroup (4 x wave64) owns a 64 x TY column block of (x, y) and marches along z over
 // [z0, z0 + bz).  Each thread keeps a 9-deep register queue of its columns' values along z
@@ -507,14 +508,19 @@ __global__ void inj3d_kernel(StepArgs a, int first, int count) {
 
 // ------------------------------------------------------------------------------ bricks
 // Forward and adjoint steps on bricks of 64 x 8 x 8 points: the march above needs two to three
-// microseconds per plane when there are too few blocks to hide its barrier and load latency, so a
-// grid that cannot fill the chip with long marches is cut into bricks instead.  A workgroup (8
+// microseconds per plane when there are too few blocks to hide its barrier and load latency.  A workgroup (8
 // waves) issues every load of its brick at once - wave w the columns of y-row w over 16 planes,
 // one halo row of the 8 planes and the x-halo of plane w - and then computes its 8 planes from LDS
 // (x and y neighbours) and registers (z neighbours) behind a single barrier.  The price is the halo
 // re-read (u^{k-1} 3.1 times, from the caches).  The adjoint injects its residual here as well, with
 // the roundings of inj3d_kernel, instead of in a launch of its own.
-// Measured, us per level, march (best of all blocks) -> bricks: see default_shapes.
+// Measured, us per level, best march of 4, 8, 16 rows and z-blocks of 32 planes up to the depth -> bricks:
+//            forward        with BF16 store   reverse from BF16 store
+//   120^3   33.5 ->   9.2     34.9 ->  12.0      28.0 ->  14.2
+//   144^3   36.5 ->  13.5     39.0 ->  19.8      35.3 ->  23.1
+//   240^3   67.5 ->  43.7     76.3 ->  55.1     100.5 ->  90.9
+//   336^3  127.8 -> 120.5    148.6 -> 149.4     247.9 -> 234.5
+//   400^3  240.5 -> 224.2    276.9 -> 270.5     474.4 -> 445.6
 constexpr int kBY = 8, kBZ = 8;           // brick rows (one per wave) and planes
 constexpr int kBT = 64 * kBY;
 constexpr int kBH = kBY + 2 * kHalo;      // 16 LDS rows
