@@ -361,7 +361,8 @@ awe_status awe_plan_set_tiles(awe_plan* plan, int32_t tz, int32_t ty, int32_t bz
  * FP64 sum in the order two launches would), also where the mode changes between a kept forward and its
  * awe_backward.  Two levels per launch need tiles of 8, 16, 24 or 32 rows (16 or 32 are set
  * otherwise, as by awe_plan_set_tiles_dir).  Else the call keeps the tables of every mode it has seen (until the
- * shapes or the groups change) and any kept forward, and a HIP graph captured before stays valid.
+ * shapes or the groups change) and any kept forward, and a HIP graph captured before stays valid.  The first call
+ * with a mode builds its tables (a device allocation and a copy: not inside a stream capture).
  * Errors: INVALID_ARG (mode outside 0..3), HIP. */
 enum { AWE_FUSE_NONE = 0, AWE_FUSE_FORWARD = 1, AWE_FUSE_ADJOINT = 2, AWE_FUSE_BOTH = 3 };
 awe_status awe_plan_set_fusion(awe_plan* plan, int32_t mode);
